@@ -130,6 +130,76 @@ void pool_free(int device, void *p, size_t bytes) {
   g_pool.push_back({device, p, bytes});
 }
 
+// ---- pinned host staging ------------------------------------------------------------
+// Blocks of pinned host memory that kernels write results into.  A call takes one for
+// itself and hands it back after its stream has drained, so a block never has two users,
+// whatever the threads and streams.  At most kStageKeep free blocks are kept (pinning takes
+// longer than the download it serves); snn_memory_cache_release returns them.
+constexpr size_t kStageMinBytes = 1u << 20, kStageMaxBytes = 32u << 20;
+constexpr size_t kStageKeep = 4;
+struct StageBlock {
+  void *p = nullptr;
+  size_t bytes = 0;
+};
+std::mutex g_stage_mutex;
+std::vector<StageBlock> g_stage;  // free blocks
+
+void stage_release() {
+  std::vector<StageBlock> drop;
+  {
+    std::lock_guard<std::mutex> lock(g_stage_mutex);
+    drop.swap(g_stage);
+  }
+  for (const StageBlock &b : drop) (void)hipHostFree(b.p);
+}
+
+// A block of at least `want` bytes, `want` clamped to [kStageMinBytes, kStageMaxBytes].
+class Stage {
+ public:
+  explicit Stage(size_t want) {
+    want = std::min(std::max(want, kStageMinBytes), kStageMaxBytes);
+    {
+      std::lock_guard<std::mutex> lock(g_stage_mutex);
+      for (size_t k = 0; k < g_stage.size(); ++k) {
+        if (g_stage[k].bytes < want) continue;
+        b_ = g_stage[k];
+        g_stage.erase(g_stage.begin() + (std::ptrdiff_t)k);
+        return;
+      }
+    }
+    size_t bytes = kStageMinBytes;
+    while (bytes < want) bytes *= 2;
+    if (hipHostMalloc(&b_.p, bytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      fail(SNN_E_OOM, "pinned host allocation of " + std::to_string(bytes) + " bytes failed");
+    }
+    b_.bytes = bytes;
+  }
+  ~Stage() {
+    StageBlock drop = b_;
+    try {
+      std::lock_guard<std::mutex> lock(g_stage_mutex);
+      if (g_stage.size() < kStageKeep) {
+        g_stage.push_back(b_);
+        drop.p = nullptr;
+      } else {
+        // keep the larger blocks
+        for (StageBlock &k : g_stage)
+          if (k.bytes < drop.bytes) std::swap(k, drop);
+      }
+    } catch (...) {
+    }
+    if (drop.p) (void)hipHostFree(drop.p);
+  }
+  Stage(const Stage &) = delete;
+  Stage &operator=(const Stage &) = delete;
+  unsigned char *data() const { return static_cast<unsigned char *>(b_.p); }
+  size_t bytes() const { return b_.bytes; }
+
+ private:
+  StageBlock b_;
+};
+
 void *dev_alloc(snn_network *net, size_t bytes) {
   if (bytes == 0) bytes = 16;
   bytes = (bytes + 255) & ~(size_t)255;
@@ -548,7 +618,10 @@ void build(snn_network *net) {
   net->queue_stride = snn::kQueueGroups * net->group_cap;
   net->queue = dev_array<int32_t>(net, (size_t)net->slots * net->queue_stride);
   net->qlen = dev_array<uint32_t>(net, (size_t)net->slots * snn::kQueueGroups * snn::kQlenStride);
-  net->raster = dev_array<uint64_t>(net, (size_t)net->raster_cap * net->words);
+  // the raster ring, and behind it the offsets scratch of the spike download
+  const size_t ring_words = (size_t)net->raster_cap * net->words;
+  net->raster = dev_array<uint64_t>(net, ring_words + snn::raster_units(ring_words, nullptr));
+  net->raster_offset = net->raster + ring_words;
   net->d_table32 = dev_array<uint32_t>(net, snn::kTableCap);
   net->d_guide = dev_array<uint16_t>(net, snn::kGuideBuckets);
   net->ctl = dev_array<snn::Ctl>(net, 1);
@@ -911,7 +984,52 @@ void copy_raster_rows(snn_network *net, uint64_t t0, uint64_t t1, uint64_t *out)
 }
 
 
-
+// The spikes of steps [t0, t1) as sorted pairs in the caller's arrays, their number in
+// *n_spikes.  Device kernels find the pairs and write them into pinned staging, in pieces if
+// they do not fit one block; the caller's arrays are written only once the count is known
+// to fit them.
+void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps, uint32_t *ids,
+                    uint64_t capacity, uint64_t *n_spikes) {
+  *n_spikes = 0;
+  if (t0 == t1) return;
+  constexpr size_t kHead = 256;  // the count, on a line of its own
+  const size_t pair = 2 * sizeof(uint32_t);
+  // (the clamp keeps the product in range for any capacity)
+  Stage stage(kHead + std::min<uint64_t>(capacity, kStageMaxBytes / pair) * pair);
+  const uint64_t piece = (stage.bytes() - kHead) / pair;
+  snn::RasterArgs a{};
+  a.raster = net->raster;
+  a.ring_words = (uint64_t)net->raster_cap * net->words;
+  a.first_word = t0 % net->raster_cap * net->words;
+  a.total_words = (t1 - t0) * net->words;
+  a.t_begin = t0;
+  a.offset = net->raster_offset;
+  a.words = net->words;
+  a.count = reinterpret_cast<uint64_t *>(stage.data());
+  a.steps = reinterpret_cast<uint32_t *>(stage.data() + kHead);
+  a.ids = a.steps + piece;
+  a.out_cap = steps && ids ? std::min(capacity, piece) : 0;
+  struct Drained {  // the block goes back only after nothing writes to it any more
+    hipStream_t s;
+    ~Drained() { (void)hipStreamSynchronize(s); }
+  } drained{net->stream};
+  check(snn::launch_raster_pairs(a, net->stream), "raster pairs");
+  sync(net);
+  const uint64_t count = *a.count;
+  *n_spikes = count;
+  if (count > capacity) fail(SNN_E_OVERFLOW, "raster holds " + std::to_string(count) + " spikes");
+  if (count && (!steps || !ids)) fail(SNN_E_INVALID, "null output arrays");
+  for (uint64_t lo = 0; lo < count; lo += piece) {
+    if (lo) {
+      a.out_lo = lo;
+      check(snn::launch_raster_pairs(a, net->stream), "raster pairs");
+      sync(net);
+    }
+    const size_t part = (size_t)std::min(piece, count - lo);
+    std::memcpy(steps + lo, a.steps, part * sizeof(uint32_t));
+    std::memcpy(ids + lo, a.ids, part * sizeof(uint32_t));
+  }
+}
 
 // ---- delivery reconfiguration, timing and autotuning --------------------------------
 void dev_free(snn_network *net, void *p) {
@@ -1743,7 +1861,10 @@ snn_status snn_memory_cache_stats(int device, uint64_t *bytes, uint64_t *blocks,
 }
 
 snn_status snn_memory_cache_release(int device) {
-  return guarded([&] { pool_release(device); });
+  return guarded([&] {
+    pool_release(device);
+    stage_release();
+  });
 }
 
 snn_status snn_sync(snn_network *net) {
@@ -1766,25 +1887,7 @@ snn_status snn_get_raster(snn_network *net, uint64_t t_begin, uint64_t t_end, ui
   return guarded([&] {
     if (!net || !n_spikes) fail(SNN_E_INVALID, "null argument");
     raster_range_check(net, t_begin, t_end);
-    std::vector<uint64_t> rows((size_t)(t_end - t_begin) * net->words);
-    copy_raster_rows(net, t_begin, t_end, rows.data());
-    uint64_t count = 0;
-    for (uint64_t w : rows) count += (uint64_t)__builtin_popcountll(w);
-    *n_spikes = count;
-    if (count > capacity) fail(SNN_E_OVERFLOW, "raster holds " + std::to_string(count) + " spikes");
-    if (count && (!steps || !ids)) fail(SNN_E_INVALID, "null output arrays");
-    uint64_t k = 0;
-    for (uint64_t t = t_begin; t < t_end; ++t)
-      for (uint32_t w = 0; w < net->words; ++w) {
-        uint64_t bits = rows[(t - t_begin) * net->words + w];
-        while (bits) {
-          const int b = __builtin_ctzll(bits);
-          bits &= bits - 1;
-          steps[k] = (uint32_t)t;
-          ids[k] = w * 64u + (uint32_t)b;
-          ++k;
-        }
-      }
+    download_pairs(net, t_begin, t_end, steps, ids, capacity, n_spikes);
   });
 }
 

@@ -77,6 +77,8 @@ class Network:
     (allocate through torch's caching allocator and run on torch's current stream).
     """
 
+    _spike_hint = 1024  # entries allocated for the next spike download
+
     def __init__(self, spec, raster_steps=1024, window=0, delivery="auto", tiles=0, block=0,
                  grid=0, synapse_weights="auto", plasticity="eager", torch_memory=True, device=0):
         lib = L.load()
@@ -180,14 +182,21 @@ class Network:
     def spikes(self, t0, t1):
         """(steps, ids) sorted by step then id."""
         n = C.c_uint64()
-        st = self._lib.snn_get_raster(self._h, t0, t1, None, None, 0, C.byref(n))
-        if st not in (L.SNN_OK, L.SNN_E_OVERFLOW):
-            L.check(st)
-        steps = np.zeros(n.value, dtype=np.uint32)
-        ids = np.zeros(n.value, dtype=np.uint32)
-        L.check(self._lib.snn_get_raster(self._h, t0, t1, _ptr(steps), _ptr(ids), n.value,
-                                         C.byref(n)))
-        return steps, ids
+        # one call suffices where the arrays hold the range's spikes: they are sized from
+        # the latest download, and grown to the count that a call finds beyond them
+        cap = self._spike_hint
+        while True:
+            steps, ids = np.empty(cap, np.uint32), np.empty(cap, np.uint32)
+            st = self._lib.snn_get_raster(self._h, t0, t1, _ptr(steps), _ptr(ids), cap, C.byref(n))
+            if st != L.SNN_E_OVERFLOW or n.value <= cap:
+                break
+            cap = n.value
+        L.check(st)
+        count = n.value
+        self._spike_hint = max(1024, count + count // 4)
+        if 2 * count < cap:  # hold no more memory than the spikes need
+            return steps[:count].copy(), ids[:count].copy()
+        return steps[:count], ids[:count]
 
     def state(self, queues=False, weights=False):
         inf = self.info()

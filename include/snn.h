@@ -210,7 +210,9 @@ snn_status snn_step(snn_network *net);
 /* Advance n_steps steps: the loop of repeated step() calls that drives a network in
  * the paper's interface (Sec. III-B, the listing that ends in `while (true)
  * net.step()`), each step being the Fig. 1 pipeline.  Launches are grouped into windows
- * of up to `window` steps and replayed from a captured HIP graph where possible.  The
+ * of up to `window` steps and replayed from a captured HIP graph where possible; a small
+ * static network without drive whose delivery is left to AUTO (and whose window, tiles,
+ * block and grid are 0) is stepped by one persistent launch instead.  The
  * result is identical to n_steps calls of snn_step.  Asynchronous.  SNN_E_STATE for a
  * batch member; SNN_E_HIP if a launch fails. */
 snn_status snn_run(snn_network *net, uint32_t n_steps);

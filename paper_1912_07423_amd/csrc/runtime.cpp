@@ -464,6 +464,8 @@ void alloc_tile_offsets(snn_network *net) {
         "tile index");
 }
 
+bool choose_solo(const snn_network *net);
+
 void build(snn_network *net) {
   validate_and_derive(net);
   choose_schedule(net);
@@ -602,6 +604,7 @@ void build(snn_network *net) {
   }
 
   choose_delivery(net);
+  net->solo = choose_solo(net);
   if (net->delivery == SNN_DELIVERY_TILED) alloc_tile_offsets(net);
   check(hipEventRecord(ev[5], s), "hipEventRecord");
 
@@ -900,6 +903,104 @@ void issue_window(snn_network *net, uint32_t steps) {
   net->t_host += steps;
 }
 
+// ---- the persistent one-workgroup form -----------------------------------------------
+// Drive thresholds a 32-bit word can reach.
+uint32_t drive_thresholds(const snn_network *net) {
+  uint32_t below = 0;
+  while (below < net->table_len && net->table[below] < (1ull << 32)) ++below;
+  return below;
+}
+
+uint32_t lanes_shift_for(double degree, uint32_t degree_div) {
+  const double want = degree / (double)std::max(1u, degree_div);
+  uint32_t sh = 0;
+  while (sh < 6 && (double)(1u << sh) < want) ++sh;
+  return sh;
+}
+
+// A static network as the persistent kernels see it.
+snn::BatchNet batch_net(snn_network *m) {
+  snn::BatchNet d{};
+  d.row_ptr = m->row_ptr;
+  d.col = m->col;
+  d.w_q16 = m->w_q16;
+  d.w_src = m->w_src;
+  d.v = m->v;
+  d.ref = m->ref;
+  d.input = m->input;
+  d.queue = m->queue;
+  d.qlen = m->qlen;
+  d.raster = m->raster;
+  d.table32 = m->d_table32;
+  d.ctl = m->ctl;
+  d.n = m->n;
+  d.words = m->words;
+  d.delay = m->delay;
+  d.raster_cap = m->raster_cap;
+  d.slots = m->slots;
+  d.queue_stride = m->queue_stride;
+  d.group_cap = m->group_cap;
+  d.window = m->window;
+  d.below = drive_thresholds(m);
+  d.lanes_shift = lanes_shift_for(m->n ? (double)m->nnz / m->n : 0.0, 4);
+  d.key0 = m->key0;
+  d.key1 = m->key1;
+  d.alpha = m->alpha;
+  d.v_inf = m->v_inf;
+  d.v_th = m->v_th;
+  d.v_reset = m->v_reset;
+  d.ref_steps = m->ref_steps;
+  d.w_ext_q16 = m->w_ext_q16;
+  return d;
+}
+
+// LDS of a persistent launch whose largest network needs `need` bytes and has n neurons.
+snn::LdsPlan lds_plan(size_t need, uint32_t n, size_t limit) {
+  snn::LdsPlan r{};
+  r.q_cap = (uint32_t)std::min<size_t>(snn::kBatchQueueMax, (limit - need) / 12);
+  r.words = (uint32_t)std::min(limit / 4, need / 4 + 3 * (size_t)r.q_cap + n + 1);
+  return r;
+}
+
+size_t solo_need(const snn_network *net) { return (size_t)net->delay * net->n * 4; }
+
+// Whether snn_run steps the network by the persistent kernel: a small static network without
+// drive, with nothing about its delivery chosen by the caller.  A step of the pipeline costs
+// two launches per window of `delay` steps, whatever the size: 6.6-8.9 us with the atomic
+// delivery (1,000-40,000 neurons) and 9.6-11.2 us with the tiled one.  A persistent step
+// costs about 0.9 us, 0.105 us per 1,000 neurons and 1 us per 8,200 synaptic events: 0.9 us
+// at 1,000 neurons, 1.4 at 4,000, 1.9 at 8,000, 3.1 at 16,000, 5.0 at 32,000, against 6.6,
+// 7.9, 8.3, 8.6 and 10.9 us (delay 1).  The rule takes 15 Hz for the unknown rate: at 20 mV
+// of background, 32,000 neurons and 22,500 events a step took 7.8 against 11.4 us, but
+// 40,000 neurons and 80,000 events 14.7 against 11.6.
+bool choose_solo(const snn_network *net) {
+  if (net->plastic || net->owner || net->prm.delivery != SNN_DELIVERY_AUTO || net->prm.window || net->prm.tiles ||
+      net->prm.block || net->prm.grid)
+    return false;
+  if (net->n > snn::kSoloMaxNeurons || net->n_inbuf != net->delay || drive_thresholds(net)) return false;
+  if (solo_need(net) + snn::kBatchStaticLds > net->lds_limit) return false;
+  const double events = (double)net->nnz * 15.0 * net->prm.dt_ms * 1e-3;
+  const double step_us = 0.9 + 0.105e-3 * net->n + events / 8200.0;
+  return step_us * net->delay <= (net->delivery == SNN_DELIVERY_TILED ? 9.6 : 6.6);
+}
+
+// Steps per persistent launch: long enough to amortise the launch and the state's way in
+// and out, short enough that a launch stays well below a tenth of a second.
+constexpr uint32_t kMaxChunk = 1u << 14;
+
+void run_solo(snn_network *net, uint64_t n_steps) {
+  const snn::BatchNet d = batch_net(net);
+  const snn::LdsPlan lds = lds_plan(solo_need(net), net->n, net->lds_limit - snn::kBatchStaticLds);
+  while (n_steps > 0) {
+    const uint32_t chunk = (uint32_t)std::min<uint64_t>(n_steps, kMaxChunk);
+    check(snn::launch_solo(d, chunk, snn::kBatchCommit | snn::kBatchWriteRaster | snn::kBatchQueues, lds,
+                           net->stream),
+          "persistent launch");
+    net->t_host += chunk;
+    n_steps -= chunk;
+  }
+}
+
 void ensure_graph(snn_network *net) {
   if (net->graph) return;
   const uint32_t windows = std::max(1u, (64u + net->window - 1) / net->window);
@@ -924,6 +1025,7 @@ void ensure_graph(snn_network *net) {
 }
 
 void run(snn_network *net, uint64_t n_steps) {
+  if (net->solo && !net->profiling && n_steps > 1) return run_solo(net, n_steps);
   while (n_steps > 0) {
     if (!net->profiling && n_steps >= 64 && net->stream) {
       ensure_graph(net);
@@ -1057,11 +1159,11 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     uint32_t p_delivery, p_tiles, p_block, p_grid, delivery, block, tiles, tile_size, grid;
     void *tile_off;
     uint16_t *col16;
-    bool tile_off16;
+    bool tile_off16, solo;
   };
   const Saved old{net->prm.delivery, net->prm.tiles, net->prm.block, net->prm.grid, net->delivery,
                   net->block,        net->tiles,     net->tile_size, net->grid,     net->tile_off,
-                  net->col16,        net->tile_off16};
+                  net->col16,        net->tile_off16, net->solo};
   try {
     net->prm.delivery = delivery;
     net->prm.tiles = tiles;
@@ -1069,6 +1171,7 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->prm.grid = grid;
     net->delivery = delivery;
     choose_delivery(net);
+    net->solo = choose_solo(net);
     if (net->delivery == SNN_DELIVERY_TILED) {
       net->tile_off = nullptr;  // a fresh index; the old one stays valid until this succeeds
       alloc_tile_offsets(net);  // reuses col16 when it exists (it does not depend on the tiling)
@@ -1089,6 +1192,7 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->tiles = old.tiles;
     net->tile_size = old.tile_size;
     net->grid = old.grid;
+    net->solo = old.solo;
     net->tile_off = old.tile_off;
     net->col16 = old.col16;
     net->tile_off16 = old.tile_off16;
@@ -1383,18 +1487,12 @@ struct snn_batch {
   uint32_t n_max = 0;
   size_t lds_need = 0;               // dynamic LDS of the largest member
   uint32_t lds_limit = 0;
+  size_t lds_budget = 0;             // dynamic LDS a launch may use
   snn_batch_tuning tuning{};
   std::vector<std::pair<uint32_t, hipGraphExec_t>> graphs;  // by steps per launch
 };
 
 namespace {
-
-uint32_t lanes_shift_for(double degree, uint32_t degree_div) {
-  const double want = degree / (double)std::max(1u, degree_div);
-  uint32_t sh = 0;
-  while (sh < 6 && (double)(1u << sh) < want) ++sh;
-  return sh;
-}
 
 void batch_clear_graphs(snn_batch *b) {
   for (auto &g : b->graphs) (void)hipGraphExecDestroy(g.second);
@@ -1420,8 +1518,9 @@ void batch_apply_tuning(snn_batch *b, const snn_batch_tuning &t) {
 void batch_launch(snn_batch *b, uint32_t steps, uint32_t flags) {
   for (const snn::BatchNet &d : b->desc)
     if (d.below) flags |= snn::kBatchDrive;
+  const snn::LdsPlan lds = lds_plan(b->lds_need, b->n_max, b->lds_budget);
   check(snn::launch_batch(b->d_desc, b->d_order, (uint32_t)b->nets.size(), steps, b->tuning.block,
-                          b->tuning.per_lane, flags, b->lds_need, b->pool.stream), "batch launch");
+                          b->tuning.per_lane, flags, lds, b->pool.stream), "batch launch");
 }
 
 hipGraphExec_t batch_graph(snn_batch *b, uint32_t steps) {
@@ -1450,7 +1549,6 @@ hipGraphExec_t batch_graph(snn_batch *b, uint32_t steps) {
 // Each launch advances every member by `chunk` steps; one kernel node per launch,
 // replayed from a graph captured once per chunk length.
 void batch_run(snn_batch *b, uint64_t n_steps) {
-  constexpr uint32_t kMaxChunk = 1u << 14;
   while (n_steps > 0) {
     const uint32_t chunk = (uint32_t)std::min<uint64_t>(n_steps, kMaxChunk);
     check(hipGraphLaunch(batch_graph(b, chunk), b->pool.stream), "graph launch");
@@ -1477,7 +1575,7 @@ void build_batch(snn_batch *b, const snn_batch_member *members, uint32_t n_nets,
   int lds_max = 0;
   check(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, b->pool.device),
         "LDS limit");
-  b->lds_limit = (uint32_t)std::max(0, lds_max - 64);  // the kernel's static LDS
+  b->lds_limit = (uint32_t)std::max(0, lds_max - (int)snn::kBatchStaticLds);
   for (uint32_t k = 0; k < n_nets; ++k) {
     const snn_batch_member &mb = members[k];
     if (!mb.params || (!mb.pops && mb.n_pops) || (!mb.proj && mb.n_proj))
@@ -1504,8 +1602,7 @@ void build_batch(snn_batch *b, const snn_batch_member *members, uint32_t n_nets,
     }
     if (m->plastic) fail(SNN_E_INVALID, "member " + std::to_string(k) + ": the batched form needs static weights");
     if (m->n_inbuf != m->delay) fail(SNN_E_INVALID, "member " + std::to_string(k) + ": unexpected input ring");
-    uint32_t below = 0;
-    while (below < m->table_len && m->table[below] < (1ull << 32)) ++below;
+    const uint32_t below = drive_thresholds(m);
     const size_t lds = ((size_t)m->delay * m->n + below) * 4;
     if (m->n > 20480 || lds > b->lds_limit)
       fail(SNN_E_INVALID, "member " + std::to_string(k) + " does not fit one workgroup (n = " + std::to_string(m->n) +
@@ -1513,34 +1610,16 @@ void build_batch(snn_batch *b, const snn_batch_member *members, uint32_t n_nets,
                               std::to_string(b->lds_limit) + ")");
     b->lds_need = std::max(b->lds_need, (lds + 15) & ~(size_t)15);
     b->n_max = std::max(b->n_max, m->n);
-    snn::BatchNet d{};
-    d.row_ptr = m->row_ptr;
-    d.col = m->col;
-    d.w_q16 = m->w_q16;
-    d.w_src = m->w_src;
-    d.v = m->v;
-    d.ref = m->ref;
-    d.input = m->input;
-    d.queue = m->queue;
-    d.raster = m->raster;
-    d.table32 = m->d_table32;
-    d.ctl = m->ctl;
-    d.n = m->n;
-    d.words = m->words;
-    d.delay = m->delay;
-    d.raster_cap = m->raster_cap;
-    d.below = below;
-    d.key0 = m->key0;
-    d.key1 = m->key1;
-    d.alpha = m->alpha;
-    d.v_inf = m->v_inf;
-    d.v_th = m->v_th;
-    d.v_reset = m->v_reset;
-    d.ref_steps = m->ref_steps;
-    d.w_ext_q16 = m->w_ext_q16;
+    const snn::BatchNet d = batch_net(m);
     b->desc.push_back(d);
     b->degree.push_back(m->n ? (double)m->nnz / m->n : 0.0);
   }
+  // Batches of more networks than compute units keep what LDS use lets two or more
+  // workgroups share a unit; the others may use all of it.
+  b->lds_budget = b->lds_limit;
+  if (n_nets > b->pool.cu_count && b->lds_need)
+    b->lds_budget = std::max(b->lds_need, (size_t)lds_max / ((size_t)lds_max / (b->lds_need + snn::kBatchStaticLds)) -
+                                              snn::kBatchStaticLds);
   // heaviest networks first: the first workgroups start first and get a CU each
   std::vector<double> work(n_nets);
   for (uint32_t k = 0; k < n_nets; ++k) work[k] = (double)b->nets[k]->nnz + 8.0 * b->nets[k]->n;
@@ -1553,7 +1632,9 @@ void build_batch(snn_batch *b, const snn_batch_member *members, uint32_t n_nets,
   snn_batch_tuning t{};
   t.degree_div = 4;
   t.block = 256;
-  for (uint32_t blk : {512u, 1024u, 256u})
+  // 1,024 threads: 3.5 us per step of 96 networks of 1,000 to 20,000 neurons (4.3 with 512,
+  // 6.2 with 256), 5.2 of 512 such networks (6.0, 7.4), 1.9 of 64 of up to 5,000 (2.1, 2.5)
+  for (uint32_t blk : {1024u, 512u, 256u})
     if (snn::batch_per_lane(blk, b->n_max)) {
       t.block = blk;
       break;
@@ -1801,6 +1882,9 @@ snn_status snn_build_network(const snn_params *prm, const snn_population *pops, 
       hipDeviceProp_t props;
       check(hipGetDeviceProperties(&props, net->device), "hipGetDeviceProperties");
       net->cu_count = (uint32_t)std::max(1, props.multiProcessorCount);
+      int lds_max = 0;
+      check(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, net->device), "LDS limit");
+      net->lds_limit = (uint32_t)std::max(0, lds_max);
       if (stream) {
         net->stream = (hipStream_t)stream;
       } else {

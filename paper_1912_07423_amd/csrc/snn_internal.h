@@ -173,11 +173,13 @@ struct BatchNet {
   float *v;
   int32_t *ref;
   int32_t *input;            // [delay][n] Q16 accumulators, slot t mod delay
-  int32_t *queue;            // >= n spike ids
+  int32_t *queue;            // [slots][queue_stride] the FIFO ring of spike queues
+  uint32_t *qlen;            // its counters (written with kBatchQueues)
   uint64_t *raster;          // [raster_cap][words]
   const uint32_t *table32;   // drive thresholds below 2^32
   Ctl *ctl;
   uint32_t n, words, delay, raster_cap;
+  uint32_t slots, queue_stride, group_cap, window;  // of the FIFO ring
   uint32_t below;            // number of drive thresholds below 2^32 (0: no drive)
   uint32_t lanes_shift;      // log2 of the lanes that share one spike's row
   uint32_t key0, key1;
@@ -187,10 +189,22 @@ struct BatchNet {
 constexpr uint32_t kBatchCommit = 1u;       // write state, counters and t back
 constexpr uint32_t kBatchWriteRaster = 2u;  // write the raster rows
 constexpr uint32_t kBatchDrive = 4u;        // some member has a Poisson drive
+constexpr uint32_t kBatchQueues = 8u;      // leave the FIFO ring as the step pipeline does
+constexpr uint32_t kBatchStaticLds = 64u;   // bound on the kernels' static LDS
+constexpr uint32_t kBatchQueueMax = 512u;   // queue entries in LDS (12 bytes each)
+constexpr uint32_t kSoloMaxNeurons = 40960u;
+// Dynamic LDS of a persistent launch in 4-byte words: a network's accumulators and drive
+// thresholds, q_cap queue entries of three words, and, for the networks whose n + 1 row offsets fit behind
+// them, those.
+struct LdsPlan {
+  uint32_t words, q_cap;
+};
 bool batch_variant_supported(uint32_t block, uint32_t per);
 uint32_t batch_per_lane(uint32_t block, uint32_t n_max);  // 0: n_max too large for block
 hipError_t launch_batch(const BatchNet *nets, const uint32_t *order, uint32_t n_nets, uint32_t steps,
-                        uint32_t block, uint32_t per, uint32_t flags, size_t lds, hipStream_t s);
+                        uint32_t block, uint32_t per, uint32_t flags, LdsPlan lds, hipStream_t s);
+// One network of at most kSoloMaxNeurons neurons without drive by itself (one workgroup).
+hipError_t launch_solo(const BatchNet &d, uint32_t steps, uint32_t flags, LdsPlan lds, hipStream_t s);
 
 // Surrogate-gradient BPTT plan as its kernels see it (bptt.hip).  Batch <= 64: lane b
 // of a wavefront is batch element b; sizes are B batch, T steps, C inputs, H hidden,
@@ -392,6 +406,9 @@ struct snn_network {
   uint64_t t_host = 0;  // steps issued (mirror of the device counter)
   snn_batch *owner = nullptr;  // set for the members of a batch
   uint64_t device_bytes = 0;
+
+  bool solo = false;         // snn_run steps it by the persistent one-workgroup kernel
+  uint32_t lds_limit = 0;    // largest workgroup LDS
 
   // graph of a fixed chunk of windows
   hipGraphExec_t graph = nullptr;

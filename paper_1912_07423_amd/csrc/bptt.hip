@@ -9,7 +9,8 @@
 //   vck   [T/K][H][64]       membrane potential before each checkpoint segment
 //   vseg  [K][H][64]         membranes of one segment, recomputed in the backward pass
 //   lamu  [T][O][64]         readout adjoint
-//   lamv  [T][H][64]         membrane adjoint of every step (+ zeros [H][64] for step T)
+//   lamv  [T][S][H][8]       membrane adjoint of every step, in S slices of 8 batch elements
+//                            ([T][H][64] without slices; + zeros for step T)
 //   xbits [C][T], sbits [H][T]  64-bit batch masks of the binary input and hidden spikes
 //                            (8 readable entries after each, and before sbits)
 // Weights stay in the caller's CSR order (rows = presynaptic neuron, sorted targets);
@@ -634,6 +635,141 @@ __global__ __launch_bounds__(256) void k_adjoint_step(BpttArgs a, uint32_t t, co
   lam_out[(size_t)i * 64 + b] = a.beta * ln + surrogate(z, a.slope, a.smooth != 0) * ds;
 }
 
+// ---- the sliced membrane adjoint -------------------------------------------------------
+// With at most kSliceMaxNeurons hidden neurons the membrane adjoint is held in slices of 8
+// batch elements, lamv[t][slice][H][8], of which there are S = ceil(B / 8).
+__device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uint32_t b, uint32_t j) {
+  return (((size_t)t * a.S + (b >> 3)) * a.H + j) * 8 + (b & 7u);
+}
+
+// Readout part of the spike adjoint of every step (as k_readout_adjoint), in the sliced
+// layout.  A workgroup per (block of 32 neurons, t): thread (neuron, b mod 8) keeps the sums
+// of all slices; the readout adjoints of up to kReadoutChunk readouts and the block's
+// weights are staged in LDS, the adjoints as [o][b mod 8][slice], so that a thread's slices
+// of one readout are two 16-byte reads.  Bound: the store of the result (65 MB for 64 x 250
+// x 1,024).
+constexpr int kReadoutChunk = 32;
+constexpr int kAdjointRows = 32;  // neurons per workgroup, here and in k_adjoint_slice
+__global__ __launch_bounds__(256) void k_readout_adjoint_slice(BpttArgs a, float *dsr) {
+  __shared__ __align__(16) float lu[kReadoutChunk][8][8];  // [o][b mod 8][slice]
+  __shared__ float wl[kAdjointRows][kReadoutChunk + 1];
+  const uint32_t t = blockIdx.y, i0 = blockIdx.x * kAdjointRows;
+  const uint32_t il = threadIdx.x >> 3, b8 = threadIdx.x & 7u, i = i0 + il;
+  float acc[8] = {};
+  for (uint32_t o0 = 0; o0 < a.O; o0 += kReadoutChunk) {
+    const uint32_t no = std::min<uint32_t>(kReadoutChunk, a.O - o0);
+    if (o0) __syncthreads();
+    for (uint32_t x = threadIdx.x; x < no * 64u; x += 256u)
+      lu[x >> 6][x & 7u][(x >> 3) & 7u] = a.lamu[((size_t)t * a.O + o0) * 64 + x];
+    for (uint32_t x = threadIdx.x; x < kAdjointRows * no; x += 256u) {
+      const uint32_t r = x / no, o = x % no;
+      wl[r][o] = i0 + r < a.H ? a.w_out[(size_t)(i0 + r) * a.O + o0 + o] : 0.0f;
+    }
+    __syncthreads();
+    for (uint32_t o = 0; o < no; ++o) {
+      const float w = wl[il][o];
+      const float4 lo = *reinterpret_cast<const float4 *>(&lu[o][b8][0]);
+      const float4 hi = *reinterpret_cast<const float4 *>(&lu[o][b8][4]);
+      const float l[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc[q] = acc[q] + w * l[q];
+    }
+  }
+  if (i >= a.H) return;
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+    if ((uint32_t)q < a.S) dsr[(((size_t)t * a.S + q) * a.H + i) * 8 + b8] = acc[q];
+}
+
+// x + the value of another lane of the 16-lane row, by DPP.
+template <int kCtrl>
+__device__ __forceinline__ float add_row_lane(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
+}
+
+// Sum over the 16 lanes of a row, in every lane: neighbours, pairs, then the quads and halves
+// by mirroring (whose lanes already agree).
+__device__ __forceinline__ float row_sum(float x) {
+  x = add_row_lane<0xB1>(x);    // quad_perm 1,0,3,2
+  x = add_row_lane<0x4E>(x);    // quad_perm 2,3,0,1
+  x = add_row_lane<0x141>(x);   // row_half_mirror
+  return add_row_lane<0x140>(x);  // row_mirror
+}
+
+// Membrane adjoint of step t in the sliced layout.  A workgroup per (slice, 32 neurons): the
+// slice's lamV_{t+1} of all H neurons (32 H bytes, contiguous) is staged in LDS, requested
+// together with the neurons' outgoing synapses (padded rows of (target, weight) pairs, so no
+// row bounds come first) and their own state: one memory round trip.  A wavefront holds two
+// neurons; of the 32 lanes of one, 16 take every 16th synapse for 4 batch elements each, one
+// 16-byte LDS read and four multiply-adds per synapse, and a 16-lane sum completes them.
+// Slices are dealt round-robin over the workgroups, so that with 8 slices each XCD (they
+// take workgroups round-robin too) works on one slice, which its own L2 holds.  A launch and
+// its round trip bound it: 4.9 us per step at 64 x 1,024 with rows of about 102 synapses
+// (7.4 with a wavefront per neuron that gathers 256-byte rows from memory, the form kept for
+// more neurons), 3.6 us at 19 x 201 (7.7).
+// lam_next / lam_out: slices of steps t + 1 and t; lam_out holds the readout part on entry.
+// V_t of (neuron, batch element) is at v_t[i * v_i + b * v_b].
+constexpr int kAdjointAhead = 8;  // rounds of synapses requested before the barrier
+__global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float *v_t, uint32_t v_i, size_t v_b,
+                                                        const float *lam_next, float *lam_out) {
+  extern __shared__ float4 lam_sl[];  // [H][2]
+  const uint32_t slice = blockIdx.x % a.S, block = blockIdx.x / a.S;
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint32_t p = lane & 15u, b4 = (lane >> 4) & 1u;
+  const uint32_t i = block * kAdjointRows + wave * 2u + (lane >> 5);
+  const bool live = i < a.H;
+  const uint32_t il = live ? i : a.H - 1u;
+  const uint2 *row = a.adj_pair + (size_t)il * a.adj_w;
+  const uint32_t len = live ? a.adj_len[il] : 0u;
+  uint2 e[kAdjointAhead];
+#pragma unroll
+  for (int k = 0; k < kAdjointAhead; ++k) {
+    e[k] = make_uint2(0u, 0u);
+    if ((uint32_t)k * 16u < a.adj_w) e[k] = row[(uint32_t)k * 16u + p];  // uniform condition
+  }
+  // this lane's element of the result (p < 4): batch element b
+  const uint32_t b = slice * 8u + b4 * 4u + (p & 3u);
+  const size_t own = ((size_t)slice * a.H + il) * 8 + (b & 7u);
+  const float ln = lam_next[own], readout = lam_out[own];
+  const float vt = b < a.B ? v_t[(size_t)il * v_i + b * v_b] : 0.0f;
+  const float4 *src = reinterpret_cast<const float4 *>(lam_next + (size_t)slice * a.H * 8);
+  for (uint32_t x0 = threadIdx.x; x0 < a.H * 2u; x0 += 4u * 1024u) {
+    float4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = src[std::min<uint32_t>(x0 + (uint32_t)q * 1024u, a.H * 2u - 1u)];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (x0 + (uint32_t)q * 1024u < a.H * 2u) lam_sl[x0 + (uint32_t)q * 1024u] = v[q];
+  }
+  __syncthreads();
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  // (a padding entry is skipped, not multiplied: its target's adjoint may not be finite)
+  auto add = [&](const uint2 &s, uint32_t at) {
+    const float4 l = lam_sl[s.x * 2u + b4];
+    const float w = __uint_as_float(s.y);
+    if (at < len) {
+      acc.x = __builtin_fmaf(w, l.x, acc.x);
+      acc.y = __builtin_fmaf(w, l.y, acc.y);
+      acc.z = __builtin_fmaf(w, l.z, acc.z);
+      acc.w = __builtin_fmaf(w, l.w, acc.w);
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < kAdjointAhead; ++k)
+    if ((uint32_t)k * 16u < a.adj_w) add(e[k], (uint32_t)k * 16u + p);
+  for (uint32_t at = kAdjointAhead * 16u + p; at < a.adj_w; at += 16u) add(row[at], at);
+  acc.x = row_sum(acc.x);
+  acc.y = row_sum(acc.y);
+  acc.z = row_sum(acc.z);
+  acc.w = row_sum(acc.w);
+  if (!live || p >= 4u) return;
+  const float sum = p == 0 ? acc.x : p == 1 ? acc.y : p == 2 ? acc.z : acc.w;
+  float ds = readout + sum;
+  if (!a.detach_reset) ds = ds - a.theta * ln;
+  const float z = vt - a.theta;
+  lam_out[own] = a.beta * ln + surrogate(z, a.slope, a.smooth != 0) * ds;
+}
+
 // Batch masks of a [T][rows][64] trajectory: bits[r][t] bit b = (val[t][r][b] != 0) for
 // b < B; flag receives 1 if any of those values is neither 0 nor 1 (the masks then do
 // not represent the values and the gradients take the general path).  A wavefront per
@@ -695,8 +831,11 @@ __global__ __launch_bounds__(kGradBlock) void k_grad_edges(BpttArgs a, const uin
     for (uint32_t tc = 0; tc < T; tc += kGradChunk) {
       const uint32_t len = min(kGradChunk, T - tc);
       __syncthreads();  // the previous chunk has been read by every lane
-      for (uint32_t x = threadIdx.x; x < len * 64; x += kGradBlock)
-        lam_s[x] = a.lamv[((size_t)(tc + x / 64) * a.H + j) * 64 + (x & 63u)];
+      for (uint32_t x = threadIdx.x; x < len * 64; x += kGradBlock) {
+        const uint32_t t = tc + x / 64, b = x & 63u;
+        if (a.S) lam_s[x] = b < a.S * 8u ? a.lamv[slice_index(a, t, b, j)] : 0.0f;
+        else lam_s[x] = a.lamv[((size_t)t * a.H + j) * 64 + b];
+      }
       __syncthreads();
       if (!live) continue;
       if (use_bits) {
@@ -772,6 +911,12 @@ __global__ void k_gather_ell(const float *w, const uint32_t *edge, float *w_ell,
   if (x < n) w_ell[x] = edge[x] == 0xFFFFFFFFu ? 0.0f : w[edge[x]];
 }
 
+// The weights of the sliced adjoint's padded rows: edge e of the CSR order at pos[e].
+__global__ void k_scatter_pairs(const float *w, const uint32_t *pos, uint2 *pair, uint64_t nnz) {
+  const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < nnz) pair[pos[e]].y = __float_as_uint(w[e]);
+}
+
 static void gather_weights(const BpttArgs &a, hipStream_t s) {
   if (a.ell_w)
     hipLaunchKernelGGL(k_gather_ell, dim3(blocks_for((uint64_t)a.H * a.ell_w, 256)), dim3(256), 0, s, a.w_rec,
@@ -842,7 +987,10 @@ hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float
 hipError_t bptt_backward_prologue(const BpttArgs &a, const float *g_loss, hipStream_t s) {
   gather_weights(a, s);
   hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && a.nnz_rec)
+  if (a.S && a.nnz_rec)
+    hipLaunchKernelGGL(k_scatter_pairs, dim3(blocks_for(a.nnz_rec, 256)), dim3(256), 0, s, a.w_rec, a.adj_pos,
+                       a.adj_pair, a.nnz_rec);
+  else if (e == hipSuccess && a.nnz_rec)
     e = hipMemcpyAsync(a.w_rec_c, a.w_rec, (size_t)a.nnz_rec * 4, hipMemcpyDeviceToDevice, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_lam_u, dim3(a.O), dim3(64), 0, s, a, g_loss);
@@ -861,7 +1009,10 @@ hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
                        g.sbits, g.flags + 1);
   // the readout part of every step's spike adjoint, into lamv (each adjoint step reads
   // its own entries, then overwrites them with lamV_t)
-  hipLaunchKernelGGL(k_readout_adjoint, dim3(blocks_for((uint64_t)g.T * g.H, 4)), dim3(256), 0, s, g, g.lamv);
+  if (g.S)
+    hipLaunchKernelGGL(k_readout_adjoint_slice, dim3(blocks_for(g.H, kAdjointRows), g.T), dim3(256), 0, s, g, g.lamv);
+  else
+    hipLaunchKernelGGL(k_readout_adjoint, dim3(blocks_for((uint64_t)g.T * g.H, 4)), dim3(256), 0, s, g, g.lamv);
   const dim3 grid(blocks_for(g.H, 4));
   const uint32_t n_seg = (g.T + g.K - 1) / g.K;
   for (int32_t seg = (int32_t)n_seg - 1; seg >= 0; --seg) {
@@ -879,12 +1030,26 @@ hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
                        g.vseg);
     for (int32_t k = (int32_t)len - 1; k >= 0; --k) {
       const uint32_t t = t0 + (uint32_t)k;
+      if (g.S) {
+        const size_t step = (size_t)g.S * g.H * 8;
+        hipLaunchKernelGGL(k_adjoint_slice, dim3(g.S * blocks_for(g.H, kAdjointRows)), dim3(1024), (size_t)g.H * 32, s, g,
+                           g.vseg + (size_t)k * g.H * 64, 64u, (size_t)1,
+                           t + 1 < g.T ? g.lamv + (t + 1) * step : g.lam_carry, g.lamv + t * step);
+        continue;
+      }
       const float *lam_next = t + 1 < g.T ? g.lamv + (size_t)(t + 1) * g.H * 64 : g.lam_carry;
       hipLaunchKernelGGL(k_adjoint_step, grid, dim3(256), 0, s, g, t, g.vseg + (size_t)k * g.H * 64, lam_next,
                          g.lamv + (size_t)t * g.H * 64);
     }
   }
   return hipGetLastError();
+}
+
+// The sliced adjoint's dynamic LDS, once per plan.
+hipError_t bptt_prepare(const BpttArgs &a) {
+  if (!a.S) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_adjoint_slice),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSliceMaxNeurons * 32u));
 }
 
 // the gradients, written to the caller's arrays

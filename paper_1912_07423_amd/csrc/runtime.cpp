@@ -1808,10 +1808,33 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     a.ell_len = upload(pool, el);
     a.ell_wt = dev_array<float>(pool, es.size());
   }
+  // padded rows of the recurrent weights for the sliced adjoint
+  uint64_t max_row = 0;
+  for (uint32_t i = 0; i < a.H; ++i) max_row = std::max<uint64_t>(max_row, rec_ptr[i + 1] - rec_ptr[i]);
+  const uint64_t adj_w = std::max<uint64_t>(16, (max_row + 15) / 16 * 16);
+  if (a.H <= snn::kSliceMaxNeurons && adj_w * a.H <= snn::kSliceMaxPairs) {
+    a.S = (a.B + 7) / 8;
+    a.adj_w = (uint32_t)adj_w;
+    std::vector<uint2> pair((size_t)a.H * adj_w, make_uint2(0u, 0u));
+    std::vector<uint32_t> pos(nnz_rec), len(a.H);
+    for (uint32_t i = 0; i < a.H; ++i) {
+      len[i] = (uint32_t)(rec_ptr[i + 1] - rec_ptr[i]);
+      for (uint32_t k = 0; k < len[i]; ++k) {
+        const uint64_t e = rec_ptr[i] + k;
+        pos[e] = (uint32_t)(i * adj_w + k);
+        pair[pos[e]].x = (uint32_t)rec_col[e];
+      }
+    }
+    a.adj_pair = upload(pool, pair);
+    a.adj_pos = upload(pool, pos);
+    a.adj_len = upload(pool, len);
+    check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
+    check(snn::bptt_prepare(a), "bptt prepare");
+  }
   a.flags = dev_array<uint32_t>(pool, 2);
   a.w_in_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_in));
   a.w_rec_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
-  a.w_rec_c = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
+  if (!a.S) a.w_rec_c = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
   a.w_out_c = dev_array<float>(pool, (size_t)a.H * a.O);
   a.xt = dev_array<float>(pool, (size_t)a.T * a.C * 64);
   a.iin = dev_array<float>(pool, (size_t)a.T * HB);

@@ -213,8 +213,17 @@ hipError_t launch_solo(const BatchNet &d, uint32_t steps, uint32_t flags, LdsPla
 // loads), and at most 8,192 hidden neurons (their 64 KiB of spike masks in LDS).
 constexpr uint32_t kEllMaxWidth = 256;
 constexpr uint32_t kEllMaxNeurons = 8192;
+// The sliced membrane adjoint: a slice of all neurons (32 bytes each) is staged in LDS, and
+// the synapses are held as padded rows of at most kSliceMaxPairs entries in all.
+constexpr uint32_t kSliceMaxNeurons = 4096;
+constexpr uint64_t kSliceMaxPairs = 1ull << 26;
 struct BpttArgs {
   uint32_t B, T, C, H, O, K;
+  uint32_t S;                  // slices of 8 batch elements of the membrane adjoint (0: not sliced)
+  uint32_t adj_w;              // width of its padded rows of W_rec, a multiple of 16
+  uint2 *adj_pair;             // [H][adj_w] (target, weight); padding (0, 0)
+  const uint32_t *adj_pos;     // [nnz_rec] place of each CSR edge
+  const uint32_t *adj_len;     // [H] row lengths
   float beta, beta_out, theta, slope;
   uint32_t smooth, detach_reset;
   uint64_t nnz_in, nnz_rec;
@@ -246,6 +255,7 @@ struct BpttArgs {
 // caller's arrays, the body only the plan's buffers (capturable once per plan).  The body
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
+hipError_t bptt_prepare(const BpttArgs &a);
 hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s);
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s);
 hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float *loss, hipStream_t s);

@@ -1,0 +1,60 @@
+"""The surrogate-gradient form at the sizes where its kernels change form or have remainders,
+against the oracle with the tolerances of test_gpu_bptt: batches that fill slices of 8 or not,
+hidden sizes around the 32 neurons of an adjoint workgroup and beyond the sliced form's limit,
+synapse rows longer than the rounds requested ahead, and more readouts than one LDS chunk."""
+import numpy as np
+import pytest
+
+from paper_1912_07423_amd import workloads as W
+from test_gpu_bptt import _compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu(gpu_available):
+    return gpu_available
+
+
+def _inputs(B, T, C, H, O, p_in=0.4, p_rec=0.3, seed=31):
+    return W.bptt_inputs(batch=B, steps=T, n_in=C, n_hidden=H, n_out=O, p_in=p_in, p_rec=p_rec, rate_lo=100.0,
+                         rate_hi=400.0, seed=seed)
+
+
+@pytest.mark.parametrize("B,H", [(1, 33), (8, 32), (9, 31), (17, 64), (63, 65), (64, 1)])
+@pytest.mark.parametrize("smooth", [False, True])
+def test_slices_and_neuron_blocks(B, H, smooth):
+    _compare(_inputs(B, 20, 15, H, 4), 6, smooth=smooth)
+
+
+@pytest.mark.parametrize("O", [1, 32, 33, 70])
+def test_readouts(O):
+    _compare(_inputs(10, 17, 12, 40, O), 5)
+
+
+def test_rows_longer_than_the_rounds_requested_ahead():
+    d = _inputs(6, 15, 10, 300, 3, p_rec=0.7)
+    assert d["mask_rec"].sum(axis=1).max() > 128 + 16
+    _compare(d, 5)
+
+
+def test_uneven_rows():
+    """A neuron without outgoing recurrent synapses beside one with a full row."""
+    d = _inputs(9, 25, 14, 90, 4, p_rec=0.1)
+    d["mask_rec"][5], d["mask_rec"][7] = False, True
+    d["mask_rec"][7, 7] = False
+    rng = np.random.default_rng(3)
+    d["w_rec"] = (rng.standard_normal(d["mask_rec"].shape) * 0.2).astype(np.float32) * d["mask_rec"]
+    _compare(d, 8)
+
+
+def test_no_recurrent_synapses():
+    d = _inputs(5, 12, 10, 40, 3)
+    d["mask_rec"][:] = False
+    d["w_rec"][:] = 0
+    _compare(d, 4)
+
+
+def test_more_neurons_than_the_sliced_adjoint_holds():
+    d = _inputs(3, 6, 10, 4100, 2, p_rec=0.003)
+    _compare(d, 4)

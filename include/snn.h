@@ -406,7 +406,8 @@ void snn_batch_destroy(snn_batch *b);
  * the exact derivative with the reset term (smooth = 1, for finite-difference checks).
  * The forward keeps every step's s and the membrane state at the end of every
  * `checkpoint` steps; the backward recomputes each segment's membranes from its
- * checkpoint.  The current into neuron j sums its in-edges in ascending source order,
+ * checkpoint.  In spiking mode with at most 2,048 hidden neurons it keeps the membranes of
+ * every step instead (the spikes then as bits), and the backward recomputes nothing.  The current into neuron j sums its in-edges in ascending source order,
  * input projection first, one term at a time; the readout sums ascending; the maximum
  * over time is taken at its first step. */
 typedef struct snn_bptt snn_bptt;

@@ -320,7 +320,9 @@ __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a) {
   for (uint64_t w = first; w < (uint64_t)a.T * a.H; w += (uint64_t)gridDim.x * 4) {
     const uint32_t t = (uint32_t)(w / a.H), j = (uint32_t)(w % a.H);
     const float *xt = a.xt + (size_t)t * a.C * 64;
-    a.iin[w * 64 + b] = ordered_gather_sum(0.0f, a.in_t_ptr[j], a.in_t_ptr[j + 1], a.in_t_src, a.w_in_t, xt, b);
+    const float sum = ordered_gather_sum(0.0f, a.in_t_ptr[j], a.in_t_ptr[j + 1], a.in_t_src, a.w_in_t, xt, b);
+    if (!a.events) a.iin[w * 64 + b] = sum;
+    else if (b < a.B) a.vall[((size_t)t * a.B + b) * a.Hp + j] = sum;
   }
 }
 
@@ -431,6 +433,324 @@ __global__ __launch_bounds__(256) void k_hidden_step_ell(BpttArgs a, uint32_t t,
       a.sbits_t[(size_t)t * a.H + j] = mk;
     }
   }
+}
+
+// ---- the event-driven forward pass ------------------------------------------------------
+// In spiking mode with at most kEventMaxNeurons hidden neurons the forward pass works on what
+// is not zero.  Batch elements do not interact in it, so a workgroup steps one of them through
+// the whole sequence, with nothing to wait for outside itself.  Weights are held as dense
+// rows (Hp columns, zeros off the synapses): a presynaptic spike adds its row to the
+// currents of all neurons, one neuron per lane, sources in ascending order, which is the
+// defined sum (a term off the synapses adds +0 to a sum that starts from +0, and w * 1 = w).
+//   vall  [T][B][Hp]  the input current of every step, replaced by the membrane potential
+//   spk   [B][T][nw]  spikes of every step, 64 neurons per word
+
+__device__ __forceinline__ size_t row_index(const BpttArgs &a, uint32_t t, uint32_t b) {
+  return ((size_t)t * a.B + b) * a.Hp;
+}
+
+// The caller's weights into the plan's layouts, edge e at pos[e]: dense rows of the input and
+// recurrent weights, and the target-major pairs of the many-spikes form.
+__global__ void k_scatter_weights(BpttArgs a) {
+  const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < a.nnz_in) a.dense_in[a.in_pos[e]] = a.w_in[e];
+  if (e < a.nnz_rec) {
+    const float w = a.w_rec[e];
+    a.dense_rec[a.rec_pos[e]] = w;
+    a.col_pair[a.col_pos[e]].y = __float_as_uint(w);
+  }
+}
+
+// Input-projection current of every (batch element, step) from binary inputs: a wavefront
+// finds the active inputs of 64 at a time by a ballot and adds their dense rows, 16 bytes per
+// lane and block of 256 columns, up to four rows and kInputBlocks blocks in flight.  Bound:
+// the rows' way from L2 (280,000 active inputs x 4 KB at 64 x 250 x 700 -> 1,024).
+constexpr int kInputBlocks = 4;
+__global__ __launch_bounds__(256) void k_input_rows(BpttArgs a, const float *x) {
+  if (a.flags[0] != 0) return;  // not binary: k_input_current_values
+  const uint32_t bt = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (bt >= a.B * a.T) return;
+  const uint32_t lane = lane_id();
+  const uint32_t nb = std::min<uint32_t>(kInputBlocks, a.Hp / 256 - blockIdx.y * kInputBlocks);
+  const size_t col = (size_t)blockIdx.y * kInputBlocks * 256 + lane * 4;
+  const float *xr = x + (size_t)bt * a.C;
+  float4 acc[kInputBlocks];
+#pragma unroll
+  for (int q = 0; q < kInputBlocks; ++q) acc[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float xv = lane < a.C ? xr[lane] : 0.0f;
+  for (uint32_t c0 = 0; c0 < a.C; c0 += kWave) {
+    uint64_t m = __ballot(xv != 0.0f);
+    xv = c0 + kWave + lane < a.C ? xr[c0 + kWave + lane] : 0.0f;  // the next 64
+    while (m) {
+      const uint32_t n = std::min<uint32_t>(4u, (uint32_t)__popcll(m));  // uniform
+      float4 w[4][kInputBlocks];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if ((uint32_t)u < n) {
+          const float *row = a.dense_in + (size_t)(c0 + (uint32_t)__builtin_ctzll(m)) * a.Hp + col;
+          m &= m - 1;
+#pragma unroll
+          for (int q = 0; q < kInputBlocks; ++q)
+            if ((uint32_t)q < nb) w[u][q] = *reinterpret_cast<const float4 *>(row + q * 256);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if ((uint32_t)u < n) {
+#pragma unroll
+          for (int q = 0; q < kInputBlocks; ++q) {
+            if ((uint32_t)q < nb) {
+              acc[q].x = acc[q].x + w[u][q].x;
+              acc[q].y = acc[q].y + w[u][q].y;
+              acc[q].z = acc[q].z + w[u][q].z;
+              acc[q].w = acc[q].w + w[u][q].w;
+            }
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kInputBlocks; ++q)
+    if ((uint32_t)q < nb) *reinterpret_cast<float4 *>(a.vall + row_index(a, bt % a.T, bt / a.T) + col + q * 256) = acc[q];
+}
+
+// All hidden steps of one batch element: one workgroup, a wavefront per kPer words of 64
+// neurons (neuron 64 q + lane of its range), one barrier per step, at which the step's spikes
+// are published as words in LDS.  Every wavefront takes the sources off the words by itself,
+// mostly with scalar instructions, so few wavefronts with several words each do better than
+// one per word (1,024 neurons: 1.4 us per step, 1.6 with 16 wavefronts).  Global memory other
+// than weight rows is touched once per kSeqChunk steps: the chunk's input currents, requested
+// a chunk ahead, pass through LDS (so that a step can index them), where the membranes replace
+// them until the chunk is written out with its spike words; a store in every step would be
+// waited for by the step's row reads.  Per step a wavefront reads the previous step's words,
+// takes its sources off them in ascending order and adds their rows, up to kSeqRows in
+// flight; with more sources than twice the longest column it walks the columns (target-major
+// pairs) and tests each source's bit instead.  64 x 250 x 1,024 with 3.7 spikes per step: 344
+// us, where a launch per step took 1,540; 19 x 103 x 201: 49 us (370).
+constexpr uint32_t kSeqChunk = 16;
+constexpr uint32_t kSeqThreads = kEventMaxNeurons / 4;
+constexpr int kSeqRows = 4;
+template <int kPer>
+__global__ __launch_bounds__(kSeqThreads) void k_hidden_seq(BpttArgs a) {
+  extern __shared__ float cur_s[];  // [kSeqChunk][Hp]
+  __shared__ uint64_t words_s[2 * kSeqChunk][kEventMaxNeurons / 64];  // step mod 2 chunks
+  const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const size_t step_rows = (size_t)a.B * a.Hp;
+  float *vrow = a.vall + row_index(a, 0, b);
+  uint64_t *srow = a.spk + (size_t)b * a.T * a.nw;
+  float v[kPer], sp[kPer], ahead[kSeqChunk][kPer];
+  const uint32_t w0 = wave * kPer;            // this wavefront's words [w0, w0 + kPer)
+  const uint32_t col0 = w0 * kWave + lane;    // its neurons col0 + 64 q (inside Hp: whole
+                                              // wavefronts of words, kPer of them divide Hp)
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) v[q] = sp[q] = 0.0f;
+  auto request = [&](uint32_t t0) {
+#pragma unroll
+    for (uint32_t k = 0; k < kSeqChunk; ++k)
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) ahead[k][q] = vrow[std::min<uint32_t>(t0 + k, a.T - 1) * step_rows + col0 + (uint32_t)q * kWave];
+  };
+  // membranes and spike words of the steps [t0, t1), t0 a chunk's first step, after a barrier
+  auto flush = [&](uint32_t t0, uint32_t t1) {
+#pragma unroll
+    for (uint32_t k = 0; k < kSeqChunk; ++k)
+#pragma unroll
+      for (int q = 0; q < kPer; ++q)
+        if (t0 + k < t1) vrow[(t0 + k) * step_rows + col0 + (uint32_t)q * kWave] = cur_s[k * a.Hp + col0 + (uint32_t)q * kWave];
+    for (uint32_t x = tid; x < (t1 - t0) * a.nw; x += blockDim.x)
+      srow[(size_t)t0 * a.nw + x] = words_s[(t0 + x / a.nw) % (2 * kSeqChunk)][x % a.nw];
+  };
+  request(0);
+  for (uint32_t t = 0; t < a.T; ++t) {
+    const uint32_t k = t % kSeqChunk;
+    if (k == 0) {  // a lane reads back only what it wrote
+      if (t) flush(t - kSeqChunk, t);
+#pragma unroll
+      for (uint32_t u = 0; u < kSeqChunk; ++u)
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          cur_s[u * a.Hp + col0 + (uint32_t)q * kWave] = ahead[u][q];
+      if (t + kSeqChunk < a.T) request(t + kSeqChunk);
+    }
+    float acc[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) acc[q] = cur_s[k * a.Hp + col0 + (uint32_t)q * kWave];
+    if (t) {
+      const uint64_t *prev = words_s[(t - 1) % (2 * kSeqChunk)];
+      const uint64_t mine = lane < a.nw ? prev[lane] : 0ull;
+      uint64_t any = __ballot(mine != 0);  // words with spikes
+      bool columns = false;
+      if ((uint32_t)__popcll(any) * 64u > 2u * a.col_w) {  // the count can exceed the limit
+        const uint32_t incl = wave_inclusive_scan((uint32_t)__popcll(mine));
+        columns = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1) > 2u * a.col_w;
+      }
+      if (columns) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+          const uint2 *pairs = a.col_pair + col0 + (uint32_t)q * kWave;
+#pragma unroll 4
+          for (uint32_t r = 0; r < a.col_w; ++r) {
+            const uint2 e = pairs[(size_t)r * a.Hp];  // padding: source 0, weight 0
+            const float sum = acc[q] + __uint_as_float(e.y);
+            acc[q] = (prev[e.x >> 6] >> (e.x & 63u)) & 1u ? sum : acc[q];
+          }
+        }
+      } else {
+        uint64_t word = 0;
+        uint32_t at = 0;
+        while (any) {
+          float w[kSeqRows][kPer];
+          uint32_t n = 0;
+#pragma unroll
+          for (int u = 0; u < kSeqRows; ++u) {
+            if (any) {  // uniform
+              if (!word) {
+                at = (uint32_t)__builtin_ctzll(any);
+                word = lane_read64(mine, at);
+              }
+              const uint32_t src = at * 64u + (uint32_t)__builtin_ctzll(word);
+              word &= word - 1;
+              if (!word) any &= any - 1;
+              const float *row = a.dense_rec + (size_t)src * a.Hp;
+#pragma unroll
+              for (int q = 0; q < kPer; ++q) w[u][q] = row[col0 + (uint32_t)q * kWave];
+              n = (uint32_t)u + 1u;
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < kSeqRows; ++u)
+            if ((uint32_t)u < n) {
+#pragma unroll
+              for (int q = 0; q < kPer; ++q) acc[q] = acc[q] + w[u][q];
+            }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const uint32_t j = col0 + (uint32_t)q * kWave;
+      float vn = a.beta * v[q];
+      vn = vn + acc[q];
+      vn = vn - a.theta * sp[q];
+      v[q] = vn;
+      const bool spike = j < a.H && spike_fn(vn - a.theta, a.slope, false) != 0.0f;
+      sp[q] = spike ? 1.0f : 0.0f;
+      const uint64_t m = __ballot(spike);
+      if (lane == 0) words_s[t % (2 * kSeqChunk)][w0 + (uint32_t)q] = m;
+      cur_s[k * a.Hp + j] = vn;
+    }
+    __syncthreads();
+  }
+  flush((a.T - 1) / kSeqChunk * kSeqChunk, a.T);
+}
+
+// Batch masks of the hidden spikes from the words of every batch element: a workgroup per
+// (word, kMaskBlock steps) sets the few spikes' bits in LDS and writes the 64 neurons' masks
+// of its steps, contiguous per neuron.
+constexpr uint32_t kMaskBlock = 16;
+__global__ __launch_bounds__(256) void k_spike_masks(BpttArgs a) {
+  __shared__ unsigned long long mask[64][kMaskBlock];
+  const uint32_t w = blockIdx.x, t0 = blockIdx.y * kMaskBlock, tid = threadIdx.x;
+  const uint32_t tl = tid % kMaskBlock, t = t0 + tl;
+  uint64_t word[64 * kMaskBlock / 256];  // (step tl, batch elements tid / 16 + 16 q)
+#pragma unroll
+  for (uint32_t q = 0; q < 64 * kMaskBlock / 256; ++q) {
+    const uint32_t b = tid / kMaskBlock + q * (256 / kMaskBlock);
+    word[q] = b < a.B && t < a.T ? a.spk[((size_t)b * a.T + t) * a.nw + w] : 0ull;
+  }
+  for (uint32_t x = tid; x < 64 * kMaskBlock; x += 256) (&mask[0][0])[x] = 0ull;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t q = 0; q < 64 * kMaskBlock / 256; ++q)
+    for (uint64_t m = word[q]; m; m &= m - 1)
+      atomicOr(&mask[__builtin_ctzll(m)][tl], 1ull << (tid / kMaskBlock + q * (256 / kMaskBlock)));
+  __syncthreads();
+  for (uint32_t x = tid; x < 64 * kMaskBlock; x += 256) {
+    const uint32_t i = w * 64u + x / kMaskBlock;
+    if (i < a.H && t0 + x % kMaskBlock < a.T) a.sbits[(size_t)i * a.T + t0 + x % kMaskBlock] = (&mask[0][0])[x];
+  }
+}
+
+// Readout drive of every (batch element, step) from its spikes: ro[b][t][o] = sum of the
+// spiking neurons' readout weights, ascending; a wavefront per (b, t), lanes = readouts.
+__global__ __launch_bounds__(256) void k_readout_events(BpttArgs a, float *ro) {
+  const uint32_t bt = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (bt >= a.B * a.T) return;
+  const uint32_t lane = lane_id();
+  const uint64_t mine = lane < a.nw ? a.spk[(size_t)bt * a.nw + lane] : 0ull;
+  for (uint32_t o0 = 0; o0 < a.O; o0 += kWave) {
+    const uint32_t o = std::min<uint32_t>(o0 + lane, a.O - 1);
+    float acc = 0.0f;
+    uint64_t any = __ballot(mine != 0), word = 0;
+    uint32_t at = 0;
+    while (any) {
+      float w[4];
+      uint32_t n = 0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (any) {
+          if (!word) {
+            at = (uint32_t)__builtin_ctzll(any);
+            word = lane_read64(mine, at);
+          }
+          w[u] = a.w_out[(size_t)(at * 64u + (uint32_t)__builtin_ctzll(word)) * a.O + o];
+          word &= word - 1;
+          if (!word) any &= any - 1;
+          n = (uint32_t)u + 1u;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if ((uint32_t)u < n) acc = acc + w[u];
+    }
+    if (o0 + lane < a.O) ro[(size_t)bt * a.O + o0 + lane] = acc;
+  }
+}
+
+// The leaky readout's scan (as k_readout_scan) over ro[b][t][o]: block (b, 64 readouts).
+__global__ __launch_bounds__(64) void k_readout_scan_events(BpttArgs a, const float *ro) {
+  const uint32_t b = blockIdx.x, o = blockIdx.y * 64u + threadIdx.x;
+  const float *r0 = ro + (size_t)b * a.T * a.O + std::min<uint32_t>(o, a.O - 1);
+  float u = 0.0f, m = 0.0f;
+  uint32_t tm = 0;
+  auto step = [&](uint32_t t, float r) {
+    float ut = a.beta_out * u;
+    ut = ut + r;
+    u = ut;
+    if (t == 0 || ut > m) {
+      m = ut;
+      tm = t;
+    }
+  };
+  constexpr uint32_t kAhead = 16;  // drives requested before the steps that use them
+  float r[kAhead], nx[kAhead];
+#pragma unroll
+  for (uint32_t q = 0; q < kAhead; ++q) r[q] = r0[(size_t)std::min<uint32_t>(q, a.T - 1) * a.O];
+  for (uint32_t t = 0; t < a.T; t += kAhead) {
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q) nx[q] = r0[(size_t)std::min<uint32_t>(t + kAhead + q, a.T - 1) * a.O];
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q)
+      if (t + q < a.T) step(t + q, r[q]);
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q) r[q] = nx[q];
+  }
+  if (o < a.O) {
+    a.m[(size_t)b * a.O + o] = m;
+    a.tmax[(size_t)b * a.O + o] = (int32_t)tm;
+  }
+}
+
+// Membrane checkpoints [segment][H][64] of the latest forward pass, for the trace.
+__global__ void k_trace_v(BpttArgs a) {
+  const uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t n_seg = (a.T + a.K - 1) / a.K;
+  if (x >= (uint64_t)n_seg * a.H * 64) return;
+  const uint32_t b = (uint32_t)(x & 63u), j = (uint32_t)((x >> 6) % a.H), seg = (uint32_t)((x >> 6) / a.H);
+  const uint32_t t = std::min<uint32_t>((seg + 1) * a.K - 1, a.T - 1);
+  a.vck[x] = b < a.B ? a.vall[row_index(a, t, b) + j] : 0.0f;
 }
 
 // Backward recomputation of one checkpoint segment [t0, t0 + len).  The spikes of every
@@ -650,12 +970,28 @@ __device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uin
 // x 1,024).
 constexpr int kReadoutChunk = 32;
 constexpr int kAdjointRows = 32;  // neurons per workgroup, here and in k_adjoint_slice
+// In the event-driven form it also takes the surrogate derivative of its membranes, which
+// come as rows of one batch element each, to the slices (an adjoint step that gathered them
+// itself took 0.8 us longer).
 __global__ __launch_bounds__(256) void k_readout_adjoint_slice(BpttArgs a, float *dsr) {
   __shared__ __align__(16) float lu[kReadoutChunk][8][8];  // [o][b mod 8][slice]
   __shared__ float wl[kAdjointRows][kReadoutChunk + 1];
   const uint32_t t = blockIdx.y, i0 = blockIdx.x * kAdjointRows;
   const uint32_t il = threadIdx.x >> 3, b8 = threadIdx.x & 7u, i = i0 + il;
   float acc[8] = {};
+  // membranes of the block: [b][neuron], 32 neurons (128 bytes) contiguous
+  __shared__ float vs[64][kAdjointRows + 1];
+  if (a.events) {
+    float v[8];
+    const uint32_t n = threadIdx.x % kAdjointRows, b0 = threadIdx.x / kAdjointRows;
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t b = b0 + 8u * q;
+      v[q] = b < a.B && i0 + n < a.H ? a.vall[((size_t)t * a.B + b) * a.Hp + i0 + n] : 0.0f;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) vs[b0 + 8u * q][n] = v[q];
+  }
   for (uint32_t o0 = 0; o0 < a.O; o0 += kReadoutChunk) {
     const uint32_t no = std::min<uint32_t>(kReadoutChunk, a.O - o0);
     if (o0) __syncthreads();
@@ -678,7 +1014,11 @@ __global__ __launch_bounds__(256) void k_readout_adjoint_slice(BpttArgs a, float
   if (i >= a.H) return;
 #pragma unroll
   for (int q = 0; q < 8; ++q)
-    if ((uint32_t)q < a.S) dsr[(((size_t)t * a.S + q) * a.H + i) * 8 + b8] = acc[q];
+    if ((uint32_t)q < a.S) {
+      const size_t at = (((size_t)t * a.S + q) * a.H + i) * 8 + b8;
+      dsr[at] = acc[q];
+      if (a.events) a.sg[at] = surrogate(vs[q * 8 + b8][il] - a.theta, a.slope, false);
+    }
 }
 
 // x + the value of another lane of the 16-lane row, by DPP.
@@ -708,10 +1048,10 @@ __device__ __forceinline__ float row_sum(float x) {
 // (7.4 with a wavefront per neuron that gathers 256-byte rows from memory, the form kept for
 // more neurons), 3.6 us at 19 x 201 (7.7).
 // lam_next / lam_out: slices of steps t + 1 and t; lam_out holds the readout part on entry.
-// V_t of (neuron, batch element) is at v_t[i * v_i + b * v_b].
+// v_t: V_t as [H][64], or, in the event-driven form, its surrogate derivative in the slices.
 constexpr int kAdjointAhead = 8;  // rounds of synapses requested before the barrier
-__global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float *v_t, uint32_t v_i, size_t v_b,
-                                                        const float *lam_next, float *lam_out) {
+__global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float *v_t, const float *lam_next,
+                                                        float *lam_out) {
   extern __shared__ float4 lam_sl[];  // [H][2]
   const uint32_t slice = blockIdx.x % a.S, block = blockIdx.x / a.S;
   const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
@@ -731,7 +1071,7 @@ __global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float 
   const uint32_t b = slice * 8u + b4 * 4u + (p & 3u);
   const size_t own = ((size_t)slice * a.H + il) * 8 + (b & 7u);
   const float ln = lam_next[own], readout = lam_out[own];
-  const float vt = b < a.B ? v_t[(size_t)il * v_i + b * v_b] : 0.0f;
+  const float vt = a.events ? v_t[own] : v_t[(size_t)il * 64 + b];
   const float4 *src = reinterpret_cast<const float4 *>(lam_next + (size_t)slice * a.H * 8);
   for (uint32_t x0 = threadIdx.x; x0 < a.H * 2u; x0 += 4u * 1024u) {
     float4 v[4];
@@ -766,8 +1106,8 @@ __global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float 
   const float sum = p == 0 ? acc.x : p == 1 ? acc.y : p == 2 ? acc.z : acc.w;
   float ds = readout + sum;
   if (!a.detach_reset) ds = ds - a.theta * ln;
-  const float z = vt - a.theta;
-  lam_out[own] = a.beta * ln + surrogate(z, a.slope, a.smooth != 0) * ds;
+  const float g = a.events ? vt : surrogate(vt - a.theta, a.slope, a.smooth != 0);
+  lam_out[own] = a.beta * ln + g * ds;
 }
 
 // Batch masks of a [T][rows][64] trajectory: bits[r][t] bit b = (val[t][r][b] != 0) for
@@ -896,6 +1236,51 @@ __global__ __launch_bounds__(256) void k_grad_out(BpttArgs a) {
   if (b == 0) a.g_w_out[(size_t)i * a.O + o] = sum;
 }
 
+// The same from the spike masks: a wavefront per (neuron, block of kOutBlock readouts) visits
+// the steps at which the neuron spikes in some batch element and adds the readout adjoints of
+// the lanes (batch elements) that spike.
+constexpr int kOutBlock = 4;
+constexpr int kOutSteps = 8;
+__global__ __launch_bounds__(256) void k_grad_out_events(BpttArgs a) {
+  const uint32_t n_blocks = (a.O + kOutBlock - 1) / kOutBlock;
+  const uint32_t w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  if (w >= a.H * n_blocks) return;
+  const uint32_t i = w / n_blocks, o0 = w % n_blocks * kOutBlock, lane = lane_id();
+  const uint32_t no = std::min<uint32_t>(kOutBlock, a.O - o0);
+  float acc[kOutBlock] = {};
+  for (uint32_t t0 = 0; t0 < a.T; t0 += kWave) {
+    const uint64_t mine = t0 + lane < a.T ? a.sbits[(size_t)i * a.T + t0 + lane] : 0ull;
+    // kOutSteps steps requested together (the last one again where fewer are left, unused)
+    uint64_t any = __ballot(mine != 0);
+    while (any) {
+      float l[kOutSteps][kOutBlock];
+      uint64_t on[kOutSteps];
+      uint32_t k = 0;
+#pragma unroll
+      for (int u = 0; u < kOutSteps; ++u) {
+        const bool more = any != 0;  // uniform
+        if (more) k = (uint32_t)__builtin_ctzll(any);
+        any &= any - 1;
+        on[u] = more ? lane_read64(mine, k) : 0ull;
+        const float *lu = a.lamu + ((size_t)(t0 + k) * a.O + o0) * 64 + lane;
+#pragma unroll
+        for (int q = 0; q < kOutBlock; ++q) l[u][q] = lu[std::min<uint32_t>(q, no - 1) * 64];
+      }
+#pragma unroll
+      for (int u = 0; u < kOutSteps; ++u) {
+        const bool mine_on = __builtin_amdgcn_inverse_ballot_w64(on[u]);
+#pragma unroll
+        for (int q = 0; q < kOutBlock; ++q) acc[q] += mine_on ? l[u][q] : 0.0f;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kOutBlock; ++q) {
+    const float sum = wave_sum(acc[q]);
+    if (lane == 0 && (uint32_t)q < no) a.g_w_out[(size_t)i * a.O + o0 + q] = sum;
+  }
+}
+
 __global__ void k_fill(float *p, uint64_t n, float v) {
   const uint64_t idx = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx < n) p[idx] = v;
@@ -935,18 +1320,40 @@ static void gather_weights(const BpttArgs &a, hipStream_t s) {
 // runtime can capture it once per plan in a HIP graph and replay it on every call.
 
 hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s) {
-  gather_weights(a, s);
+  if (!a.events) gather_weights(a, s);
   // flags[0] is set below if some input is neither 0 nor 1; flags[1] only by the backward
   // pass of a smooth-mode plan
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
   hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
                      a.T, a.C);
+  if (a.events) {
+    // every kernel of the pass is launched here: they are few, and some read the caller's arrays
+    const uint64_t nnz = std::max(a.nnz_in, a.nnz_rec);
+    if (nnz) hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
+    if (a.nnz_in)
+      hipLaunchKernelGGL(k_gather_t, dim3(blocks_for(a.nnz_in, 256)), dim3(256), 0, s, a.w_in, a.in_t_edge,
+                         a.w_in_t, a.nnz_in);
+    hipLaunchKernelGGL(k_input_rows, dim3(blocks_for((uint64_t)a.B * a.T, 4), blocks_for(a.Hp / 256, kInputBlocks)),
+                       dim3(256), 0, s, a, x);
+    hipLaunchKernelGGL(k_input_current_values, dim3(std::min<uint32_t>(blocks_for((uint64_t)a.T * a.H, 4), kValuesGrid)),
+                       dim3(256), 0, s, a);
+    // whole wavefronts up to Hp, a multiple of 256
+    const size_t lds = (size_t)kSeqChunk * a.Hp * sizeof(float);
+    if (a.Hp <= 256) hipLaunchKernelGGL(k_hidden_seq<1>, dim3(a.B), dim3(a.Hp), lds, s, a);
+    else if (a.Hp <= 512) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
+    else hipLaunchKernelGGL(k_hidden_seq<4>, dim3(a.B), dim3(a.Hp / 4), lds, s, a);
+    hipLaunchKernelGGL(k_spike_masks, dim3(a.nw, blocks_for(a.T, kMaskBlock)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_readout_events, dim3(blocks_for((uint64_t)a.B * a.T, 4)), dim3(256), 0, s, a, a.ro);
+    hipLaunchKernelGGL(k_readout_scan_events, dim3(a.B, blocks_for(a.O, 64)), dim3(64), 0, s, a, a.ro);
+    return hipGetLastError();
+  }
   const hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
 
 // g: the plan's arguments with w_out = w_out_c
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s) {
+  if (g.events) return hipSuccess;  // all in the prologue
   // the inputs' batch masks and flags[0] come from the prologue's transpose
   hipLaunchKernelGGL(k_input_current, dim3(blocks_for((uint64_t)((g.T + kMaskSteps - 1) / kMaskSteps) * g.H, 4)),
                      dim3(256), 0, s, g);
@@ -985,7 +1392,7 @@ hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float
 }
 
 hipError_t bptt_backward_prologue(const BpttArgs &a, const float *g_loss, hipStream_t s) {
-  gather_weights(a, s);
+  if (!a.events) gather_weights(a, s);
   hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   if (a.S && a.nnz_rec)
     hipLaunchKernelGGL(k_scatter_pairs, dim3(blocks_for(a.nnz_rec, 256)), dim3(256), 0, s, a.w_rec, a.adj_pos,
@@ -1013,6 +1420,15 @@ hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
     hipLaunchKernelGGL(k_readout_adjoint_slice, dim3(blocks_for(g.H, kAdjointRows), g.T), dim3(256), 0, s, g, g.lamv);
   else
     hipLaunchKernelGGL(k_readout_adjoint, dim3(blocks_for((uint64_t)g.T * g.H, 4)), dim3(256), 0, s, g, g.lamv);
+  const size_t slices = (size_t)g.S * g.H * 8;
+  if (g.events) {
+    // the forward pass kept the membranes of every step
+    for (uint32_t t = g.T; t-- > 0;)
+      hipLaunchKernelGGL(k_adjoint_slice, dim3(g.S * blocks_for(g.H, kAdjointRows)), dim3(1024), (size_t)g.H * 32, s, g,
+                         g.sg + t * slices,
+                         t + 1 < g.T ? g.lamv + (t + 1) * slices : g.lam_carry, g.lamv + t * slices);
+    return hipGetLastError();
+  }
   const dim3 grid(blocks_for(g.H, 4));
   const uint32_t n_seg = (g.T + g.K - 1) / g.K;
   for (int32_t seg = (int32_t)n_seg - 1; seg >= 0; --seg) {
@@ -1031,10 +1447,9 @@ hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
     for (int32_t k = (int32_t)len - 1; k >= 0; --k) {
       const uint32_t t = t0 + (uint32_t)k;
       if (g.S) {
-        const size_t step = (size_t)g.S * g.H * 8;
         hipLaunchKernelGGL(k_adjoint_slice, dim3(g.S * blocks_for(g.H, kAdjointRows)), dim3(1024), (size_t)g.H * 32, s, g,
-                           g.vseg + (size_t)k * g.H * 64, 64u, (size_t)1,
-                           t + 1 < g.T ? g.lamv + (t + 1) * step : g.lam_carry, g.lamv + t * step);
+                           g.vseg + (size_t)k * g.H * 64,
+                           t + 1 < g.T ? g.lamv + (t + 1) * slices : g.lam_carry, g.lamv + t * slices);
         continue;
       }
       const float *lam_next = t + 1 < g.T ? g.lamv + (size_t)(t + 1) * g.H * 64 : g.lam_carry;
@@ -1045,16 +1460,32 @@ hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The sliced adjoint's dynamic LDS, once per plan.
+// The dynamic LDS of the plan's kernels, once per plan.
 hipError_t bptt_prepare(const BpttArgs &a) {
-  if (!a.S) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_adjoint_slice),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kSliceMaxNeurons * 32u));
+  auto allow = [](const void *k, size_t bytes) {
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  hipError_t e = hipSuccess;
+  if (a.S) e = allow(reinterpret_cast<const void *>(&k_adjoint_slice), kSliceMaxNeurons * 32u);
+  if (e == hipSuccess && a.events) {
+    e = allow(reinterpret_cast<const void *>(&k_hidden_seq<4>), kEventMaxNeurons * kSeqChunk * sizeof(float));
+  }
+  return e;
+}
+
+hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s) {
+  const uint64_t n = (uint64_t)((a.T + a.K - 1) / a.K) * a.H * 64;
+  hipLaunchKernelGGL(k_trace_v, dim3(blocks_for(n, 256)), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 // the gradients, written to the caller's arrays
 hipError_t bptt_backward_epilogue(const BpttArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_grad_out, dim3(blocks_for((uint64_t)a.H * a.O, 4)), dim3(256), 0, s, a);
+  if (a.events)
+    hipLaunchKernelGGL(k_grad_out_events, dim3(blocks_for((uint64_t)a.H * blocks_for(a.O, kOutBlock), 4)), dim3(256), 0, s,
+                       a);
+  else
+    hipLaunchKernelGGL(k_grad_out, dim3(blocks_for((uint64_t)a.H * a.O, 4)), dim3(256), 0, s, a);
   if (a.nnz_in + a.nnz_rec)
     hipLaunchKernelGGL(k_grad_edges, dim3(a.H), dim3(kGradBlock), (size_t)std::min(kGradChunk, a.T) * 64 * 4, s, a,
                        a.xbits, a.sbits, a.flags);

@@ -1791,7 +1791,38 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   uint64_t max_deg = 0;
   for (uint32_t j = 0; j < a.H; ++j) max_deg = std::max<uint64_t>(max_deg, rt_ptr[j + 1] - rt_ptr[j]);
   a.ell_w = 0;
-  if (nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {
+  a.Hp = (a.H + 255) / 256 * 256;
+  a.nw = (a.H + 63) / 64;
+  a.events = !a.smooth && a.H <= snn::kEventMaxNeurons && (uint64_t)a.C * a.Hp <= snn::kEventMaxInput ? 1u : 0u;
+  if (a.events) {
+    // dense rows of both weight matrices and the target-major pairs of W_rec
+    a.col_w = (uint32_t)max_deg;
+    std::vector<uint32_t> in_pos(nnz_in), rec_pos(nnz_rec), col_pos(nnz_rec);
+    for (uint32_t c = 0; c < a.C; ++c)
+      for (uint64_t e = in_ptr[c]; e < in_ptr[c + 1]; ++e) in_pos[e] = c * a.Hp + (uint32_t)in_col[e];
+    for (uint32_t i = 0; i < a.H; ++i)
+      for (uint64_t e = rec_ptr[i]; e < rec_ptr[i + 1]; ++e) rec_pos[e] = i * a.Hp + (uint32_t)rec_col[e];
+    std::vector<uint2> pair(std::max<size_t>(1, (size_t)a.col_w * a.Hp), make_uint2(0u, 0u));
+    for (uint32_t j = 0; j < a.H; ++j)
+      for (uint64_t x = rt_ptr[j]; x < rt_ptr[j + 1]; ++x) {
+        const uint32_t at = (uint32_t)(x - rt_ptr[j]) * a.Hp + j;
+        pair[at].x = (uint32_t)rt_src[x];
+        col_pos[rt_edge[x]] = at;
+      }
+    a.in_pos = upload(pool, in_pos);
+    a.rec_pos = upload(pool, rec_pos);
+    a.col_pos = upload(pool, col_pos);
+    a.col_pair = upload(pool, pair);
+    const size_t n_in = (size_t)a.C * a.Hp, n_rec = (size_t)a.H * a.Hp;
+    a.dense_in = dev_array<float>(pool, n_in);
+    a.dense_rec = dev_array<float>(pool, n_rec);
+    check(hipMemsetAsync(a.dense_in, 0, n_in * 4, pool->stream), "clear dense weights");
+    check(hipMemsetAsync(a.dense_rec, 0, n_rec * 4, pool->stream), "clear dense weights");
+    a.vall = dev_array<float>(pool, (size_t)a.B * a.T * a.Hp);
+    a.spk = dev_array<uint64_t>(pool, (size_t)a.B * a.T * a.nw);
+    check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
+  }
+  if (!a.events && nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {
     const uint32_t wd = (uint32_t)((max_deg + 63) / 64 * 64);
     std::vector<int32_t> es((size_t)a.H * wd, 0);
     std::vector<uint32_t> ee((size_t)a.H * wd, 0xFFFFFFFFu), el(a.H);
@@ -1829,23 +1860,26 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     a.adj_pos = upload(pool, pos);
     a.adj_len = upload(pool, len);
     check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
-    check(snn::bptt_prepare(a), "bptt prepare");
   }
+  check(snn::bptt_prepare(a), "bptt prepare");
   a.flags = dev_array<uint32_t>(pool, 2);
   a.w_in_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_in));
   a.w_rec_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
   if (!a.S) a.w_rec_c = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
   a.w_out_c = dev_array<float>(pool, (size_t)a.H * a.O);
   a.xt = dev_array<float>(pool, (size_t)a.T * a.C * 64);
-  a.iin = dev_array<float>(pool, (size_t)a.T * HB);
-  a.s = dev_array<float>(pool, (size_t)a.T * HB);
+  if (!a.events) {  // the event-driven form keeps its trajectory in vall and spk
+    a.iin = dev_array<float>(pool, (size_t)a.T * HB);
+    a.s = dev_array<float>(pool, (size_t)a.T * HB);
+    a.vtmp = dev_array<float>(pool, 2 * HB);
+    a.vseg = dev_array<float>(pool, (size_t)a.K * HB);
+  }
   a.vck = dev_array<float>(pool, n_seg * HB);
-  a.vtmp = dev_array<float>(pool, 2 * HB);
-  a.vseg = dev_array<float>(pool, (size_t)a.K * HB);
   a.ro = dev_array<float>(pool, (size_t)a.T * a.O * 64);
   a.lamu = dev_array<float>(pool, (size_t)a.T * a.O * 64);
-  a.lamv = dev_array<float>(pool, (size_t)a.T * HB);
+  a.lamv = dev_array<float>(pool, a.S ? (size_t)a.T * a.S * a.H * 8 : (size_t)a.T * HB);
   a.lam_carry = dev_array<float>(pool, HB);
+  if (a.events) a.sg = dev_array<float>(pool, (size_t)a.T * a.S * a.H * 8);
   a.m = dev_array<float>(pool, (size_t)a.B * a.O);
   a.dm = dev_array<float>(pool, (size_t)a.B * a.O);
   a.tmax = dev_array<int32_t>(pool, (size_t)a.B * a.O);
@@ -2371,7 +2405,7 @@ snn_status snn_bptt_forward(snn_bptt *p, const float *x, const float *w_in, cons
     check(snn::bptt_forward_prologue(a, x, s), "bptt forward");
     snn::BpttArgs g = p->args;  // the body reads the plan's buffers only
     g.w_out = g.w_out_c;
-    bptt_body(p, p->g_fwd, s, [&](hipStream_t st) { return snn::bptt_forward_body(g, st); });
+    if (!a.events) bptt_body(p, p->g_fwd, s, [&](hipStream_t st) { return snn::bptt_forward_body(g, st); });
     check(snn::bptt_forward_epilogue(a, labels, loss, s), "bptt forward");
     p->forwards++;
   });
@@ -2409,12 +2443,26 @@ snn_status snn_bptt_get_trace(snn_bptt *p, float *spikes, float *v_checkpoints, 
     const snn::BpttArgs &a = p->args;
     hipStream_t s = stream ? (hipStream_t)stream : p->pool.stream;
     const size_t HB = (size_t)a.H * 64, n_seg = (a.T + a.K - 1) / a.K;
-    if (spikes) check(hipMemcpyAsync(spikes, a.s, (size_t)a.T * HB * 4, hipMemcpyDeviceToHost, s), "copy");
+    std::vector<uint64_t> masks;
+    if (a.events) {
+      if (v_checkpoints) check(snn::bptt_trace_v(a, s), "trace");
+      if (spikes) {
+        masks.resize((size_t)a.H * a.T);
+        check(hipMemcpyAsync(masks.data(), a.sbits, masks.size() * 8, hipMemcpyDeviceToHost, s), "copy");
+      }
+    } else if (spikes) {
+      check(hipMemcpyAsync(spikes, a.s, (size_t)a.T * HB * 4, hipMemcpyDeviceToHost, s), "copy");
+    }
     if (v_checkpoints) check(hipMemcpyAsync(v_checkpoints, a.vck, n_seg * HB * 4, hipMemcpyDeviceToHost, s), "copy");
     if (readout_max) check(hipMemcpyAsync(readout_max, a.m, (size_t)a.B * a.O * 4, hipMemcpyDeviceToHost, s), "copy");
     if (readout_argmax)
       check(hipMemcpyAsync(readout_argmax, a.tmax, (size_t)a.B * a.O * 4, hipMemcpyDeviceToHost, s), "copy");
     check(hipStreamSynchronize(s), "sync");
+    if (!masks.empty())  // the event-driven form holds spikes as batch masks
+      for (uint32_t t = 0; t < a.T; ++t)
+        for (uint32_t i = 0; i < a.H; ++i)
+          for (uint32_t b = 0; b < 64; ++b)
+            spikes[((size_t)t * a.H + i) * 64 + b] = (float)((masks[(size_t)i * a.T + t] >> b) & 1u);
   });
 }
 

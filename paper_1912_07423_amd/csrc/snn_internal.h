@@ -216,9 +216,23 @@ constexpr uint32_t kEllMaxNeurons = 8192;
 // The sliced membrane adjoint: a slice of all neurons (32 bytes each) is staged in LDS, and
 // the synapses are held as padded rows of at most kSliceMaxPairs entries in all.
 constexpr uint32_t kSliceMaxNeurons = 4096;
+// The event-driven forward pass holds the weights as dense rows: at most 2,048 hidden neurons
+// (16 MB of recurrent weights; a presynaptic spike costs a whole row of them) and 64 MB of
+// input weights.
+constexpr uint32_t kEventMaxNeurons = 2048;
+constexpr uint64_t kEventMaxInput = 1ull << 24;
 constexpr uint64_t kSliceMaxPairs = 1ull << 26;
 struct BpttArgs {
   uint32_t B, T, C, H, O, K;
+  uint32_t events;             // event-driven forward pass (spiking mode); then also:
+  uint32_t Hp, nw, col_w;      // columns of a dense row (multiple of 256), words of 64 neurons,
+                               // longest column of W_rec
+  float *dense_in, *dense_rec; // [C][Hp], [H][Hp]
+  uint2 *col_pair;             // [col_w][Hp] (source, weight) in ascending source order
+  const uint32_t *in_pos, *rec_pos, *col_pos;  // place of each CSR edge in them
+  float *vall;                 // [T][B][Hp] input currents, then membranes of every step
+  float *sg;                   // [T][S][H][8] surrogate derivatives (backward pass)
+  uint64_t *spk;               // [B][T][nw] spikes of every step
   uint32_t S;                  // slices of 8 batch elements of the membrane adjoint (0: not sliced)
   uint32_t adj_w;              // width of its padded rows of W_rec, a multiple of 16
   uint2 *adj_pair;             // [H][adj_w] (target, weight); padding (0, 0)
@@ -256,6 +270,7 @@ struct BpttArgs {
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
 hipError_t bptt_prepare(const BpttArgs &a);
+hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s);  // fills vck (event-driven plans)
 hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s);
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s);
 hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float *loss, hipStream_t s);

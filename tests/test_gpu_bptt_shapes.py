@@ -1,7 +1,9 @@
 """The surrogate-gradient form at the sizes where its kernels change form or have remainders,
 against the oracle with the tolerances of test_gpu_bptt: batches that fill slices of 8 or not,
-hidden sizes around the 32 neurons of an adjoint workgroup and beyond the sliced form's limit,
-synapse rows longer than the rounds requested ahead, and more readouts than one LDS chunk."""
+hidden sizes around the 32 neurons of an adjoint workgroup, the words of a wavefront and the
+limits of the event-driven and the sliced form, step counts around a chunk, synapse rows
+longer than the rounds requested ahead, more readouts than one LDS chunk or wavefront, and
+spike rates at which the forward pass turns from rows to columns."""
 import numpy as np
 import pytest
 
@@ -25,6 +27,35 @@ def _inputs(B, T, C, H, O, p_in=0.4, p_rec=0.3, seed=31):
 @pytest.mark.parametrize("smooth", [False, True])
 def test_slices_and_neuron_blocks(B, H, smooth):
     _compare(_inputs(B, 20, 15, H, 4), 6, smooth=smooth)
+
+
+@pytest.mark.parametrize("H", [255, 257, 512, 513, 1025])
+def test_words_per_wavefront(H):
+    _compare(_inputs(5, 18, 12, H, 3, p_rec=0.05), 5)
+
+
+@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 33])
+def test_chunks_of_steps(T):
+    _compare(_inputs(7, T, 25, 70, 3), 4)
+
+
+@pytest.mark.parametrize("C", [1, 63, 64, 65, 130])
+def test_input_words(C):
+    _compare(_inputs(6, 12, C, 50, 3, p_in=0.9), 4)
+
+
+@pytest.mark.parametrize("H,p_rec", [(40, 0.05), (150, 0.02), (700, 0.01)])
+def test_many_spikes_against_short_columns(H, p_rec):
+    """Inputs strong enough that most neurons spike at most steps: more sources than twice the
+    longest column."""
+    d = _inputs(6, 24, 20, H, 3, p_rec=p_rec)
+    d["w_in"] = np.abs(d["w_in"]) * 3
+    _, fw = _compare(d, 7)
+    assert fw["s"].sum(axis=2).max() > 2 * d["mask_rec"].sum(axis=0).max()
+
+
+def test_wide_hidden_layer_without_the_event_driven_form():
+    _compare(_inputs(4, 10, 12, 2049, 2, p_rec=0.01), 4)
 
 
 @pytest.mark.parametrize("O", [1, 32, 33, 70])

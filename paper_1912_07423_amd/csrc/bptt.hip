@@ -1129,6 +1129,7 @@ __global__ __launch_bounds__(256) void k_bits(const float *val, uint32_t rows, u
   }
 }
 
+constexpr uint32_t kXcdCount = 8;  // XCDs take workgroups round-robin
 constexpr int kGradBlock = 256;
 constexpr uint32_t kGradChunk = 128;  // steps of lamV staged in LDS at a time (32 KB)
 constexpr int kMaskAhead = 8;         // mask words in flight per lane
@@ -1213,6 +1214,143 @@ __global__ __launch_bounds__(kGradBlock) void k_grad_edges(BpttArgs a, const uin
       }
     }
     if (live) (is_in ? a.g_w_in : a.g_w_rec)[edge] = total;
+  }
+}
+
+// ---- sparse-weight gradients from event lists (the event-driven form) ------------------------
+// A source's events of a chunk of kListChunk steps, as 16-bit indices into the chunk's
+// lamV_t[b] values ((t - t_chunk) 64 + b, ascending), padded to whole groups of 8 with the
+// index of a zero: lanes that walk lists of their own diverge only in the lists' lengths,
+// where lanes that walk 64-bit masks step by step wait for the busiest lane in every step.
+constexpr uint32_t kListChunk = 128;
+constexpr uint32_t kListCap = kListChunk * 64 / 4;  // events of a list: a quarter of the chunk
+constexpr uint32_t kListStride = kListCap + 8;      // one group is read ahead
+constexpr uint32_t kListZero = kListChunk * 64;
+
+// Lists of the inputs (sources 0 .. C - 1, step t) and of the hidden neurons (C .. C + H - 1,
+// step t - 1); a wavefront per (source, chunk).  A source with more than kListCap events in
+// the chunk gets its count only.
+__global__ __launch_bounds__(256) void k_event_lists(BpttArgs a) {
+  const uint32_t w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t n_chunks = (a.T + kListChunk - 1) / kListChunk;
+  if (w >= (a.C + a.H) * n_chunks) return;
+  const uint32_t r = w / n_chunks, c = w % n_chunks, lane = lane_id();
+  const bool is_in = r < a.C;
+  const uint64_t *row = is_in ? a.xbits + (size_t)r * a.T : a.sbits + (size_t)(r - a.C) * a.T;
+  const uint32_t lag = is_in ? 0u : 1u;
+  uint16_t *list = a.lists + (size_t)w * kListStride;
+  uint64_t m[kListChunk / 64];
+#pragma unroll
+  for (uint32_t h = 0; h < kListChunk / 64; ++h) {
+    const uint32_t t = c * kListChunk + h * 64u + lane;
+    m[h] = t < a.T && t >= lag ? row[t - lag] : 0ull;
+  }
+  uint32_t n = 0, at[kListChunk / 64];
+#pragma unroll
+  for (uint32_t h = 0; h < kListChunk / 64; ++h) {
+    const uint32_t p = (uint32_t)__popcll(m[h]), incl = wave_inclusive_scan(p);
+    at[h] = n + incl - p;
+    n += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  }
+  if (lane == 0) a.list_len[w] = n;
+  if (n > kListCap) return;
+#pragma unroll
+  for (uint32_t h = 0; h < kListChunk / 64; ++h)
+    for (uint64_t x = m[h]; x; x &= x - 1) list[at[h]++] = (uint16_t)((h * 64u + lane) * 64u + (uint32_t)__builtin_ctzll(x));
+  if (lane < ((0u - n) & 7u)) list[n + lane] = (uint16_t)kListZero;
+}
+
+// One owner per synapse, as k_grad_edges: a workgroup per target j stages lamV_t[j][.] of a
+// chunk in LDS; a lane owns up to kListEdges in-edges and adds the values at its source's
+// events, eight per 16-byte list read, in four sums.  Targets are numbered so that four
+// neighbours, whose slices share cache lines, run on one XCD one after another.  Bound: the
+// LDS reads, of the longest list in each wavefront.  248,000 edges of 64 x 250, 700 -> 1,024:
+// 65 us and 5 us of lists, where walking the masks took 263.
+constexpr int kListEdges = 4;
+__global__ __launch_bounds__(kGradBlock) void k_grad_lists(BpttArgs a) {
+  __shared__ float lam_c[kListChunk * 64 + 1];
+  const uint32_t g = blockIdx.x / kXcdCount;
+  const uint32_t j = ((g >> 2) * kXcdCount + blockIdx.x % kXcdCount) * 4u + (g & 3u);
+  if (j >= a.H) return;
+  const uint64_t in0 = a.in_t_ptr[j], rec0 = a.rec_t_ptr[j];
+  const uint32_t n_in = (uint32_t)(a.in_t_ptr[j + 1] - in0), n_rec = (uint32_t)(a.rec_t_ptr[j + 1] - rec0);
+  const uint32_t deg = n_in + n_rec, n_chunks = (a.T + kListChunk - 1) / kListChunk;
+  const bool x_bits = a.flags[0] == 0;
+  if (threadIdx.x == 0) lam_c[kListZero] = 0.0f;
+  for (uint32_t base = 0; base < deg; base += kGradBlock * kListEdges) {
+    float total[kListEdges];
+    uint32_t src[kListEdges];
+#pragma unroll
+    for (int p = 0; p < kListEdges; ++p) {
+      const uint32_t k = base + (uint32_t)p * kGradBlock + threadIdx.x;
+      total[p] = 0.0f;
+      src[p] = k < n_in ? (uint32_t)a.in_t_src[in0 + k] : k < deg ? a.C + (uint32_t)a.rec_t_src[rec0 + (k - n_in)] : 0u;
+    }
+    for (uint32_t c = 0; c < n_chunks; ++c) {
+      const uint32_t tc = c * kListChunk, len = min(kListChunk, a.T - tc);
+      __syncthreads();  // the previous chunk has been read by every lane
+      for (uint32_t x0 = threadIdx.x; x0 < len * 64; x0 += 8 * kGradBlock) {
+        float v[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) {
+          const uint32_t x = std::min<uint32_t>(x0 + q * kGradBlock, len * 64 - 1), b = x & 63u;
+          v[q] = b < a.S * 8u ? a.lamv[slice_index(a, tc + (x >> 6), b, j)] : 0.0f;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q)
+          if (x0 + q * kGradBlock < len * 64) lam_c[x0 + q * kGradBlock] = v[q];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int p = 0; p < kListEdges; ++p) {
+        const uint32_t k = base + (uint32_t)p * kGradBlock + threadIdx.x;
+        if (k >= deg) continue;
+        const bool is_in = k < n_in;
+        if (is_in && !x_bits) {  // inputs other than 0 and 1
+          for (uint32_t u = 0; u < len; ++u) {
+            const float *val = a.xt + ((size_t)(tc + u) * a.C + src[p]) * 64, *lt = lam_c + u * 64;
+            float part = 0.0f;
+            for (uint32_t b = 0; b < a.B; ++b) part += val[b] * lt[b];
+            total[p] += part;
+          }
+          continue;
+        }
+        const size_t id = (size_t)src[p] * n_chunks + c;
+        const uint32_t n = a.list_len[id];
+        if (n > kListCap) {  // too many events for a list: the masks
+          const uint32_t lag = is_in ? 0u : 1u;
+          const uint64_t *row = is_in ? a.xbits + (size_t)src[p] * a.T : a.sbits + (size_t)(src[p] - a.C) * a.T;
+          for (uint32_t u = tc < lag ? 1u : 0u; u < len; ++u) {
+            float part = 0.0f;
+            for (uint64_t m = row[tc + u - lag]; m; m &= m - 1) part += lam_c[u * 64 + (uint32_t)__builtin_ctzll(m)];
+            total[p] += part;
+          }
+          continue;
+        }
+        const uint4 *list = reinterpret_cast<const uint4 *>(a.lists + id * kListStride);
+        float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+        uint4 e = list[0];
+        for (uint32_t q = 0; q < n; q += 8) {
+          const uint4 nx = list[q / 8 + 1];
+          s0 += lam_c[e.x & 0xFFFFu];
+          s1 += lam_c[e.x >> 16];
+          s2 += lam_c[e.y & 0xFFFFu];
+          s3 += lam_c[e.y >> 16];
+          s0 += lam_c[e.z & 0xFFFFu];
+          s1 += lam_c[e.z >> 16];
+          s2 += lam_c[e.w & 0xFFFFu];
+          s3 += lam_c[e.w >> 16];
+          e = nx;
+        }
+        total[p] += (s0 + s1) + (s2 + s3);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < kListEdges; ++p) {
+      const uint32_t k = base + (uint32_t)p * kGradBlock + threadIdx.x;
+      if (k < n_in) a.g_w_in[a.in_t_edge[in0 + k]] = total[p];
+      else if (k < deg) a.g_w_rec[a.rec_t_edge[rec0 + (k - n_in)]] = total[p];
+    }
   }
 }
 
@@ -1473,6 +1611,9 @@ hipError_t bptt_prepare(const BpttArgs &a) {
   return e;
 }
 
+uint64_t bptt_lists(const BpttArgs &a) { return (uint64_t)(a.C + a.H) * blocks_for(a.T, kListChunk); }
+uint32_t bptt_list_stride() { return kListStride; }
+
 hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s) {
   const uint64_t n = (uint64_t)((a.T + a.K - 1) / a.K) * a.H * 64;
   hipLaunchKernelGGL(k_trace_v, dim3(blocks_for(n, 256)), dim3(256), 0, s, a);
@@ -1486,7 +1627,11 @@ hipError_t bptt_backward_epilogue(const BpttArgs &a, hipStream_t s) {
                        a);
   else
     hipLaunchKernelGGL(k_grad_out, dim3(blocks_for((uint64_t)a.H * a.O, 4)), dim3(256), 0, s, a);
-  if (a.nnz_in + a.nnz_rec)
+  if (a.events && a.nnz_in + a.nnz_rec) {
+    const uint32_t n_lists = (a.C + a.H) * blocks_for(a.T, kListChunk);
+    hipLaunchKernelGGL(k_event_lists, dim3(blocks_for(n_lists, 4)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_grad_lists, dim3(blocks_for(a.H, 4 * kXcdCount) * 4 * kXcdCount), dim3(kGradBlock), 0, s, a);
+  } else if (a.nnz_in + a.nnz_rec)
     hipLaunchKernelGGL(k_grad_edges, dim3(a.H), dim3(kGradBlock), (size_t)std::min(kGradChunk, a.T) * 64 * 4, s, a,
                        a.xbits, a.sbits, a.flags);
   return hipGetLastError();

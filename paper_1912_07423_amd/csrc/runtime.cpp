@@ -1820,6 +1820,8 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     check(hipMemsetAsync(a.dense_rec, 0, n_rec * 4, pool->stream), "clear dense weights");
     a.vall = dev_array<float>(pool, (size_t)a.B * a.T * a.Hp);
     a.spk = dev_array<uint64_t>(pool, (size_t)a.B * a.T * a.nw);
+    a.lists = dev_array<uint16_t>(pool, snn::bptt_lists(a) * snn::bptt_list_stride());
+    a.list_len = dev_array<uint32_t>(pool, snn::bptt_lists(a));
     check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
   }
   if (!a.events && nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {

@@ -232,6 +232,8 @@ struct BpttArgs {
   const uint32_t *in_pos, *rec_pos, *col_pos;  // place of each CSR edge in them
   float *vall;                 // [T][B][Hp] input currents, then membranes of every step
   float *sg;                   // [T][S][H][8] surrogate derivatives (backward pass)
+  uint16_t *lists;             // event lists of every source and chunk of steps
+  uint32_t *list_len;          // their lengths
   uint64_t *spk;               // [B][T][nw] spikes of every step
   uint32_t S;                  // slices of 8 batch elements of the membrane adjoint (0: not sliced)
   uint32_t adj_w;              // width of its padded rows of W_rec, a multiple of 16
@@ -270,6 +272,8 @@ struct BpttArgs {
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
 hipError_t bptt_prepare(const BpttArgs &a);
+uint64_t bptt_lists(const BpttArgs &a);  // number of event lists, entries held for each
+uint32_t bptt_list_stride();
 hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s);  // fills vck (event-driven plans)
 hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s);
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s);

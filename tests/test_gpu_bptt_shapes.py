@@ -58,6 +58,26 @@ def test_wide_hidden_layer_without_the_event_driven_form():
     _compare(_inputs(4, 10, 12, 2049, 2, p_rec=0.01), 4)
 
 
+@pytest.mark.parametrize("T", [127, 128, 129, 300])
+def test_chunks_of_event_lists(T):
+    _compare(_inputs(4, T, 20, 33, 3), 25)
+
+
+def test_more_events_than_a_list_holds():
+    """Inputs active in most steps, on a batch that fills a wavefront: counts beyond a quarter
+    of a chunk, beside inputs that stay below it."""
+    d = W.bptt_inputs(batch=64, steps=140, n_in=12, n_hidden=40, n_out=3, p_in=0.5, p_rec=0.3, rate_lo=0.0,
+                      rate_hi=900.0, seed=33)
+    on = d["x"][:, :128].sum(axis=(0, 1))
+    assert (on > 2048).any() and (on < 2048).any()
+    _compare(d, 25)
+
+
+def test_more_edges_per_target_than_one_pass():
+    _compare(W.bptt_inputs(batch=3, steps=9, n_in=1100, n_hidden=37, n_out=2, p_in=1.0, p_rec=0.5, rate_lo=20.0,
+                           rate_hi=60.0, seed=34), 4)
+
+
 @pytest.mark.parametrize("O", [1, 32, 33, 70])
 def test_readouts(O):
     _compare(_inputs(10, 17, 12, 40, O), 5)

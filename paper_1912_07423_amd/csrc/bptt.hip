@@ -320,9 +320,26 @@ __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a) {
   for (uint64_t w = first; w < (uint64_t)a.T * a.H; w += (uint64_t)gridDim.x * 4) {
     const uint32_t t = (uint32_t)(w / a.H), j = (uint32_t)(w % a.H);
     const float *xt = a.xt + (size_t)t * a.C * 64;
-    const float sum = ordered_gather_sum(0.0f, a.in_t_ptr[j], a.in_t_ptr[j + 1], a.in_t_src, a.w_in_t, xt, b);
-    if (!a.events) a.iin[w * 64 + b] = sum;
-    else if (b < a.B) a.vall[((size_t)t * a.B + b) * a.Hp + j] = sum;
+    if (!a.events) {
+      a.iin[w * 64 + b] = ordered_gather_sum(0.0f, a.in_t_ptr[j], a.in_t_ptr[j + 1], a.in_t_src, a.w_in_t, xt, b);
+      continue;
+    }
+    // the event-driven form holds the weights as dense rows; eight terms requested together
+    float sum = 0.0f;
+    const uint64_t e1 = a.in_t_ptr[j + 1];
+    for (uint64_t e = a.in_t_ptr[j]; e < e1; e += 8) {
+      float wv[8], x[8];
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u) {
+        const uint32_t c = (uint32_t)a.in_t_src[std::min<uint64_t>(e + u, e1 - 1)];
+        wv[u] = a.dense_in[(size_t)c * a.Hp + j];
+        x[u] = xt[(size_t)c * 64 + b];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u)
+        if (e + u < e1) sum = sum + wv[u] * x[u];
+    }
+    if (b < a.B) a.vall[((size_t)t * a.B + b) * a.Hp + j] = sum;
   }
 }
 
@@ -453,6 +470,7 @@ __device__ __forceinline__ size_t row_index(const BpttArgs &a, uint32_t t, uint3
 // recurrent weights, and the target-major pairs of the many-spikes form.
 __global__ void k_scatter_weights(BpttArgs a) {
   const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < 2) a.flags[e] = 0;  // k_transpose_x, next, sets flags[0] for inputs other than 0 and 1
   if (e < a.nnz_in) a.dense_in[a.in_pos[e]] = a.w_in[e];
   if (e < a.nnz_rec) {
     const float w = a.w_rec[e];
@@ -1110,6 +1128,115 @@ __global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float 
   lam_out[own] = a.beta * ln + g * ds;
 }
 
+// ---- the membrane adjoint of one batch element in one workgroup ---------------------------
+// Batch elements do not interact in the membrane adjoint either.  Where the synapses fit the
+// registers and the LDS of a compute unit, a workgroup runs all steps of one element:
+// lamV_{t+1} of all neurons sits in LDS, and seq_p lanes share a neuron's row of W_rec.  A
+// lane's synapses keep their places for the whole pass, the first kRegs of them in registers
+// (a weight, and an LDS offset in 16 bits), the others in LDS.  The plan orders a lane's
+// synapses so that the 32 lanes that read LDS together meet few bank conflicts, and deals
+// rows to lanes by length, so that a wavefront's lanes carry equally many.  Places without a
+// synapse read a zero that follows the neurons.  One barrier per step; no step waits for a
+// launch: 0.5 us per step at 201 neurons (3.4 launched), 2.5 at 700 with 70 synapses each
+// (about 4).  104,000 synapses at 1,024 neurons do not fit; a variant that streamed what did
+// not fit from L2 took 6.2 us per step, against 4.5 launched.
+constexpr int kSeqState = 4;  // steps of (readout part, surrogate) requested ahead
+template <int kRegs>
+__global__ __launch_bounds__(1024) void k_adjoint_seq(BpttArgs a) {
+  extern __shared__ float4 more_s[];  // the places past kRegs: weights, then offsets
+  __shared__ float lam_s[2][kSeqMaxNeurons + 1];
+  // the 8 elements of a slice run on one XCD (workgroups are dealt round-robin), whose L2
+  // merges their 4-byte reads and writes of the slice's lines
+  const uint32_t b = a.S == 8 ? (blockIdx.x & 7u) * 8u + (blockIdx.x >> 3) : blockIdx.x;
+  if (b >= a.B) return;
+  const uint32_t tid = threadIdx.x, n_thr = a.seq_threads, lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const uint32_t row = a.seq_row[tid];
+  const bool owner = row != 0xFFFFFFFFu && (tid & (a.seq_p - 1u)) == 0;  // stores the row's result
+  const uint32_t i = row != 0xFFFFFFFFu ? row : 0u;
+  const uint32_t groups = a.seq_groups[wave];    // groups of four places, of them in LDS:
+  const uint32_t more = groups > kRegs / 4 ? groups - kRegs / 4 : 0u;
+  const float4 *wg = reinterpret_cast<const float4 *>(a.seq_w) + tid;
+  const uint2 *cg = reinterpret_cast<const uint2 *>(a.seq_col) + tid;
+  float4 w[kRegs / 4];
+  uint2 c[kRegs / 4];
+#pragma unroll
+  for (int g = 0; g < kRegs / 4; ++g) {
+    w[g] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    c[g] = make_uint2(0u, 0u);
+    if ((uint32_t)g < groups) {
+      w[g] = wg[(size_t)g * n_thr];
+      c[g] = cg[(size_t)g * n_thr];
+    }
+  }
+  float4 *w_more = more_s + a.seq_more[wave] * kWave + lane;
+  uint2 *c_more = reinterpret_cast<uint2 *>(more_s + a.seq_more_all * kWave) + a.seq_more[wave] * kWave + lane;
+  for (uint32_t g = 0; g < more; ++g) {  // a lane reads back only what it wrote
+    w_more[g * kWave] = wg[(size_t)(kRegs / 4 + g) * n_thr];
+    c_more[g * kWave] = cg[(size_t)(kRegs / 4 + g) * n_thr];
+  }
+  const size_t slices = (size_t)a.S * a.H * 8, own = ((size_t)(b >> 3) * a.H + i) * 8 + (b & 7u);
+  float *lam_out = a.lamv + own;
+  const float *sg = a.sg + own;
+  float ln = 0.0f, ro_t[kSeqState], sg_t[kSeqState];
+#pragma unroll
+  for (int q = 0; q < kSeqState; ++q) {
+    const uint32_t t = a.T - 1u - std::min<uint32_t>((uint32_t)q, a.T - 1u);
+    ro_t[q] = lam_out[t * slices];
+    sg_t[q] = sg[t * slices];
+  }
+  for (uint32_t x = tid; x < 2 * (kSeqMaxNeurons + 1); x += blockDim.x) (&lam_s[0][0])[x] = 0.0f;
+  __syncthreads();
+  auto add4 = [&](float4 &acc, const float4 &wv, const uint2 &cv, const char *l) {
+    acc.x = __builtin_fmaf(wv.x, *reinterpret_cast<const float *>(l + (cv.x & 0xFFFFu)), acc.x);
+    acc.y = __builtin_fmaf(wv.y, *reinterpret_cast<const float *>(l + (cv.x >> 16)), acc.y);
+    acc.z = __builtin_fmaf(wv.z, *reinterpret_cast<const float *>(l + (cv.y & 0xFFFFu)), acc.z);
+    acc.w = __builtin_fmaf(wv.w, *reinterpret_cast<const float *>(l + (cv.y >> 16)), acc.w);
+  };
+  for (uint32_t n0 = 0; n0 < a.T; n0 += kSeqState) {
+#pragma unroll
+    for (int q = 0; q < kSeqState; ++q) {
+      if (n0 + (uint32_t)q < a.T) {  // uniform
+        const uint32_t t = a.T - 1u - (n0 + (uint32_t)q);
+        const char *l = reinterpret_cast<const char *>(&lam_s[q & 1][0]);  // kSeqState is even
+        float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+        for (int g = 0; g < kRegs / 4; ++g)
+          if ((uint32_t)g < groups) add4(acc, w[g], c[g], l);
+        if (more) {
+          float4 wn = w_more[0];
+          uint2 cn = c_more[0];
+          for (uint32_t g = 0; g < more; ++g) {
+            const float4 wv = wn;
+            const uint2 cv = cn;
+            const uint32_t nx = std::min<uint32_t>(g + 1u, more - 1u);
+            wn = w_more[nx * kWave];
+            cn = c_more[nx * kWave];
+            add4(acc, wv, cv, l);
+          }
+        }
+        float sum = (acc.x + acc.y) + (acc.z + acc.w);
+        if (a.seq_p >= 2) sum = add_row_lane<0xB1>(sum);
+        if (a.seq_p >= 4) sum = add_row_lane<0x4E>(sum);
+        if (a.seq_p >= 8) sum = add_row_lane<0x141>(sum);
+        if (a.seq_p >= 16) sum = add_row_lane<0x140>(sum);
+        float ds = ro_t[q] + sum;
+        if (!a.detach_reset) ds = ds - a.theta * ln;
+        ln = a.beta * ln + sg_t[q] * ds;
+        // the state of kSeqState steps ahead
+        const uint32_t t_next = t >= (uint32_t)kSeqState ? t - kSeqState : 0u;
+        ro_t[q] = lam_out[t_next * slices];
+        sg_t[q] = sg[t_next * slices];
+        if (owner) {
+          lam_s[(q & 1) ^ 1][i] = ln;
+          lam_out[t * slices] = ln;
+        }
+        __syncthreads();
+      }
+    }
+  }
+}
+
 // Batch masks of a [T][rows][64] trajectory: bits[r][t] bit b = (val[t][r][b] != 0) for
 // b < B; flag receives 1 if any of those values is neither 0 nor 1 (the masks then do
 // not represent the values and the gradients take the general path).  A wavefront per
@@ -1440,6 +1567,11 @@ __global__ void k_scatter_pairs(const float *w, const uint32_t *pos, uint2 *pair
   if (e < nnz) pair[pos[e]].y = __float_as_uint(w[e]);
 }
 
+__global__ void k_scatter_rows(const float *w, const uint32_t *pos, float *rows, uint64_t nnz) {
+  const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < nnz) rows[pos[e]] = w[e];
+}
+
 static void gather_weights(const BpttArgs &a, hipStream_t s) {
   if (a.ell_w)
     hipLaunchKernelGGL(k_gather_ell, dim3(blocks_for((uint64_t)a.H * a.ell_w, 256)), dim3(256), 0, s, a.w_rec,
@@ -1458,19 +1590,12 @@ static void gather_weights(const BpttArgs &a, hipStream_t s) {
 // runtime can capture it once per plan in a HIP graph and replay it on every call.
 
 hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s) {
-  if (!a.events) gather_weights(a, s);
-  // flags[0] is set below if some input is neither 0 nor 1; flags[1] only by the backward
-  // pass of a smooth-mode plan
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
-  hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                     a.T, a.C);
   if (a.events) {
     // every kernel of the pass is launched here: they are few, and some read the caller's arrays
-    const uint64_t nnz = std::max(a.nnz_in, a.nnz_rec);
-    if (nnz) hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
-    if (a.nnz_in)
-      hipLaunchKernelGGL(k_gather_t, dim3(blocks_for(a.nnz_in, 256)), dim3(256), 0, s, a.w_in, a.in_t_edge,
-                         a.w_in_t, a.nnz_in);
+    const uint64_t nnz = std::max<uint64_t>(std::max(a.nnz_in, a.nnz_rec), 2);
+    hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
+                       a.T, a.C);
     hipLaunchKernelGGL(k_input_rows, dim3(blocks_for((uint64_t)a.B * a.T, 4), blocks_for(a.Hp / 256, kInputBlocks)),
                        dim3(256), 0, s, a, x);
     hipLaunchKernelGGL(k_input_current_values, dim3(std::min<uint32_t>(blocks_for((uint64_t)a.T * a.H, 4), kValuesGrid)),
@@ -1480,18 +1605,28 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t 
     if (a.Hp <= 256) hipLaunchKernelGGL(k_hidden_seq<1>, dim3(a.B), dim3(a.Hp), lds, s, a);
     else if (a.Hp <= 512) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
     else hipLaunchKernelGGL(k_hidden_seq<4>, dim3(a.B), dim3(a.Hp / 4), lds, s, a);
-    hipLaunchKernelGGL(k_spike_masks, dim3(a.nw, blocks_for(a.T, kMaskBlock)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_readout_events, dim3(blocks_for((uint64_t)a.B * a.T, 4)), dim3(256), 0, s, a, a.ro);
     hipLaunchKernelGGL(k_readout_scan_events, dim3(a.B, blocks_for(a.O, 64)), dim3(64), 0, s, a, a.ro);
     return hipGetLastError();
   }
+  gather_weights(a, s);
+  // flags[0] is set below if some input is neither 0 nor 1; flags[1] only by the backward
+  // pass of a smooth-mode plan
+  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
+  hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
+                     a.T, a.C);
   const hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
 
+// The spike masks of the latest event-driven forward pass, for the backward pass and the trace.
+hipError_t bptt_spike_masks(const BpttArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_spike_masks, dim3(a.nw, blocks_for(a.T, kMaskBlock)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
 // g: the plan's arguments with w_out = w_out_c
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s) {
-  if (g.events) return hipSuccess;  // all in the prologue
   // the inputs' batch masks and flags[0] come from the prologue's transpose
   hipLaunchKernelGGL(k_input_current, dim3(blocks_for((uint64_t)((g.T + kMaskSteps - 1) / kMaskSteps) * g.H, 4)),
                      dim3(256), 0, s, g);
@@ -1530,13 +1665,23 @@ hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float
 }
 
 hipError_t bptt_backward_prologue(const BpttArgs &a, const float *g_loss, hipStream_t s) {
-  if (!a.events) gather_weights(a, s);
-  hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
-  if (a.S && a.nnz_rec)
-    hipLaunchKernelGGL(k_scatter_pairs, dim3(blocks_for(a.nnz_rec, 256)), dim3(256), 0, s, a.w_rec, a.adj_pos,
-                       a.adj_pair, a.nnz_rec);
-  else if (e == hipSuccess && a.nnz_rec)
-    e = hipMemcpyAsync(a.w_rec_c, a.w_rec, (size_t)a.nnz_rec * 4, hipMemcpyDeviceToDevice, s);
+  hipError_t e = hipSuccess;
+  if (a.events) e = bptt_spike_masks(a, s);
+  else gather_weights(a, s);
+  if (a.seq_threads) {
+    if (a.nnz_rec)
+      hipLaunchKernelGGL(k_scatter_rows, dim3(blocks_for(a.nnz_rec, 256)), dim3(256), 0, s, a.w_rec, a.seq_pos, a.seq_w,
+                         a.nnz_rec);
+  } else {
+    // the body is replayed from a graph, with copies of the weights
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
+    if (a.S && a.nnz_rec)
+      hipLaunchKernelGGL(k_scatter_pairs, dim3(blocks_for(a.nnz_rec, 256)), dim3(256), 0, s, a.w_rec, a.adj_pos,
+                         a.adj_pair, a.nnz_rec);
+    else if (e == hipSuccess && a.nnz_rec)
+      e = hipMemcpyAsync(a.w_rec_c, a.w_rec, (size_t)a.nnz_rec * 4, hipMemcpyDeviceToDevice, s);
+  }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_lam_u, dim3(a.O), dim3(64), 0, s, a, g_loss);
   return hipGetLastError();
@@ -1544,6 +1689,14 @@ hipError_t bptt_backward_prologue(const BpttArgs &a, const float *g_loss, hipStr
 
 // g: the plan's arguments with w_out = w_out_c and w_rec = w_rec_c
 hipError_t bptt_backward_body(const BpttArgs &g, hipStream_t s) {
+  if (g.seq_threads) {  // two kernels, launched without a graph
+    hipLaunchKernelGGL(k_readout_adjoint_slice, dim3(blocks_for(g.H, kAdjointRows), g.T), dim3(256), 0, s, g, g.lamv);
+    const dim3 grid(g.S == 8 ? 64u : g.B), block(g.seq_threads);
+    if (g.seq_max <= 2) hipLaunchKernelGGL(k_adjoint_seq<8>, grid, block, 0, s, g);
+    else if (g.seq_max <= 6) hipLaunchKernelGGL(k_adjoint_seq<24>, grid, block, 0, s, g);
+    else hipLaunchKernelGGL(k_adjoint_seq<kSeqRegs>, grid, block, (size_t)g.seq_more_all * kWave * kSeqGroupBytes, s, g);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_fill, dim3(blocks_for((uint64_t)g.H * 64, 256)), dim3(256), 0, s, g.lam_carry,
                      (uint64_t)g.H * 64, 0.0f);
   // batch masks of the hidden trajectory for the sparse-weight gradients: in spiking
@@ -1607,6 +1760,8 @@ hipError_t bptt_prepare(const BpttArgs &a) {
   if (a.S) e = allow(reinterpret_cast<const void *>(&k_adjoint_slice), kSliceMaxNeurons * 32u);
   if (e == hipSuccess && a.events) {
     e = allow(reinterpret_cast<const void *>(&k_hidden_seq<4>), kEventMaxNeurons * kSeqChunk * sizeof(float));
+    if (e == hipSuccess)
+      e = allow(reinterpret_cast<const void *>(&k_adjoint_seq<kSeqRegs>), kSeqMaxMore * kWave * kSeqGroupBytes);
   }
   return e;
 }

@@ -1738,6 +1738,88 @@ T *upload(snn_network *pool, const std::vector<T> &v) {
   return d;
 }
 
+// Deals the rows of W_rec to the lanes of the one-workgroup membrane adjoint and orders every
+// lane's synapses (snn_internal.h, seq_*).  Leaves seq_threads 0 where the form does not fit.
+//  * `p` neighbouring lanes share a row, the largest power of two (<= 16) with p H <= 1,024;
+//    rows go to lanes by descending length, so that a wavefront's rows are about equally long.
+//  * A row's synapses are dealt place by place: at each place, every lane takes, among the next
+//    few it has left, the one whose LDS bank is least used by the 32 lanes read together.
+void build_seq(snn_bptt *pl, const uint64_t *rec_ptr, const int32_t *rec_col) {
+  snn::BpttArgs &a = pl->args;
+  if (!a.events || !a.S || a.H > snn::kSeqMaxNeurons) return;
+  uint32_t p = 1;
+  while (p < 16 && 2 * p * a.H <= 1024) p *= 2;
+  const uint32_t rows_per_wave = 64 / p, n_waves = (a.H + rows_per_wave - 1) / rows_per_wave, n_thr = n_waves * 64;
+  std::vector<uint32_t> order(a.H);
+  std::iota(order.begin(), order.end(), 0u);
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) {
+    return rec_ptr[x + 1] - rec_ptr[x] > rec_ptr[y + 1] - rec_ptr[y];
+  });
+  // a wavefront's places: its longest row over p lanes, in groups of four
+  std::vector<uint32_t> groups(16, 0u), more(16, 0u), row(n_thr, 0xFFFFFFFFu);
+  uint32_t g_max = 0, more_all = 0;
+  for (uint32_t w = 0; w < n_waves; ++w) {
+    const uint32_t r0 = order[w * rows_per_wave];
+    const uint64_t len = (rec_ptr[r0 + 1] - rec_ptr[r0] + p - 1) / p;
+    if (len > snn::kSeqRegs + 4 * snn::kSeqMaxMore) return;
+    groups[w] = (uint32_t)((len + 3) / 4);
+    g_max = std::max(g_max, groups[w]);
+    more[w] = more_all;
+    if (groups[w] > snn::kSeqRegs / 4) more_all += groups[w] - snn::kSeqRegs / 4;
+  }
+  if (more_all > snn::kSeqMaxMore) return;
+  g_max = std::max(1u, g_max);
+  const size_t places = (size_t)g_max * n_thr * 4;
+  std::vector<uint16_t> col(places, (uint16_t)(snn::kSeqMaxNeurons * 4));  // the zero behind the neurons
+  std::vector<uint32_t> pos(rec_ptr[a.H]);
+  constexpr uint32_t kLook = 16;
+  std::vector<std::vector<uint32_t>> left(64);  // of each lane: edges not yet placed
+  for (uint32_t w = 0; w < n_waves; ++w) {
+    for (uint32_t l = 0; l < 64; ++l) {
+      left[l].clear();
+      const uint32_t k = w * rows_per_wave + l / p;
+      if (k >= a.H) continue;
+      row[w * 64 + l] = order[k];
+      for (uint64_t e = rec_ptr[order[k]] + l % p; e < rec_ptr[order[k] + 1]; e += p) left[l].push_back((uint32_t)e);
+    }
+    for (uint32_t s = 0; s < groups[w] * 4; ++s)
+      for (uint32_t half = 0; half < 2; ++half) {
+        uint32_t used[64] = {};
+        for (uint32_t x = 0; x < 32; ++x) {
+          const uint32_t l = half * 32 + (x + s) % 32;  // no lane always chooses last
+          if (left[l].empty()) continue;
+          const uint32_t n = (uint32_t)left[l].size(), look = std::min(n, kLook);
+          uint32_t best = n - 1;
+          for (uint32_t q = 0; q < look; ++q) {
+            const uint32_t at = n - 1 - q;
+            if (used[rec_col[left[l][at]] & 63] < used[rec_col[left[l][best]] & 63]) best = at;
+            if (used[rec_col[left[l][best]] & 63] == 0) break;
+          }
+          const uint32_t e = left[l][best];
+          left[l][best] = left[l].back();
+          left[l].pop_back();
+          ++used[rec_col[e] & 63];
+          const size_t at = ((size_t)(s / 4) * n_thr + w * 64 + l) * 4 + s % 4;
+          col[at] = (uint16_t)(rec_col[e] * 4);
+          pos[e] = (uint32_t)at;
+        }
+      }
+  }
+  snn_network *pool = &pl->pool;
+  a.seq_p = p;
+  a.seq_max = g_max;
+  a.seq_row = upload(pool, row);
+  a.seq_groups = upload(pool, groups);
+  a.seq_more = upload(pool, more);
+  a.seq_more_all = more_all;
+  a.seq_col = upload(pool, col);
+  a.seq_pos = upload(pool, pos);
+  a.seq_w = dev_array<float>(pool, places);
+  check(hipMemsetAsync(a.seq_w, 0, places * 4, pool->stream), "clear weights");
+  check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
+  a.seq_threads = n_thr;
+}
+
 void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, const uint64_t *rec_ptr,
                 const int32_t *rec_col) {
   const snn_bptt_desc &d = p->desc;
@@ -1863,6 +1945,7 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     a.adj_len = upload(pool, len);
     check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
   }
+  build_seq(p, rec_ptr, rec_col);
   check(snn::bptt_prepare(a), "bptt prepare");
   a.flags = dev_array<uint32_t>(pool, 2);
   a.w_in_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_in));
@@ -2430,6 +2513,11 @@ snn_status snn_bptt_backward(snn_bptt *p, const float *w_in, const float *w_rec,
     a.g_w_out = g_w_out;
     hipStream_t s = stream ? (hipStream_t)stream : p->pool.stream;
     check(snn::bptt_backward_prologue(a, g_loss, s), "bptt backward");
+    if (a.seq_threads) {  // a few kernels, on the caller's weights
+      check(snn::bptt_backward_body(a, s), "bptt backward");
+      check(snn::bptt_backward_epilogue(a, s), "bptt backward");
+      return;
+    }
     snn::BpttArgs g = p->args;
     g.w_out = g.w_out_c;
     g.w_rec = g.w_rec_c;
@@ -2449,6 +2537,7 @@ snn_status snn_bptt_get_trace(snn_bptt *p, float *spikes, float *v_checkpoints, 
     if (a.events) {
       if (v_checkpoints) check(snn::bptt_trace_v(a, s), "trace");
       if (spikes) {
+        check(snn::bptt_spike_masks(a, s), "trace");
         masks.resize((size_t)a.H * a.T);
         check(hipMemcpyAsync(masks.data(), a.sbits, masks.size() * 8, hipMemcpyDeviceToHost, s), "copy");
       }

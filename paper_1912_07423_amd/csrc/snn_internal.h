@@ -221,6 +221,13 @@ constexpr uint32_t kSliceMaxNeurons = 4096;
 // input weights.
 constexpr uint32_t kEventMaxNeurons = 2048;
 constexpr uint64_t kEventMaxInput = 1ull << 24;
+// The membrane adjoint of one batch element in one workgroup: at most kSeqMaxNeurons neurons;
+// kSeqRegs synapses of a lane in registers, the others in LDS, in groups of four (24 bytes)
+// per lane, at most kSeqMaxMore groups per wavefront in all (150 KB).
+constexpr uint32_t kSeqMaxNeurons = 1024;
+constexpr int kSeqRegs = 48;
+constexpr uint32_t kSeqGroupBytes = 24;
+constexpr uint32_t kSeqMaxMore = 98;
 constexpr uint64_t kSliceMaxPairs = 1ull << 26;
 struct BpttArgs {
   uint32_t B, T, C, H, O, K;
@@ -235,6 +242,15 @@ struct BpttArgs {
   uint16_t *lists;             // event lists of every source and chunk of steps
   uint32_t *list_len;          // their lengths
   uint64_t *spk;               // [B][T][nw] spikes of every step
+  uint32_t seq_threads;        // lanes of a one-workgroup membrane adjoint (0: steps launched)
+  uint32_t seq_p, seq_max;     // lanes per neuron, groups of four synapses of the longest wavefront
+  const uint32_t *seq_row;     // [seq_threads] neuron of each lane (0xFFFFFFFF: none)
+  const uint32_t *seq_groups;  // [16] groups of four synapses of each wavefront's lanes
+  const uint32_t *seq_more;    // [16] first LDS group of each wavefront
+  uint32_t seq_more_all;       // LDS groups of all wavefronts
+  const uint16_t *seq_col;     // [seq_max][seq_threads][4] LDS offsets of the targets
+  float *seq_w;                // [seq_max][seq_threads][4] weights
+  const uint32_t *seq_pos;     // [nnz_rec] place of each CSR edge in seq_w
   uint32_t S;                  // slices of 8 batch elements of the membrane adjoint (0: not sliced)
   uint32_t adj_w;              // width of its padded rows of W_rec, a multiple of 16
   uint2 *adj_pair;             // [H][adj_w] (target, weight); padding (0, 0)
@@ -272,6 +288,7 @@ struct BpttArgs {
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
 hipError_t bptt_prepare(const BpttArgs &a);
+hipError_t bptt_spike_masks(const BpttArgs &a, hipStream_t s);
 uint64_t bptt_lists(const BpttArgs &a);  // number of event lists, entries held for each
 uint32_t bptt_list_stride();
 hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s);  // fills vck (event-driven plans)

@@ -34,7 +34,14 @@ def test_words_per_wavefront(H):
     _compare(_inputs(5, 18, 12, H, 3, p_rec=0.05), 5)
 
 
-@pytest.mark.parametrize("T", [1, 2, 15, 16, 17, 33])
+@pytest.mark.parametrize("H,p_rec", [(16, 0.9), (60, 0.5), (130, 0.6), (256, 0.3), (513, 0.12), (640, 0.12), (1024, 0.02)])
+def test_synapses_per_lane_of_the_one_workgroup_adjoint(H, p_rec):
+    """From one group of synapses per lane to more than the registers hold, with every number
+    of lanes per neuron; an idle lane pair at 16 x 60."""
+    _compare(_inputs(9, 11, 12, H, 3, p_rec=p_rec), 4)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 15, 16, 17, 33])
 def test_chunks_of_steps(T):
     _compare(_inputs(7, T, 25, 70, 3), 4)
 

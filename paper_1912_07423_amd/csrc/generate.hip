@@ -534,7 +534,8 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t t, uint32_t tile_size, doub
 
 // One wave per (sorted) row, streaming the row's targets once:
 //  * col16[e] = col[e] mod 2^16, the tiled delivery's 2-byte target stream (a range spans
-//    fewer than 65,536 targets, so the low 16 bits identify a target inside it);
+//    fewer than 65,536 targets, so the low 16 bits identify a target inside it), unless
+//    col16 is null;
 //  * entry p of the row's tile boundaries is the offset, from the row's start, of the
 //    first target >= p * tile_size (entry `tiles` is the row length).  Targets are
 //    sorted, so element e is that boundary for every p in (tile(e - 1), tile(e)]; the
@@ -551,7 +552,7 @@ __global__ __launch_bounds__(kGenBlock) void k_tile_index(const uint64_t *row_pt
   const uint32_t lane = lane_id();
   const uint32_t wave = blockIdx.x * kGenWavesPerBlock + threadIdx.x / kWave;
   const uint32_t n_waves = gridDim.x * kGenWavesPerBlock;
-  if (blockIdx.x == 0 && threadIdx.x == 0)
+  if (col16 && blockIdx.x == 0 && threadIdx.x == 0)
     for (uint64_t e = nnz; e < count; ++e) col16[e] = 0;
   auto put = [&](uint64_t at, uint32_t rel) {
     if (off16) static_cast<uint16_t *>(tile_off)[at] = (uint16_t)rel;
@@ -587,7 +588,8 @@ __global__ __launch_bounds__(kGenBlock) void k_tile_index(const uint64_t *row_pt
           tl[j] = e0 + j < hi ? (int32_t)tile_of((uint32_t)t[gi][j], tile_size, inv) : (int32_t)tiles;
         const int32_t up = __shfl_up(tl[3], 1, kWave);
         int32_t prev = lane == 0 ? carry : up;
-        if (aligned && e0 + 4u <= hi) {
+        if (!col16) {
+        } else if (aligned && e0 + 4u <= hi) {
           *reinterpret_cast<uint2 *>(col16 + e0) =
               make_uint2(((uint32_t)t[gi][0] & 0xFFFFu) | ((uint32_t)t[gi][1] << 16),
                          ((uint32_t)t[gi][2] & 0xFFFFu) | ((uint32_t)t[gi][3] << 16));

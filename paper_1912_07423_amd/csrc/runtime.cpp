@@ -465,6 +465,7 @@ void alloc_tile_offsets(snn_network *net) {
 }
 
 bool choose_solo(const snn_network *net);
+bool choose_windows(snn_network *net);
 
 void build(snn_network *net) {
   validate_and_derive(net);
@@ -606,6 +607,7 @@ void build(snn_network *net) {
   choose_delivery(net);
   net->solo = choose_solo(net);
   if (net->delivery == SNN_DELIVERY_TILED) alloc_tile_offsets(net);
+  net->windows = choose_windows(net);
   check(hipEventRecord(ev[5], s), "hipEventRecord");
 
   // neuron state, FIFO, raster, control block
@@ -1001,6 +1003,153 @@ void run_solo(snn_network *net, uint64_t n_steps) {
   }
 }
 
+void dev_free(snn_network *net, void *p);
+
+// ---- windows of an eagerly plastic network -------------------------------------------
+// Device memory for the arriving rows of a window as the ranges read them (rows past it are
+// read where they are).
+constexpr size_t kWindowRowBytes = (size_t)256 << 20;
+
+// Targets of a workgroup: one range per CU while that leaves a wavefront of targets each.
+uint32_t window_range(const snn_network *net) {
+  const uint32_t share = (net->n + net->cu_count - 1) / net->cu_count;
+  return std::min((share + 63) / 64 * 64, snn::kPlasticBlock);
+}
+
+// Whether snn_run steps the network in windows (plastic.hip), with the buffers they need: an
+// eagerly plastic network with nothing about its delivery chosen by the caller and a delay of
+// at least two steps (a window is at most delay - 1 steps).  Two launches per window against
+// three per step, in us per step: delay 2 (one-step windows) 11.0 against 12.6 with 500
+// neurons, 13.7 against 19.3 with 20,000, 21.2 against 24.1 with 60,000; delay 10, 3.9 against
+// 19.3 with 20,000; delay 15, 2.6 against 14.0 with 4,000 and 9.6 against 24.1 with 60,000.
+// Every range looks at every arriving spike, so rows of fewer synapses than half the ranges
+// stay with the launches (200,000 neurons with 500 synapses each, 1.3 per range: 30.8 against
+// 43.5), and so does a network whose memory has no room for the windows' index.
+bool choose_windows(snn_network *net) {
+  if (!net->plastic || net->lazy || net->owner || net->delay < 2 || net->n == 0 ||
+      net->prm.delivery != SNN_DELIVERY_AUTO || net->prm.window || net->prm.tiles || net->prm.block || net->prm.grid)
+    return false;
+  const uint32_t range = window_range(net), ranges = (net->n + range - 1) / range;
+  if ((double)net->nnz < 0.5 * (double)ranges * net->n) return false;
+  if (net->range_off) return true;
+  const bool off16 = net->row_len_bound < 65536;
+  const size_t entries = (size_t)net->n * (ranges + 1);
+  // a slot holds nearly every sub-row (their lengths are about Poisson)
+  const double mean = (double)net->nnz / ((double)net->n * ranges);
+  const uint32_t shift = lanes_shift_for(mean + 2.5 * std::sqrt(mean) + 0.5, 1);
+  const size_t row_bytes = (size_t)ranges * (sizeof(snn::SubRow) + (sizeof(uint16_t) << shift));
+  const uint32_t cap = (uint32_t)std::min<size_t>(snn::kPlasticRows, kWindowRowBytes / row_bytes);
+  const uint32_t slots = net->delay + std::min(net->delay - 1, snn::kPlasticSteps) + 1;
+  void *held[7] = {};
+  try {
+    held[0] = off16 ? (void *)dev_array<uint16_t>(net, entries) : (void *)dev_array<uint32_t>(net, entries);
+    held[1] = dev_array<uint2>(net, 2 * (size_t)net->n);
+    held[2] = dev_array<uint4>(net, 2 * (size_t)net->n);
+    held[3] = dev_array<int32_t>(net, (size_t)slots * net->n);
+    held[4] = dev_array<uint32_t>(net, (size_t)(slots + 3) * snn::kQlenStride);
+    held[5] = dev_array<snn::SubRow>(net, (size_t)std::max(cap, 1u) * ranges);
+    held[6] = dev_array<uint16_t>(net, ((size_t)std::max(cap, 1u) * ranges) << shift);
+  } catch (...) {
+    for (void *p : held)
+      if (p) dev_free(net, p);
+    return false;
+  }
+  check(snn::launch_tile_index(net->row_ptr, net->col, net->n, net->nnz, net->nnz, ranges, range, nullptr, held[0],
+                               off16, net->stream),
+        "range index");
+  net->range_off = held[0];
+  net->trace = static_cast<uint2 *>(held[1]);
+  net->ltp = static_cast<uint4 *>(held[2]);
+  net->spike_list = static_cast<int32_t *>(held[3]);
+  net->spike_list_len = static_cast<uint32_t *>(held[4]);
+  net->row_head = static_cast<snn::SubRow *>(held[5]);
+  net->row_tgt = static_cast<uint16_t *>(held[6]);
+  net->list_slots = slots;
+  net->row_cap = cap;
+  net->row_shift = shift;
+  net->range = range;
+  net->ranges = ranges;
+  return true;
+}
+
+snn::PlasticArgs plastic_args(snn_network *net) {
+  snn::PlasticArgs a{};
+  a.row_ptr = net->row_ptr;
+  a.col = net->col;
+  a.w_f32 = net->w_f32;
+  a.plast_rel = net->plast_rel;
+  a.plast_len = net->plast_len;
+  a.in_ptr = net->in_ptr;
+  a.in_src = net->in_src;
+  a.in_edge = net->in_edge;
+  a.off = net->range_off;
+  for (uint32_t k = 0; k < 2; ++k) {
+    a.trace[k] = net->trace + (size_t)k * net->n;
+    a.ltp[k] = net->ltp + (size_t)k * net->n;
+    a.ltp_len[k] = net->spike_list_len + (size_t)(net->list_slots + k) * snn::kQlenStride;
+  }
+  a.list = net->spike_list;
+  a.list_len = net->spike_list_len;
+  a.list_slots = net->list_slots;
+  a.arriving = net->spike_list_len + (size_t)(net->list_slots + 2) * snn::kQlenStride;
+  a.row_head = net->row_head;
+  a.row_tgt = net->row_tgt;
+  a.row_cap = net->row_cap;
+  a.row_blocks = std::min(net->cu_count * 4, std::max(64u, net->n / 64));
+  a.v = net->v;
+  a.ref = net->ref;
+  a.input = net->input;
+  a.x_pre = net->x_pre;
+  a.x_post = net->x_post;
+  a.q = queue_ref(net);
+  a.raster = net->raster;
+  a.table32 = net->d_table32;
+  a.guide = net->d_guide;
+  a.ctl = net->ctl;
+  a.n = net->n;
+  a.slots = net->slots;
+  a.raster_cap = net->raster_cap;
+  a.words = net->words;
+  a.table_len = net->table_len;
+  a.delay = net->delay;
+  a.range = net->range;
+  a.ranges = net->ranges;
+  a.off16 = net->row_len_bound < 65536 ? 1u : 0u;
+  a.lanes_shift = net->row_shift;
+  a.key0 = net->key0;
+  a.key1 = net->key1;
+  a.alpha = net->alpha;
+  a.v_inf = net->v_inf;
+  a.v_th = net->v_th;
+  a.v_reset = net->v_reset;
+  a.beta_plus = net->beta_plus;
+  a.beta_minus = net->beta_minus;
+  a.ref_steps = net->ref_steps;
+  a.w_ext_q16 = net->w_ext_q16;
+  a.a_plus = net->a_plus;
+  a.a_minus = net->a_minus;
+  a.w_max = net->w_max;
+  return a;
+}
+
+void run_windows(snn_network *net, uint64_t n_steps) {
+  snn::PlasticArgs a = plastic_args(net);
+  check(snn::launch_plastic_import(a, net->stream), "spike lists");
+  const uint32_t most = std::min(net->delay - 1, snn::kPlasticSteps);
+  for (bool first = true; n_steps > 0; first = false) {
+    const uint32_t steps = (uint32_t)std::min<uint64_t>(n_steps, most);
+    a.first = first;
+    a.last = steps == n_steps;
+    a.ltp_blocks = first ? 0u : std::min(net->cu_count * 8, std::max(64u, net->n / 32));
+    check(snn::launch_plastic_window(a, steps, net->stream), "plastic window");
+    a.parity ^= 1u;
+    net->t_host += steps;
+    n_steps -= steps;
+  }
+  a.ltp_blocks = std::min(net->cu_count * 8, std::max(64u, net->n / 32));
+  check(snn::launch_plastic_export(a, net->stream), "potentiation and spike queues");
+}
+
 void ensure_graph(snn_network *net) {
   if (net->graph) return;
   const uint32_t windows = std::max(1u, (64u + net->window - 1) / net->window);
@@ -1026,6 +1175,11 @@ void ensure_graph(snn_network *net) {
 
 void run(snn_network *net, uint64_t n_steps) {
   if (net->solo && !net->profiling && n_steps > 1) return run_solo(net, n_steps);
+  if (net->windows && !net->profiling && n_steps > 1) {
+    for (; n_steps > 0 && net->t_host < net->windows_from; --n_steps) issue_window(net, 1);
+    if (n_steps > 0) run_windows(net, n_steps);
+    return;
+  }
   while (n_steps > 0) {
     if (!net->profiling && n_steps >= 64 && net->stream) {
       ensure_graph(net);
@@ -1159,11 +1313,11 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     uint32_t p_delivery, p_tiles, p_block, p_grid, delivery, block, tiles, tile_size, grid;
     void *tile_off;
     uint16_t *col16;
-    bool tile_off16, solo;
+    bool tile_off16, solo, windows;
   };
   const Saved old{net->prm.delivery, net->prm.tiles, net->prm.block, net->prm.grid, net->delivery,
                   net->block,        net->tiles,     net->tile_size, net->grid,     net->tile_off,
-                  net->col16,        net->tile_off16, net->solo};
+                  net->col16,        net->tile_off16, net->solo,     net->windows};
   try {
     net->prm.delivery = delivery;
     net->prm.tiles = tiles;
@@ -1179,6 +1333,8 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     } else {
       net->tile_off = nullptr;
     }
+    net->windows = choose_windows(net);
+    check(hipStreamSynchronize(net->stream), "sync after the new configuration");
   } catch (...) {
     (void)hipStreamSynchronize(net->stream);  // no index launch may still write a block freed here
     if (net->tile_off && net->tile_off != old.tile_off) dev_free(net, net->tile_off);
@@ -1193,6 +1349,7 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->tile_size = old.tile_size;
     net->grid = old.grid;
     net->solo = old.solo;
+    net->windows = old.windows;
     net->tile_off = old.tile_off;
     net->col16 = old.col16;
     net->tile_off16 = old.tile_off16;
@@ -2200,6 +2357,8 @@ snn_status snn_set_state(snn_network *net, const snn_state *st) {
     h2d(net->x_pre, st->x_pre, n * 4);
     h2d(net->x_post, st->x_post, n * 4);
     h2d(net->queue, st->queue, (size_t)net->slots * net->queue_stride * 4);
+    // the caller's queues need not be the raster's: launches until they have arrived
+    if (st->queue || st->queue_len) net->windows_from = net->t_host + net->delay + 1;
     if (st->queue_len)
       check(hipMemcpy2DAsync(net->qlen, snn::kQlenStride * 4, st->queue_len, 4, 4,
                              (size_t)net->slots * snn::kQueueGroups, hipMemcpyHostToDevice, s),

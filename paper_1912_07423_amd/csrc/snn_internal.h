@@ -163,6 +163,76 @@ struct StdpArgs {
   float a_plus, a_minus, w_max;
 };
 
+// Windows of an eagerly plastic network (plastic.hip): a workgroup per range of targets.
+constexpr uint32_t kPlasticBlock = 512;  // its lanes, and the most targets of a range
+constexpr uint32_t kPlasticRows = 2048;  // most arriving rows of a window that are laid out
+constexpr uint32_t kPlasticSteps = 16;   // most steps of a window (its arrivals are one 32-bit mask)
+// One arriving neuron's synapses on the range: [lo, lo + len), those from p0 to p1 (offsets
+// from lo) plastic, and its presynaptic trace (the value at the window's start, and bit m: it
+// arrives at step m of the window).  A row has at most one synapse per target (projections do
+// not overlap), so len <= kPlasticBlock.
+struct SubRow {
+  uint32_t lo, dims;
+  uint2 trace;
+  __host__ __device__ uint32_t len() const { return dims & 1023u; }
+  __host__ __device__ uint32_t p0() const { return (dims >> 10) & 1023u; }
+  __host__ __device__ uint32_t p1() const { return dims >> 20; }
+  // the latest arrival before step m (0: none), and whether there are several
+  __host__ __device__ uint32_t from(uint32_t m) const {
+    const uint32_t before = trace.y & ((1u << m) - 1u);
+    return before ? 31u - (uint32_t)__builtin_clz(before) : 0u;
+  }
+  __host__ __device__ bool again() const { return (trace.y & (trace.y - 1u)) != 0; }
+};
+static_assert(kPlasticBlock < 1024 && kPlasticSteps < 32, "fields of SubRow");
+struct PlasticArgs {
+  const uint64_t *row_ptr;
+  const int32_t *col;
+  float *w_f32;
+  const uint32_t *plast_rel, *plast_len;
+  const uint64_t *in_ptr;
+  const int32_t *in_src;
+  const uint32_t *in_edge;
+  const void *off;        // [n][ranges + 1] range boundaries of each row: uint16 when off16
+  // of this window at [parity], of the window before at [parity ^ 1]:
+  uint2 *trace[2];        // [n] presynaptic trace at the window's start, arrivals in its steps
+  uint4 *ltp[2];          // [n] its spiking neurons: first in-edge, in-edges, spikes
+  uint32_t *ltp_len[2];
+  uint32_t parity;
+  uint32_t first, last;   // window of the run
+  int32_t *list;          // [list_slots][n] spikes of the latest steps
+  uint32_t *list_len;     // [list_slots] on lines of their own
+  uint32_t list_slots;
+  uint32_t *arriving;     // [kPlasticSteps + 1] rows of the window's lists
+  SubRow *row_head;       // [ranges][row_cap] arriving sub-rows,
+  uint16_t *row_tgt;      // [ranges][row_cap][2^lanes_shift] their targets in the range
+  uint32_t row_cap;
+  uint32_t ltp_blocks, row_blocks;  // workgroups of the prepare launch
+  float *v;
+  int32_t *ref;
+  int32_t *input;         // [n]
+  float *x_pre, *x_post;
+  QueueRef q;
+  uint64_t *raster;
+  const uint32_t *table32;
+  const uint16_t *guide;
+  Ctl *ctl;
+  uint32_t n, slots, raster_cap, words, table_len, delay;
+  uint32_t range, ranges, off16;
+  uint32_t lanes_shift;   // log2 of the lanes that share one sub-row
+  uint32_t key0, key1;
+  float alpha, v_inf, v_th, v_reset, beta_plus, beta_minus;
+  int32_t ref_steps, w_ext_q16;
+  float a_plus, a_minus, w_max;
+};
+// The lists of the last `delay` steps, from the raster.
+hipError_t launch_plastic_import(const PlasticArgs &a, hipStream_t s);
+// steps <= min(delay - 1, kPlasticSteps) steps from ctl->t on.
+hipError_t launch_plastic_window(const PlasticArgs &a, uint32_t steps, hipStream_t s);
+// After the last window of a run (a as for a window that followed): the potentiation it
+// left, and the FIFO ring.
+hipError_t launch_plastic_export(const PlasticArgs &a, hipStream_t s);
+
 // One network of a batch as the persistent batch kernel sees it: pointers into the
 // network's own buffers (state layout identical to the single-network pipeline) and
 // its derived constants.
@@ -430,6 +500,18 @@ struct snn_network {
   uint32_t *d_table32 = nullptr;
   uint16_t *d_guide = nullptr;
   snn::Ctl *ctl = nullptr;
+  // eager plasticity: windows of steps in one launch (plastic.hip)
+  bool windows = false;       // snn_run takes them
+  uint64_t windows_from = 0;  // from this step on (the raster then holds every pending queue)
+  void *range_off = nullptr;  // range boundaries of every row
+  uint2 *trace = nullptr;     // [2][n]
+  uint4 *ltp = nullptr;       // [2][n]
+  int32_t *spike_list = nullptr;
+  uint32_t *spike_list_len = nullptr;  // [list_slots + 3], the last three for ltp and arriving
+  snn::SubRow *row_head = nullptr;
+  uint16_t *row_tgt = nullptr;
+  uint32_t list_slots = 0, row_cap = 0, row_shift = 0;
+  uint32_t range = 0, ranges = 0;
   // lazy plasticity: per-neuron spike history, row ages and traces at age, expiring rows
   uint64_t *hist = nullptr;
   uint32_t *age = nullptr;

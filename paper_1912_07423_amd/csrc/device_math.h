@@ -126,11 +126,12 @@ struct LifConst {
 // V >= V_th emits a spike, resets V and starts the refractory count.  Returns the spike.
 // Written without branches: the candidate V is computed for every lane and a
 // refractory lane keeps its old V (the same values as skipping the computation).
-__device__ __forceinline__ bool lif_advance(float &v, int32_t &ref, int32_t input, int32_t k,
-                                            const LifConst &c) {
-  const bool refractory = ref > 0;
+__device__ __forceinline__ float lif_input(int32_t input, int32_t k, const LifConst &c) {
   const uint32_t sum = (uint32_t)input + (uint32_t)k * (uint32_t)c.w_ext_q16;
-  const float dv = (float)(int32_t)sum * 0x1p-16f;
+  return (float)(int32_t)sum * 0x1p-16f;
+}
+__device__ __forceinline__ bool lif_apply(float &v, int32_t &ref, float dv, const LifConst &c) {
+  const bool refractory = ref > 0;
   float vv = v + dv;
   const float diff = vv - c.v_inf;
   const float leak = diff * c.alpha;
@@ -139,6 +140,10 @@ __device__ __forceinline__ bool lif_advance(float &v, int32_t &ref, int32_t inpu
   v = refractory ? v : (spike ? c.v_reset : vv);
   ref = refractory ? ref - 1 : (spike ? c.ref_steps : ref);
   return spike;
+}
+__device__ __forceinline__ bool lif_advance(float &v, int32_t &ref, int32_t input, int32_t k,
+                                            const LifConst &c) {
+  return lif_apply(v, ref, lif_input(input, k, c), c);
 }
 
 // Word u (0..3) of a Philox block by selects, never by a dynamic register index.

@@ -5,6 +5,8 @@
 //                    the ballot of each step is both the step's raster word and the
 //                    compaction mask of the spike queue (one queue reservation per
 //                    workgroup and step).
+//  k_update_window   the same for windows of five and more steps of a static network of up to
+//                    81,920 neurons: the steps' inputs are prepared by several wavefronts.
 //  k_deliver_atomic  Receive Spikes, one or more wavefronts per dequeued spike,
 //                    aligned 16-byte loads of targets/weights, no-return int32 atomics
 //                    into the Q16 input accumulators in global memory.
@@ -307,6 +309,110 @@ __global__ __launch_bounds__(kUpdateBlock) void k_update(UpdateArgs a, uint32_t 
     const uint32_t pos = s_exp[wave] + lanes_below(emask);
     if (pos < a.lazy.exq.group_cap)
       a.lazy.exq.ids[(size_t)(t0 & 1u) * a.lazy.exq.stride + group * a.lazy.exq.group_cap + pos] = (int32_t)i;
+  }
+}
+
+// Update Neurons of a static network, a window of several steps.  The membrane is a serial
+// chain, but its inputs are not: five wavefronts of a workgroup each take one quad of steps of
+// the same 64 neurons (a Philox block, four drive lookups, four loads of the accumulators) and
+// leave the membrane's input of every step in LDS, while a sixth walks the 64 membranes through
+// the steps behind them and files the spikes.  One LDS buffer is filled while the other is read.
+// Bound: the chain step, inputs, Philox block, lookups, membranes, queue reservation.  With one
+// wavefront doing all of it for its neurons (k_update), 20,000 neurons took 10.1 us for 15 steps
+// and 24.6 for 40; here 7.4 and 11.8 (73,000 neurons: 10.8 -> 8.9, 27.1 -> 16.5).
+constexpr int kQuadWaves = 5;
+constexpr int kWindowBlock = (kQuadWaves + 1) * kWave;
+constexpr int kWindowChunk = 4 * kQuadWaves;  // steps of a buffer
+template <bool kDrive>
+__global__ __launch_bounds__(kWindowBlock) void k_update_window(UpdateArgs a, uint32_t steps) {
+  __shared__ __align__(16) uint32_t tbl[kDrive ? kTableCap : 4];
+  __shared__ __align__(16) uint16_t guide[kDrive ? kGuideBuckets : 8];
+  __shared__ float s_in[2][kWindowChunk][kWave];
+  const uint64_t t0 = a.ctl->t;
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->t_deliver = t0;
+  if (kDrive) {
+    for (uint32_t x = threadIdx.x; x < kTableCap / 4; x += kWindowBlock)
+      reinterpret_cast<int4 *>(tbl)[x] = reinterpret_cast<const int4 *>(a.table32)[x];
+    for (uint32_t x = threadIdx.x; x < kGuideBuckets / 8; x += kWindowBlock)
+      reinterpret_cast<int4 *>(guide)[x] = reinterpret_cast<const int4 *>(a.guide)[x];
+  }
+  const uint32_t off = (uint32_t)(t0 & 3u);  // position of t0 in its quad
+  const uint32_t chunks = (off + steps + kWindowChunk - 1) / kWindowChunk;
+  const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+  const uint32_t i = blockIdx.x * kWave + lane;
+  const bool active = i < a.n;
+  const LifConst lif{a.alpha, a.v_inf, a.v_th, a.v_reset, a.ref_steps, a.w_ext_q16};
+  if (wave < kQuadWaves) {
+    const uint32_t in0 = (uint32_t)(t0 % a.n_inbuf);
+    for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+      const uint32_t p0 = chunk * kWindowChunk + 4 * wave;  // positions p: step t0 + p - off
+      int32_t x[4], k[4] = {};
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u) {
+        x[u] = 0;
+        const uint32_t w = p0 + u - off;
+        if (w < steps && active) {  // (a position before t0 wraps)
+          int32_t *in = a.input + (size_t)ring_add(in0, w, a.n_inbuf) * a.n + i;
+          x[u] = *in;
+          if (a.zero_input) *in = 0;
+        }
+      }
+      if (kDrive && p0 < off + steps) {
+        const uint64_t quad = (t0 >> 2) + p0 / 4;
+        const Words4 rnd = philox(i, (uint32_t)quad, (uint32_t)(quad >> 32), kStreamPoisson, a.key0, a.key1);
+        if (chunk == 0) __syncthreads();  // the tables
+        uint32_t gk[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) gk[u] = guide[rnd.w[u] >> (32 - kGuideBits)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          k[u] = (int32_t)(gk[u] & 0xFFu);
+          const int32_t k_hi = (int32_t)(gk[u] >> 8);
+          while (k[u] < k_hi && tbl[k[u]] <= rnd.w[u]) ++k[u];
+        }
+      } else if (kDrive && chunk == 0) {
+        __syncthreads();
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) s_in[chunk & 1u][4 * wave + u][lane] = lif_input(x[u], k[u], lif);
+      __syncthreads();
+    }
+    return;
+  }
+  float v = active ? a.v[i] : 0.f;
+  int32_t ref = active ? a.ref[i] : 0;
+  uint64_t my_mask = 0;    // lane w: ballot of step w
+  uint64_t my_spikes = 0;  // bit w: this neuron spiked at step w
+  if (kDrive) __syncthreads();
+  for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+    __syncthreads();  // the buffer is filled (and this wavefront has left the other one)
+    const uint32_t p_hi = min((chunk + 1) * kWindowChunk, off + steps);
+#pragma unroll 5
+    for (uint32_t p = chunk == 0 ? off : chunk * kWindowChunk; p < p_hi; ++p) {
+      const uint32_t w = p - off;
+      const bool spike = lif_apply(v, ref, s_in[chunk & 1u][p - chunk * kWindowChunk][lane], lif) && active;
+      const uint64_t mask = __ballot(spike);
+      if (lane == w) my_mask = mask;
+      if (spike) my_spikes |= 1ull << w;
+    }
+  }
+  if (active) {
+    a.v[i] = v;
+    a.ref[i] = ref;
+  }
+  const uint32_t slot0 = (uint32_t)(t0 % a.slots), group = i / kUpdateBlock % kQueueGroups;
+  uint32_t base = 0;
+  if (lane < steps) {
+    if (my_mask) base = atomicAdd(qcount(a.q, ring_add(slot0, lane, a.slots), group), (uint32_t)__popcll(my_mask));
+    a.raster[(size_t)ring_add((uint32_t)(t0 % a.raster_cap), lane, a.raster_cap) * a.words + blockIdx.x] = my_mask;
+  }
+  for (uint64_t some = __ballot(my_mask != 0); some; some &= some - 1) {  // steps with spikes
+    const int w = __builtin_ctzll(some);
+    const uint64_t mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(my_mask >> 32), w) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)my_mask, w);
+    const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)base, w) + lanes_below(mask);
+    if (((my_spikes >> w) & 1u) && pos < a.q.group_cap)
+      a.q.ids[(size_t)ring_add(slot0, (uint32_t)w, a.slots) * a.q.stride + group * a.q.group_cap + pos] = (int32_t)i;
   }
 }
 
@@ -1101,6 +1207,16 @@ void launch_kernel(void (*kernel)(KArgs...), uint32_t grid, uint32_t block, size
 }
 
 hipError_t launch_update(const UpdateArgs &a, uint32_t steps, hipStream_t s, const LaunchEvents &ev) {
+  // Up to 81,920 neurons all workgroups of the split form are resident at once; past that its
+  // sixth wavefronts, which alone walk the membranes, bound it (15 steps of 200,000 neurons:
+  // 17 against 15 us, of 1,000,000: 64 against 42), and below five steps there is nothing to
+  // split (73,000 neurons, 4 steps: 7.2 against 6.8).
+  const uint32_t blocks = (a.n + kWave - 1) / kWave;
+  if (!a.plastic && steps > 4 && blocks <= 1280) {
+    launch_kernel(a.table_len > 1 ? k_update_window<true> : k_update_window<false>, blocks, kWindowBlock, 0, s,
+                  ev.start, ev.stop, a, steps);
+    return hipGetLastError();
+  }
   const uint32_t grid = (a.n + kUpdateBlock - 1) / kUpdateBlock;
   // windows of 13 to 17 steps always span 4 or 5 quads, whatever their first step
   if (steps >= 4 * (kShortQuads - 1) - 3 && steps <= 4 * kShortQuads - 3)

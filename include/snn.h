@@ -150,8 +150,8 @@ typedef struct {
     float gen_rows_ms;      /* device time of the row-length pass and its scan */
     float gen_fill_ms;      /* device time of the synapse fill */
     float index_ms;         /* device time of the delivery indexes (in-edge index with STDP,
-                               tile offsets of the tiled delivery; stream time between two
-                               events, host allocation gaps included) */
+                               tile offsets of the tiled delivery unless the fill wrote them;
+                               stream time between two events, host allocation gaps included) */
     uint32_t tile_offset_bytes; /* bytes per stored tile boundary of the tiled delivery: 2
                                    (every row below 65,536 synapses) or 4; 0 without tiles */
     uint32_t target_bytes;  /* bytes per target the delivery reads: 2 for the tiled delivery

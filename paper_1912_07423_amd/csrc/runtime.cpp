@@ -452,15 +452,19 @@ hipEvent_t new_event() {
 
 // Indexes of the tiled delivery: the tile boundaries of every row (uint16 when no row can
 // reach 65,536 synapses, else uint32) and the 16-bit copy of the targets it streams.
-void alloc_tile_offsets(snn_network *net) {
+snn::RowIndex alloc_tile_offsets(snn_network *net) {
   const uint64_t count = ((net->nnz + 7) & ~7ull) + 8;  // whole 16-byte groups, one spare
   if (!net->col16) net->col16 = dev_array<uint16_t>(net, count);
   net->tile_off16 = net->row_len_bound < 65536;
   const size_t entries = (size_t)net->n * (net->tiles + 1);
   if (net->tile_off16) net->tile_off = dev_array<uint16_t>(net, entries);
   else net->tile_off = dev_array<uint32_t>(net, entries);
-  check(snn::launch_tile_index(net->row_ptr, net->col, net->n, net->nnz, count, net->tiles, net->tile_size,
-                               net->col16, net->tile_off, net->tile_off16, net->stream),
+  return {net->col16, net->tile_off, net->nnz, count, net->tiles, net->tile_size, net->tile_off16, 0u};
+}
+
+void fill_tile_offsets(snn_network *net, const snn::RowIndex &x) {
+  check(snn::launch_tile_index(net->row_ptr, net->col, net->n, x.nnz, x.count, x.tiles, x.tile_size, x.col16,
+                               x.tile_off, x.off16, net->stream),
         "tile index");
 }
 
@@ -580,8 +584,16 @@ void build(snn_network *net) {
     if (q.kind == SNN_PROJ_FIXED_OUT) max_fixed_k = std::max(max_fixed_k, q.k);
     else all_fixed = false;
   }
+  choose_delivery(net);
+  net->solo = choose_solo(net);
+  snn::RowIndex index{};
+  if (net->delivery == SNN_DELIVERY_TILED) index = alloc_tile_offsets(net);
+  // rows of one fixed out-degree projection get their indexes while they are filled
+  bool one_each = all_fixed;
+  for (uint32_t a = 0; a < n_pops; ++a) one_each = one_each && pop_proj[a + 1] - pop_proj[a] <= 1;
   check(hipEventRecord(ev[2], s), "hipEventRecord");
-  check(snn::launch_fill_rows(g, max_fixed_k, all_fixed, net->row_ptr, net->col, net->w_q16, net->w_f32, s),
+  check(snn::launch_fill_rows(g, max_fixed_k, all_fixed, net->row_ptr, net->col, net->w_q16, net->w_f32,
+                              one_each ? index : snn::RowIndex{}, s),
         "fill rows");
   check(hipEventRecord(ev[3], s), "hipEventRecord");
   check(hipEventRecord(ev[4], s), "hipEventRecord");
@@ -604,9 +616,7 @@ void build(snn_network *net) {
                                     net->in_src, net->in_edge, s), "fill in-edges");
   }
 
-  choose_delivery(net);
-  net->solo = choose_solo(net);
-  if (net->delivery == SNN_DELIVERY_TILED) alloc_tile_offsets(net);
+  if (index.col16 && !one_each) fill_tile_offsets(net, index);
   net->windows = choose_windows(net);
   check(hipEventRecord(ev[5], s), "hipEventRecord");
 
@@ -1328,7 +1338,7 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->solo = choose_solo(net);
     if (net->delivery == SNN_DELIVERY_TILED) {
       net->tile_off = nullptr;  // a fresh index; the old one stays valid until this succeeds
-      alloc_tile_offsets(net);  // reuses col16 when it exists (it does not depend on the tiling)
+      fill_tile_offsets(net, alloc_tile_offsets(net));  // reuses col16 when it exists (any tiling's)
       check(hipStreamSynchronize(net->stream), "sync after tile offsets");
     } else {
       net->tile_off = nullptr;

@@ -427,10 +427,20 @@ struct StageArgs {
 hipError_t launch_stage_window(const StageArgs &a, hipStream_t s);
 hipError_t launch_row_lengths(const GenArgs &g, uint32_t *len, uint32_t *plast_rel,
                               uint32_t *plast_len, hipStream_t s);
+// Indexes of the tiled delivery, written by the fill as well if col16 is not null (then every
+// population has at most one projection, of fixed out-degree).
+struct RowIndex {
+  uint16_t *col16;     // [count]
+  void *tile_off;      // [n][tiles + 1], uint16 if off16
+  uint64_t nnz, count;
+  uint32_t tiles, tile_size;
+  bool off16;
+  uint32_t inv32;      // set by the launcher
+};
 // all_fixed: every projection is fixed out-degree (no ER rows), which allows one
 // workgroup per row for long rows.
 hipError_t launch_fill_rows(const GenArgs &g, uint32_t max_fixed_k, bool all_fixed, const uint64_t *row_ptr,
-                            int32_t *col, int32_t *w_q16, float *w_f32, hipStream_t s);
+                            int32_t *col, int32_t *w_q16, float *w_f32, RowIndex index, hipStream_t s);
 hipError_t launch_spacing_gaps(const uint32_t *words, uint64_t n, uint32_t *gaps, hipStream_t s);
 hipError_t launch_scan_u32_to_u64(const uint32_t *in, uint64_t *out, uint32_t n,
                                   uint64_t *block_sums, hipStream_t s);

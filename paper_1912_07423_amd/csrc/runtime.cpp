@@ -200,6 +200,61 @@ class Stage {
   StageBlock b_;
 };
 
+// ---- streams -------------------------------------------------------------------------
+// Networks without a caller's stream have one of their own.  Making and destroying one takes
+// about 50 us each, so up to kStreamKeep idle ones are kept; snn_memory_cache_release destroys
+// them.
+constexpr size_t kStreamKeep = 8;
+struct IdleStream {
+  int device;
+  hipStream_t stream;
+};
+std::mutex g_stream_mutex;
+std::vector<IdleStream> g_streams;
+
+hipStream_t stream_take(int device) {
+  {
+    std::lock_guard<std::mutex> lock(g_stream_mutex);
+    for (size_t k = 0; k < g_streams.size(); ++k) {
+      if (g_streams[k].device != device) continue;
+      hipStream_t s = g_streams[k].stream;
+      g_streams.erase(g_streams.begin() + (std::ptrdiff_t)k);
+      return s;
+    }
+  }
+  hipStream_t s = nullptr;
+  check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "hipStreamCreate");
+  return s;
+}
+
+// Back after everything on it has run without an error (`clean`).
+void stream_give(int device, hipStream_t s, bool clean) {
+  if (clean) {
+    try {
+      std::lock_guard<std::mutex> lock(g_stream_mutex);
+      if (g_streams.size() < kStreamKeep) {
+        g_streams.push_back({device, s});
+        return;
+      }
+    } catch (...) {
+    }
+  }
+  (void)hipStreamDestroy(s);
+}
+
+void stream_release(int device) {
+  std::vector<hipStream_t> drop;
+  {
+    std::lock_guard<std::mutex> lock(g_stream_mutex);
+    for (size_t k = g_streams.size(); k-- > 0;) {
+      if (device >= 0 && g_streams[k].device != device) continue;
+      drop.push_back(g_streams[k].stream);
+      g_streams.erase(g_streams.begin() + (std::ptrdiff_t)k);
+    }
+  }
+  for (hipStream_t s : drop) (void)hipStreamDestroy(s);
+}
+
 void *dev_alloc(snn_network *net, size_t bytes) {
   if (bytes == 0) bytes = 16;
   bytes = (bytes + 255) & ~(size_t)255;
@@ -224,7 +279,7 @@ T *dev_array(snn_network *net, size_t count) {
 }
 
 void release(snn_network *net) {
-  if (net->stream) (void)hipStreamSynchronize(net->stream);
+  const bool clean = net->stream && hipStreamSynchronize(net->stream) == hipSuccess;
   if (net->graph) (void)hipGraphExecDestroy(net->graph);
   for (auto &a : net->allocs) {
     if (net->has_alloc) net->alloc.free(a.p, a.bytes, (void *)net->stream, net->alloc.ctx);
@@ -242,7 +297,7 @@ void release(snn_network *net) {
   net->prof_pending.clear();
   for (hipEvent_t e : net->event_pool) (void)hipEventDestroy(e);
   net->event_pool.clear();
-  if (net->own_stream && net->stream) (void)hipStreamDestroy(net->stream);
+  if (net->own_stream && net->stream) stream_give(net->device, net->stream, clean);
 }
 
 // ---- definitions of the derived constants -----------------------------------------
@@ -544,8 +599,21 @@ void build(snn_network *net) {
   uint64_t *scan_tmp = dev_array<uint64_t>(net, snn::scan_scratch_elems(n));
   check(snn::launch_scan_u32_to_u64(len, net->row_ptr, n, scan_tmp, s), "row scan");
   check(hipEventRecord(ev[1], s), "hipEventRecord");
-  check(hipMemcpyAsync(&net->nnz, net->row_ptr + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s), "read nnz");
-  check(hipStreamSynchronize(s), "sync after row scan");
+  uint32_t max_fixed_k = 0;
+  bool all_fixed = true;
+  for (const snn::GenProj &q : gp) {
+    if (q.kind == SNN_PROJ_FIXED_OUT) max_fixed_k = std::max(max_fixed_k, q.k);
+    else all_fixed = false;
+  }
+  if (all_fixed) {  // the number of synapses is known without the scan
+    net->nnz = 0;
+    for (uint32_t a = 0; a < n_pops; ++a)
+      for (uint32_t q = pop_proj[a]; q < pop_proj[a + 1]; ++q)
+        net->nnz += (uint64_t)(net->pop_off[a + 1] - net->pop_off[a]) * gp[q].k;
+  } else {
+    check(hipMemcpyAsync(&net->nnz, net->row_ptr + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s), "read nnz");
+    check(hipStreamSynchronize(s), "sync after row scan");
+  }
   if (net->plastic && net->nnz >= (1ull << 32)) fail(SNN_E_INVALID, "plastic networks are limited to 2^32 synapses");
   net->nnz_alloc = ((net->nnz + 3) & ~3ull) + 4;  // 16-byte groups of the atomic delivery
   net->col = dev_array<int32_t>(net, net->nnz_alloc);
@@ -577,12 +645,6 @@ void build(snn_network *net) {
   } else {
     net->w_q16 = dev_array<int32_t>(net, net->nnz_alloc);
     check(hipMemsetAsync(net->w_q16 + net->nnz, 0, pad_bytes, s), "clear w padding");
-  }
-  uint32_t max_fixed_k = 0;
-  bool all_fixed = true;
-  for (const snn::GenProj &q : gp) {
-    if (q.kind == SNN_PROJ_FIXED_OUT) max_fixed_k = std::max(max_fixed_k, q.k);
-    else all_fixed = false;
   }
   choose_delivery(net);
   net->solo = choose_solo(net);
@@ -1191,7 +1253,9 @@ void run(snn_network *net, uint64_t n_steps) {
     return;
   }
   while (n_steps > 0) {
-    if (!net->profiling && n_steps >= 64 && net->stream) {
+    // (capturing a graph takes the host as long as some ten windows: a short first run, with
+    // which a network may also end, is launched directly)
+    if (!net->profiling && n_steps >= 64 && net->stream && (net->graph || net->t_host > 0 || n_steps >= 256)) {
       ensure_graph(net);
       if (n_steps >= net->graph_steps) {
         check(hipGraphLaunch(net->graph, net->stream), "graph launch");
@@ -2197,7 +2261,7 @@ snn_status snn_build_network(const snn_params *prm, const snn_population *pops, 
       if (stream) {
         net->stream = (hipStream_t)stream;
       } else {
-        check(hipStreamCreateWithFlags(&net->stream, hipStreamNonBlocking), "hipStreamCreate");
+        net->stream = stream_take(net->device);
         net->own_stream = true;
       }
       const auto t0 = std::chrono::steady_clock::now();
@@ -2257,6 +2321,7 @@ snn_status snn_memory_cache_release(int device) {
   return guarded([&] {
     pool_release(device);
     stage_release();
+    stream_release(device);
   });
 }
 

@@ -290,7 +290,7 @@ def bench_stdp(args):
     i0 = net.info()   # with lazy plasticity this brings every row current
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    net.run(steps)    # launches replayed from captured HIP graphs, no per-launch timing
+    net.run(steps)    # as a user runs it, no per-launch timing
     i1 = net.info()   # the timed region ends with every row current (weights, touches)
     wall = time.perf_counter() - t0
     events, touches = i1["events"] - i0["events"], i1["touches"] - i0["touches"]

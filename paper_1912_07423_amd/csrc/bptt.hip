@@ -537,14 +537,14 @@ __global__ __launch_bounds__(256) void k_input_rows(BpttArgs a, const float *x) 
 // neurons (neuron 64 q + lane of its range), one barrier per step, at which the step's spikes
 // are published as words in LDS.  Every wavefront takes the sources off the words by itself,
 // mostly with scalar instructions, so few wavefronts with several words each do better than
-// one per word (1,024 neurons: 1.4 us per step, 1.6 with 16 wavefronts).  Global memory other
+// one per word (1,024 neurons: 1.29 us per step with 8 wavefronts, 1.35 with 4, 1.6 with 16).  Global memory other
 // than weight rows is touched once per kSeqChunk steps: the chunk's input currents, requested
 // a chunk ahead, pass through LDS (so that a step can index them), where the membranes replace
 // them until the chunk is written out with its spike words; a store in every step would be
 // waited for by the step's row reads.  Per step a wavefront reads the previous step's words,
 // takes its sources off them in ascending order and adds their rows, up to kSeqRows in
 // flight; with more sources than twice the longest column it walks the columns (target-major
-// pairs) and tests each source's bit instead.  64 x 250 x 1,024 with 3.7 spikes per step: 344
+// pairs) and tests each source's bit instead.  64 x 250 x 1,024 with 3.7 spikes per step: 323
 // us, where a launch per step took 1,540; 19 x 103 x 201: 49 us (370).
 constexpr uint32_t kSeqChunk = 16;
 constexpr uint32_t kSeqThreads = kEventMaxNeurons / 4;
@@ -1603,7 +1603,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t 
     // whole wavefronts up to Hp, a multiple of 256
     const size_t lds = (size_t)kSeqChunk * a.Hp * sizeof(float);
     if (a.Hp <= 256) hipLaunchKernelGGL(k_hidden_seq<1>, dim3(a.B), dim3(a.Hp), lds, s, a);
-    else if (a.Hp <= 512) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
+    else if (a.Hp <= 1024) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
     else hipLaunchKernelGGL(k_hidden_seq<4>, dim3(a.B), dim3(a.Hp / 4), lds, s, a);
     hipLaunchKernelGGL(k_readout_events, dim3(blocks_for((uint64_t)a.B * a.T, 4)), dim3(256), 0, s, a, a.ro);
     hipLaunchKernelGGL(k_readout_scan_events, dim3(a.B, blocks_for(a.O, 64)), dim3(64), 0, s, a, a.ro);
@@ -1760,6 +1760,7 @@ hipError_t bptt_prepare(const BpttArgs &a) {
   if (a.S) e = allow(reinterpret_cast<const void *>(&k_adjoint_slice), kSliceMaxNeurons * 32u);
   if (e == hipSuccess && a.events) {
     e = allow(reinterpret_cast<const void *>(&k_hidden_seq<4>), kEventMaxNeurons * kSeqChunk * sizeof(float));
+    if (e == hipSuccess) e = allow(reinterpret_cast<const void *>(&k_hidden_seq<2>), 1024u * kSeqChunk * sizeof(float));
     if (e == hipSuccess)
       e = allow(reinterpret_cast<const void *>(&k_adjoint_seq<kSeqRegs>), kSeqMaxMore * kWave * kSeqGroupBytes);
   }

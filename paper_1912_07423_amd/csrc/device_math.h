@@ -104,11 +104,44 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan<uint32_t>(uint32_t x) {
   return (uint32_t)v;
 }
 
+// The same shifts applied to both halves of a 64-bit value.
+template <int kCtrl, int kRows, bool kZeroOutside>
+__device__ __forceinline__ uint64_t add_dpp_u64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xf, kZeroOutside);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRows, 0xf, kZeroOutside);
+  return v + (((uint64_t)hi << 32) | lo);
+}
+
+template <>
+__device__ __forceinline__ uint64_t wave_inclusive_scan<uint64_t>(uint64_t x) {
+  x = add_dpp_u64<0x111, 0xf, true>(x);
+  x = add_dpp_u64<0x112, 0xf, true>(x);
+  x = add_dpp_u64<0x114, 0xf, true>(x);
+  x = add_dpp_u64<0x118, 0xf, true>(x);
+  x = add_dpp_u64<0x142, 0xa, false>(x);
+  x = add_dpp_u64<0x143, 0xc, false>(x);
+  return x;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T x) {
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
   return x;
+}
+
+// Integer sums by the scans above (every lane active): register operations, where a shuffle is
+// a round trip through LDS, twelve of them for a 64-bit sum.
+template <>
+__device__ __forceinline__ uint32_t wave_sum<uint32_t>(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(x), kWave - 1);
+}
+template <>
+__device__ __forceinline__ uint64_t wave_sum<uint64_t>(uint64_t x) {
+  x = wave_inclusive_scan(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, kWave - 1);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), kWave - 1);
+  return ((uint64_t)hi << 32) | lo;
 }
 
 // Constants of the LIF update (Sec. IV: current-based LIF), derived once on the host.

@@ -112,26 +112,6 @@ __device__ __forceinline__ uint64_t div_floor_u64(uint64_t num, uint64_t den, do
   return q;
 }
 
-// 64-bit inclusive scan over the wave by DPP lane shifts applied to both halves (the
-// same shifts as the 32-bit scan: 1, 2, 4, 8 inside rows of 16 lanes, then rows 0 and 2
-// into rows 1 and 3, then lane 31 into rows 2 and 3); every lane must be active.
-template <int kCtrl, int kRows, bool kZeroOutside>
-__device__ __forceinline__ uint64_t add_dpp_u64(uint64_t v) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xf, kZeroOutside);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRows, 0xf, kZeroOutside);
-  return v + (((uint64_t)hi << 32) | lo);
-}
-
-__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t x) {
-  x = add_dpp_u64<0x111, 0xf, true>(x);   // row_shr:1
-  x = add_dpp_u64<0x112, 0xf, true>(x);   // row_shr:2
-  x = add_dpp_u64<0x114, 0xf, true>(x);   // row_shr:4
-  x = add_dpp_u64<0x118, 0xf, true>(x);   // row_shr:8
-  x = add_dpp_u64<0x142, 0xa, false>(x);  // row_bcast:15, rows 1 and 3
-  x = add_dpp_u64<0x143, 0xc, false>(x);  // row_bcast:31, rows 2 and 3
-  return x;
-}
-
 __device__ __forceinline__ uint64_t last_lane_u64(uint64_t x) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, kWave - 1);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), kWave - 1);
@@ -313,7 +293,7 @@ __device__ void fixed_pass2(const GenArgs &g, const GenProj &pj, uint32_t i, uin
     }
     // four gaps are below 2^31 together
     const uint32_t lane_total = gap[0] + gap[1] + gap[2] + gap[3];
-    const uint64_t incl = wave_scan_u64(lane_total);
+    const uint64_t incl = wave_inclusive_scan((uint64_t)lane_total);
     const uint64_t s0 = carry + (incl - lane_total);
     const double s0_d = (double)s0;
     // q_k = floor(S_{k+1} spare / total + 1/2) <= spare < 2^32 from binary64: the

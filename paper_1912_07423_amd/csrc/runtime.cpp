@@ -830,6 +830,7 @@ snn::DeliverArgs deliver_args(snn_network *net) {
   a.window_max = net->window;
   a.tiles = net->tiles;
   a.tile_size = net->tile_size;
+  a.row_groups = (uint32_t)(net->nnz / std::max(1u, net->n) / 8);
   a.off16 = net->tile_off16 ? 1u : 0u;
   a.advance = 1;
   return a;

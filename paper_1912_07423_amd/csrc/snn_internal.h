@@ -124,6 +124,7 @@ struct DeliverArgs {
   Ctl *ctl;
   uint32_t n, slots, n_inbuf, delay, window_max;
   uint32_t tiles, tile_size;
+  uint32_t row_groups;    // 16-byte groups of targets of a mean row (tiled delivery)
   uint32_t off16;
   uint32_t advance;       // this launch closes the window: advance the step counter
   float *x_pre, *x_post;  // eager STDP: here x_pre += 1 for S_{t-d}, x_post += 1 for S_t (else null)

@@ -677,13 +677,19 @@ __device__ __forceinline__ uint32_t ranges_needed(uint32_t c, uint32_t steps, fl
 // are clamped to single tiles; round 2 then still finds the bound); round 2 tries 64
 // evenly spaced bounds in (X_{j-1}, X_j] for the first feasible X_j, the last being X_j
 // itself.  Without a feasible X_j every step takes r_min ranges.
-__device__ void make_schedule(uint32_t c, uint32_t steps, uint32_t tiles, uint32_t grid, TileSchedule &sch) {
+// A window with so few spikes that every range of an even split streams at most one batch of
+// groups (row_groups of a whole row) gains nothing from a balanced one, and the search is on
+// every workgroup's way to its first load: it takes the even split.
+__device__ void make_schedule(uint32_t c, uint32_t steps, uint32_t tiles, uint32_t grid, uint32_t row_groups,
+                              uint32_t batch, TileSchedule &sch) {
   const uint32_t lane = lane_id();
   const uint32_t r_min = (tiles + kTileGroupMax - 1) / kTileGroupMax;
   const float p_f = (float)tiles;
   const uint32_t total = wave_sum(c);
+  const uint32_t even = min(max(grid / steps, r_min), tiles);
+  const bool light = __ballot((uint64_t)c * (row_groups / even + 1u) > batch) == 0;
   float inv_best = 0.f;
-  if (total > 0 && grid > steps * r_min) {
+  if (!light && total > 0 && grid > steps * r_min) {
     const float x_lb = (float)total * p_f / (float)grid;
     const float x1 = x_lb * exp2f(0.25f * (float)lane);
     const uint64_t ok1 = __ballot(ranges_needed(c, steps, p_f, 1.0f / x1, r_min, tiles) <= grid);
@@ -698,7 +704,7 @@ __device__ void make_schedule(uint32_t c, uint32_t steps, uint32_t tiles, uint32
       inv_best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv2), (int)k));
     }
   }
-  const uint32_t r = lane < steps ? ranges_at((float)c * p_f, inv_best, r_min, tiles) : 0u;
+  const uint32_t r = lane >= steps ? 0u : light ? even : ranges_at((float)c * p_f, inv_best, r_min, tiles);
   const uint32_t incl = wave_inclusive_scan(r);
   sch.r[lane] = r;
   sch.first[lane + 1] = incl;
@@ -764,7 +770,7 @@ __global__ __launch_bounds__(kBlock) void k_deliver_tiled(DeliverArgs a, uint32_
     s_slot[lane] = slot;
 #pragma unroll
     for (uint32_t g = 0; g <= kQueueGroups; ++g) s_qpre[lane][g] = qp[g];
-    make_schedule(qp[kQueueGroups], steps, a.tiles, grid, sch);
+    make_schedule(qp[kQueueGroups], steps, a.tiles, grid, a.row_groups, kBlock * kU, sch);
   } else {
     const uint32_t acc_n = min(kTileGroupMax, a.tiles) * a.tile_size;
     for (uint32_t j = threadIdx.x - kWave; j < acc_n; j += kBlock - kWave) acc[j] = 0;

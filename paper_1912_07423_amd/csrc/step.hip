@@ -759,6 +759,7 @@ __global__ __launch_bounds__(kBlock) void k_deliver_tiled(DeliverArgs a, uint32_
 
   // ---- the window's queue lengths and the balanced schedule (wave 0), while the
   // other waves clear the accumulators ----
+  if (threadIdx.x == 0) s_ev = 0;
   if (wave == 0) {
     uint32_t qp[kQueueGroups + 1] = {};
     uint32_t slot = 0;
@@ -792,8 +793,6 @@ __global__ __launch_bounds__(kBlock) void k_deliver_tiled(DeliverArgs a, uint32_
   for (uint32_t g = 0; g <= kQueueGroups; ++g) qpre[g] = s_qpre[w][g];
   const uint32_t cnt = qpre[kQueueGroups];
   uint64_t ev = 0;  // synapses of the sub-rows this thread fetched
-  if (threadIdx.x == 0) s_ev = 0;
-  __syncthreads();
   for (uint32_t c0 = 0; c0 < cnt; c0 += kBlock) {
     const uint32_t mm = min((uint32_t)kBlock, cnt - c0);
     // (1) sub-row bounds of this chunk's spikes and their 16-byte group counts
@@ -825,13 +824,10 @@ __global__ __launch_bounds__(kBlock) void k_deliver_tiled(DeliverArgs a, uint32_
     const uint32_t incl = wave_inclusive_scan(groups);
     if (lane == kWave - 1) s_wave[wave] = incl;
     __syncthreads();
-    if (wave == 0) {
-      const uint32_t x = lane < kWaves ? s_wave[lane] : 0u;
-      const uint32_t xi = wave_inclusive_scan(x);
-      if (lane < kWaves) s_wave[lane] = xi - x;
-    }
-    __syncthreads();
-    const uint32_t pre = s_wave[wave] + incl - groups;
+    // every wavefront scans the wavefronts' totals by itself, which costs less than a barrier
+    const uint32_t before = wave_inclusive_scan(lane < kWaves ? s_wave[lane] : 0u);
+    const uint32_t own = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)before, (int)wave) - own + incl - groups;
     if (threadIdx.x < mm) {
       s_pre[threadIdx.x] = pre;
       s_lo[threadIdx.x] = lo;

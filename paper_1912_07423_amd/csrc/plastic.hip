@@ -22,7 +22,7 @@
 // lines per sub-row (weights, a part of a line of targets) in the window launch, two per
 // potentiated synapse (weight, its source's trace) in the prepare launch.  A window of nine
 // steps of 100,000 neurons (2e8 synapses, 130 arriving spikes a step) takes 39 + 62 us with
-// 1.9e6 potentiations, one of 10,000 neurons (45 spikes a step) 18 + 10 us: 8.0 and 3.1 us a
+// 1.9e6 potentiations, one of 10,000 neurons (45 spikes a step) 17 + 10 us: 7.9 and 3.0 us a
 // step in all, where update, plasticity and delivery launches took 30 and 17.
 //
 // k_plastic_import and k_plastic_export take the spikes to and from the FIFO ring's form at

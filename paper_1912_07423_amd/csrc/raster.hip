@@ -15,11 +15,13 @@
 #include <algorithm>
 
 #include "device_math.h"
+#include "raster_units.h"
 #include "snn_internal.h"
 
 namespace snn {
 namespace {
 
+static_assert(kUnitLanes == kWave, "a unit is whole rounds of a wavefront");
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kSmallBlock = 1024;
@@ -124,17 +126,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_raster_small(RasterArgs a) {
 // One workgroup reads 16 words per lane of a range of this size, about what the two further
 // launches of the general form cost (2.5 us each).
 constexpr uint64_t kSmallWords = 16384;
-// Units of at least 8 x 64 words, and few enough that one workgroup scans them in eight
-// rounds.
-constexpr uint64_t kMinIters = 8;
 
 }  // namespace
-
-uint64_t raster_units(uint64_t words, uint64_t *unit_words) {
-  const uint64_t per = std::max<uint64_t>(kMinIters, (words + kMaxRasterUnits * kWave - 1) / (kMaxRasterUnits * kWave));
-  if (unit_words) *unit_words = per * kWave;
-  return (words + per * kWave - 1) / (per * kWave);
-}
 
 // Counts the range's spikes into *a.count and, with a.out_cap > 0, writes the pairs.  The
 // range is not empty.
@@ -143,7 +136,9 @@ hipError_t launch_raster_pairs(RasterArgs a, hipStream_t s) {
     k_raster_small<<<1, kSmallBlock, 0, s>>>(a);
     return hipGetLastError();
   }
-  a.units = (uint32_t)raster_units(a.total_words, &a.unit_words);
+  const uint64_t units = raster_units(a.total_words, &a.unit_words);
+  if (units > a.scratch) return hipErrorInvalidValue;
+  a.units = (uint32_t)units;
   const uint32_t grid = (a.units + kWavesPerBlock - 1) / kWavesPerBlock;
   k_raster_count<<<grid, kBlock, 0, s>>>(a);
   k_raster_offsets<<<1, kSmallBlock, 0, s>>>(a);

@@ -16,6 +16,7 @@
 #include <string>
 #include <vector>
 
+#include "raster_units.h"
 #include "snn_internal.h"
 
 namespace {
@@ -697,7 +698,8 @@ void build(snn_network *net) {
   net->qlen = dev_array<uint32_t>(net, (size_t)net->slots * snn::kQueueGroups * snn::kQlenStride);
   // the raster ring, and behind it the offsets scratch of the spike download
   const size_t ring_words = (size_t)net->raster_cap * net->words;
-  net->raster = dev_array<uint64_t>(net, ring_words + snn::raster_units(ring_words, nullptr));
+  net->raster_scratch = snn::raster_scratch(ring_words);
+  net->raster = dev_array<uint64_t>(net, ring_words + net->raster_scratch);
   net->raster_offset = net->raster + ring_words;
   net->d_table32 = dev_array<uint32_t>(net, snn::kTableCap);
   net->d_guide = dev_array<uint16_t>(net, snn::kGuideBuckets);
@@ -1335,6 +1337,7 @@ void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps,
   a.total_words = (t1 - t0) * net->words;
   a.t_begin = t0;
   a.offset = net->raster_offset;
+  a.scratch = net->raster_scratch;
   a.words = net->words;
   a.count = reinterpret_cast<uint64_t *>(stage.data());
   a.steps = reinterpret_cast<uint32_t *>(stage.data() + kHead);

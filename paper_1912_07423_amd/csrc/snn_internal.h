@@ -380,7 +380,6 @@ struct LaunchEvents {
 };
 
 // Spike download (raster.hip): the (step, id) pairs of a range of raster rows.
-constexpr uint64_t kMaxRasterUnits = 8192;
 struct RasterArgs {
   const uint64_t *raster;
   uint64_t ring_words;    // raster_cap * words
@@ -388,14 +387,13 @@ struct RasterArgs {
   uint64_t total_words;   // rows * words
   uint64_t t_begin;
   uint64_t unit_words;    // words per unit (set by the launcher)
-  uint64_t *offset;       // [units] scratch: counts, then offsets
+  uint64_t *offset;       // [scratch] counts, then offsets of the units
+  uint64_t scratch;       // entries of offset: at least the range's units (raster_units.h)
   uint64_t *count;        // host-visible: spikes in the range
   uint32_t *steps, *ids;  // host-visible: pairs [out_lo, out_lo + out_cap)
   uint64_t out_lo, out_cap;
   uint32_t words, units;
 };
-// Units of a range of `words` words (the size of its offset scratch) and their length.
-uint64_t raster_units(uint64_t words, uint64_t *unit_words);
 hipError_t launch_raster_pairs(RasterArgs a, hipStream_t s);
 
 // kernel launchers (step.hip / generate.hip)
@@ -507,7 +505,8 @@ struct snn_network {
   uint32_t *qlen = nullptr;
   uint32_t queue_stride = 0, group_cap = 0;  // entries per queue slot / per sub-queue
   uint64_t *raster = nullptr;
-  uint64_t *raster_offset = nullptr;  // scratch of the spike download
+  uint64_t *raster_offset = nullptr;  // scratch of the spike download, its entries
+  uint64_t raster_scratch = 0;
   uint32_t *d_table32 = nullptr;
   uint16_t *d_guide = nullptr;
   snn::Ctl *ctl = nullptr;

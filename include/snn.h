@@ -212,10 +212,21 @@ snn_status snn_step(snn_network *net);
  * net.step()`), each step being the Fig. 1 pipeline.  Launches are grouped into windows
  * of up to `window` steps and replayed from a captured HIP graph where possible; a small
  * static network without drive whose delivery is left to AUTO (and whose window, tiles,
- * block and grid are 0) is stepped by one persistent launch instead.  The
+ * block and grid are 0) is stepped by one persistent launch instead, and an eagerly plastic
+ * one (delay of at least two steps, the same parameters 0) in windows of up to delay - 1
+ * steps by two launches each (snn_get_route).  The
  * result is identical to n_steps calls of snn_step.  Asynchronous.  SNN_E_STATE for a
  * batch member; SNN_E_HIP if a launch fails. */
 snn_status snn_run(snn_network *net, uint32_t n_steps);
+
+/* How snn_run would advance the network now, by more than one step.  The results do not
+ * depend on it.  SNN_E_STATE for a batch member. */
+#define SNN_ROUTE_LAUNCHES 0u   /* launches per window of steps, as snn_step and profiled
+                                   steps always take */
+#define SNN_ROUTE_PERSISTENT 1u /* one persistent launch of one workgroup */
+#define SNN_ROUTE_WINDOWS 2u    /* two launches per up to delay - 1 steps of an eagerly plastic
+                                   network, a workgroup per range of targets */
+snn_status snn_get_route(snn_network *net, uint32_t *route);
 
 /* Download of timestamped spikes (Sec. III-B: the simulators compared there let the
  * user download the spikes of a run with their time stamps): the spikes of steps

@@ -23,6 +23,7 @@ PROJ_KIND = {"er": 0, "fixed": 1}
 DELIVERY = {"auto": 0, "atomic": 1, "tiled": 2}
 PLASTICITY = {"eager": 0, "lazy": 1}
 DELIVERY_NAME = {1: "atomic", 2: "tiled"}
+ROUTE_NAME = {0: "launches", 1: "persistent", 2: "windows"}
 
 
 class Population(C.Structure):
@@ -115,6 +116,7 @@ SIGNATURES = {
                                       C.c_void_p, C.POINTER(C.c_void_p)]),
     "snn_step": (C.c_int32, [C.c_void_p]),
     "snn_run": (C.c_int32, [C.c_void_p, C.c_uint32]),
+    "snn_get_route": (C.c_int32, [C.c_void_p, C.POINTER(C.c_uint32)]),
     "snn_get_raster": (C.c_int32, [C.c_void_p, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p,
                                    C.c_uint64, C.POINTER(C.c_uint64)]),
     "snn_get_raster_bits": (C.c_int32, [C.c_void_p, C.c_uint64, C.c_uint64, C.c_void_p]),

@@ -1248,9 +1248,17 @@ void ensure_graph(snn_network *net) {
   net->graph_steps = steps;
 }
 
+// How a run of more than one step goes (the windows after the launches that queues written by
+// the caller still need).
+uint32_t route(const snn_network *net) {
+  if (net->profiling) return SNN_ROUTE_LAUNCHES;
+  return net->solo ? SNN_ROUTE_PERSISTENT : net->windows ? SNN_ROUTE_WINDOWS : SNN_ROUTE_LAUNCHES;
+}
+
 void run(snn_network *net, uint64_t n_steps) {
-  if (net->solo && !net->profiling && n_steps > 1) return run_solo(net, n_steps);
-  if (net->windows && !net->profiling && n_steps > 1) {
+  const uint32_t way = n_steps > 1 ? route(net) : SNN_ROUTE_LAUNCHES;
+  if (way == SNN_ROUTE_PERSISTENT) return run_solo(net, n_steps);
+  if (way == SNN_ROUTE_WINDOWS) {
     for (; n_steps > 0 && net->t_host < net->windows_from; --n_steps) issue_window(net, 1);
     if (n_steps > 0) run_windows(net, n_steps);
     return;
@@ -2300,6 +2308,14 @@ snn_status snn_run(snn_network *net, uint32_t n_steps) {
     if (!net) fail(SNN_E_INVALID, "null network");
     refuse_member(net);
     run(net, n_steps);
+  });
+}
+
+snn_status snn_get_route(snn_network *net, uint32_t *out) {
+  return guarded([&] {
+    if (!net || !out) fail(SNN_E_INVALID, "null argument");
+    refuse_member(net);
+    *out = route(net);
   });
 }
 

@@ -152,6 +152,12 @@ class Network:
     def sync(self):
         L.check(self._lib.snn_sync(self._h))
 
+    def route(self):
+        """How run() would advance the network now: "launches", "persistent" or "windows"."""
+        r = C.c_uint32()
+        L.check(self._lib.snn_get_route(self._h, C.byref(r)))
+        return L.ROUTE_NAME[r.value]
+
     # -- readback ---------------------------------------------------------------------
     def info(self):
         i = L.Info()

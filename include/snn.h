@@ -225,7 +225,10 @@ snn_status snn_run(snn_network *net, uint32_t n_steps);
                                    steps always take */
 #define SNN_ROUTE_PERSISTENT 1u /* one persistent launch of one workgroup */
 #define SNN_ROUTE_WINDOWS 2u    /* two launches per up to delay - 1 steps of an eagerly plastic
-                                   network, a workgroup per range of targets */
+                                   network, a workgroup per range of targets.  Taken only where
+                                   device memory for its buffers is left: 2 bytes (4 with rows of
+                                   65,536 and more) per neuron and range of 64 to 512 targets, up
+                                   to 256 MiB of laid-out rows, and 2 delay + 1 spike lists */
 snn_status snn_get_route(snn_network *net, uint32_t *route);
 
 /* Download of timestamped spikes (Sec. III-B: the simulators compared there let the

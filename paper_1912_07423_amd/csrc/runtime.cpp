@@ -680,7 +680,6 @@ void build(snn_network *net) {
   }
 
   if (index.col16 && !one_each) fill_tile_offsets(net, index);
-  net->windows = choose_windows(net);
   check(hipEventRecord(ev[5], s), "hipEventRecord");
 
   // neuron state, FIFO, raster, control block
@@ -756,6 +755,8 @@ void build(snn_network *net) {
   const float lo = (float)net->prm.v0_lo_mV;
   const float span = (float)(net->prm.v0_hi_mV - net->prm.v0_lo_mV);
   check(snn::launch_init_neurons(net->v, net->ref, n, net->key0, net->key1, lo, span, s), "init neurons");
+  // after everything the network cannot do without: the windows' buffers take what is left
+  net->windows = choose_windows(net);
   check(hipStreamSynchronize(s), "sync after build");
   check(hipEventElapsedTime(&net->gen_rows_ms, ev[0], ev[1]), "hipEventElapsedTime");
   check(hipEventElapsedTime(&net->gen_fill_ms, ev[2], ev[3]), "hipEventElapsedTime");

@@ -316,7 +316,9 @@ typedef struct {
  * 768 targets (ranges of up to 32) x 512/1024-thread workgroups x 1, 2 and 3
  * workgroups per CU (the tiled ones for networks of at least 1,024 neurons), each on
  * the spikes of the network's latest window (taken from its raster), `reps` launches
- * each, on scratch queues and accumulators; keep the fastest and return it.  The
+ * each, on scratch queues and accumulators; keep the fastest for the launches and return it.
+ * A network that snn_run advances by a route of its own (snn_get_route), which delivers inside
+ * its own kernels, keeps that route: only snn_set_delivery with a caller's choice ends it.  The
  * simulation state (weights and traces included) is unchanged.  SNN_E_STATE if fewer
  * than `window` steps have run, or for a network with lazy plasticity. */
 snn_status snn_autotune_delivery(snn_network *net, uint32_t reps, snn_delivery_tuning *chosen);

@@ -648,6 +648,7 @@ void build(snn_network *net) {
     check(hipMemsetAsync(net->w_q16 + net->nnz, 0, pad_bytes, s), "clear w padding");
   }
   choose_delivery(net);
+  net->delivery_chosen = net->prm.delivery != SNN_DELIVERY_AUTO || net->prm.tiles || net->prm.block || net->prm.grid;
   net->solo = choose_solo(net);
   snn::RowIndex index{};
   if (net->delivery == SNN_DELIVERY_TILED) index = alloc_tile_offsets(net);
@@ -1052,9 +1053,7 @@ size_t solo_need(const snn_network *net) { return (size_t)net->delay * net->n * 
 // of background, 32,000 neurons and 22,500 events a step took 7.8 against 11.4 us, but
 // 40,000 neurons and 80,000 events 14.7 against 11.6.
 bool choose_solo(const snn_network *net) {
-  if (net->plastic || net->owner || net->prm.delivery != SNN_DELIVERY_AUTO || net->prm.window || net->prm.tiles ||
-      net->prm.block || net->prm.grid)
-    return false;
+  if (net->plastic || net->owner || net->delivery_chosen || net->prm.window) return false;
   if (net->n > snn::kSoloMaxNeurons || net->n_inbuf != net->delay || drive_thresholds(net)) return false;
   if (solo_need(net) + snn::kBatchStaticLds > net->lds_limit) return false;
   const double events = (double)net->nnz * 15.0 * net->prm.dt_ms * 1e-3;
@@ -1102,8 +1101,8 @@ uint32_t window_range(const snn_network *net) {
 // stay with the launches (200,000 neurons with 500 synapses each, 1.3 per range: 30.8 against
 // 43.5), and so does a network whose memory has no room for the windows' index.
 bool choose_windows(snn_network *net) {
-  if (!net->plastic || net->lazy || net->owner || net->delay < 2 || net->n == 0 ||
-      net->prm.delivery != SNN_DELIVERY_AUTO || net->prm.window || net->prm.tiles || net->prm.block || net->prm.grid)
+  if (!net->plastic || net->lazy || net->owner || net->delay < 2 || net->n == 0 || net->delivery_chosen ||
+      net->prm.window)
     return false;
   const uint32_t range = window_range(net), ranges = (net->n + range - 1) / range;
   if ((double)net->nnz < 0.5 * (double)ranges * net->n) return false;
@@ -1391,8 +1390,10 @@ void dev_free(snn_network *net, void *p) {
 // variant filled it).  The new configuration is resolved and its tile index built before
 // anything of the old one is released; if any of that fails (an impossible block or
 // tiling, device memory, a launch), every field and buffer of the old configuration is
-// restored, so the network keeps running as before.
-void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t block, uint32_t grid) {
+// restored, so the network keeps running as before.  Without `by_caller` the launches' delivery
+// changes and nothing else: a route of its own that snn_run takes stays.
+void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t block, uint32_t grid,
+                  bool by_caller) {
   if (net->lazy) fail(SNN_E_STATE, "lazy plasticity delivers inside its own kernel; there is no variant to choose");
   if (delivery > SNN_DELIVERY_TILED) fail(SNN_E_INVALID, "unknown delivery variant");
   check(hipStreamSynchronize(net->stream), "sync");
@@ -1400,11 +1401,11 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     uint32_t p_delivery, p_tiles, p_block, p_grid, delivery, block, tiles, tile_size, grid;
     void *tile_off;
     uint16_t *col16;
-    bool tile_off16, solo, windows;
+    bool tile_off16, solo, windows, chosen;
   };
   const Saved old{net->prm.delivery, net->prm.tiles, net->prm.block, net->prm.grid, net->delivery,
                   net->block,        net->tiles,     net->tile_size, net->grid,     net->tile_off,
-                  net->col16,        net->tile_off16, net->solo,     net->windows};
+                  net->col16,        net->tile_off16, net->solo,     net->windows,   net->delivery_chosen};
   try {
     net->prm.delivery = delivery;
     net->prm.tiles = tiles;
@@ -1412,7 +1413,6 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->prm.grid = grid;
     net->delivery = delivery;
     choose_delivery(net);
-    net->solo = choose_solo(net);
     if (net->delivery == SNN_DELIVERY_TILED) {
       net->tile_off = nullptr;  // a fresh index; the old one stays valid until this succeeds
       fill_tile_offsets(net, alloc_tile_offsets(net));  // reuses col16 when it exists (any tiling's)
@@ -1420,8 +1420,12 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     } else {
       net->tile_off = nullptr;
     }
-    net->windows = choose_windows(net);
-    check(hipStreamSynchronize(net->stream), "sync after the new configuration");
+    if (by_caller) {
+      net->delivery_chosen = delivery != SNN_DELIVERY_AUTO || tiles || block || grid;
+      net->solo = choose_solo(net);
+      net->windows = choose_windows(net);
+      check(hipStreamSynchronize(net->stream), "sync after the new configuration");
+    }
   } catch (...) {
     (void)hipStreamSynchronize(net->stream);  // no index launch may still write a block freed here
     if (net->tile_off && net->tile_off != old.tile_off) dev_free(net, net->tile_off);
@@ -1437,6 +1441,7 @@ void set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles, uint32_t 
     net->grid = old.grid;
     net->solo = old.solo;
     net->windows = old.windows;
+    net->delivery_chosen = old.chosen;
     net->tile_off = old.tile_off;
     net->col16 = old.col16;
     net->tile_off16 = old.tile_off16;
@@ -1658,7 +1663,10 @@ double time_delivery_static(snn_network *net, const uint32_t *ids, uint32_t n_id
 }
 
 // Times every candidate delivery configuration on the spikes of the latest window (read
-// from the raster ring) and keeps the fastest.
+// from the raster ring) and keeps the fastest for the launches.  The tuner's choice is not the
+// caller's: a network that snn_run advances by a route of its own (which delivers inside its own
+// kernels) keeps it.  (With the choice taken for the caller's, a tuned 4,000-neuron network went
+// from 1.4 to 8 us per step and a plastic one of 10,000 from 3 to 16.)
 snn_delivery_tuning autotune_delivery(snn_network *net, uint32_t reps) {
   if (net->lazy) fail(SNN_E_STATE, "lazy plasticity delivers inside its own kernel; there is no variant to tune");
   const uint32_t W = net->window;
@@ -1689,31 +1697,36 @@ snn_delivery_tuning autotune_delivery(snn_network *net, uint32_t reps) {
         for (uint32_t grid : {net->cu_count, 2 * net->cu_count, 3 * net->cu_count})
           cands.push_back({SNN_DELIVERY_TILED, std::max(1u, (net->n + tile - 1) / tile), block, grid});
   }
-  const Cand keep{net->delivery, net->prm.tiles, net->prm.block, net->prm.grid};
+  const Cand keep{net->prm.delivery, net->prm.tiles, net->prm.block, net->prm.grid};
   snn_delivery_tuning best{};
   best.ms_per_launch = 1e300;
-  for (const Cand &c : cands) {
+  try {
+    for (const Cand &c : cands) {
+      try {
+        set_delivery(net, c.delivery, c.tiles, c.block, c.grid, false);
+      } catch (const Failure &) {
+        continue;  // e.g. a tile larger than the LDS allows
+      }
+      uint64_t ev = 0;
+      const double ms = time_delivery(net, per_step, reps, &ev);
+      if (ms < best.ms_per_launch) {
+        best.ms_per_launch = ms;
+        best.delivery = net->delivery;
+        best.tiles = net->tiles;
+        best.block = net->block;
+        best.grid = net->grid;
+        best.events_per_launch = ev;
+      }
+    }
+    if (best.ms_per_launch == 1e300) fail(SNN_E_STATE, "no delivery configuration could be timed");
+    set_delivery(net, best.delivery, best.tiles, best.block, best.grid, false);
+  } catch (...) {
     try {
-      set_delivery(net, c.delivery, c.tiles, c.block, c.grid);
-    } catch (const Failure &) {
-      continue;  // e.g. a tile larger than the LDS allows
+      set_delivery(net, keep.delivery, keep.tiles, keep.block, keep.grid, false);
+    } catch (...) {
     }
-    uint64_t ev = 0;
-    const double ms = time_delivery(net, per_step, reps, &ev);
-    if (ms < best.ms_per_launch) {
-      best.ms_per_launch = ms;
-      best.delivery = net->delivery;
-      best.tiles = net->tiles;
-      best.block = net->block;
-      best.grid = net->grid;
-      best.events_per_launch = ev;
-    }
+    throw;
   }
-  if (best.ms_per_launch == 1e300) {
-    set_delivery(net, keep.delivery, keep.tiles, keep.block, keep.grid);
-    fail(SNN_E_STATE, "no delivery configuration could be timed");
-  }
-  set_delivery(net, best.delivery, best.tiles, best.block, best.grid);
   return best;
 }
 
@@ -2594,7 +2607,7 @@ snn_status snn_set_delivery(snn_network *net, uint32_t delivery, uint32_t tiles,
   return guarded([&] {
     if (!net) fail(SNN_E_INVALID, "null network");
     refuse_member(net);
-    set_delivery(net, delivery, tiles, block, grid);
+    set_delivery(net, delivery, tiles, block, grid, true);
   });
 }
 

@@ -545,6 +545,7 @@ struct snn_network {
   snn_batch *owner = nullptr;  // set for the members of a batch
   uint64_t device_bytes = 0;
 
+  bool delivery_chosen = false;  // by the caller, with the parameters or snn_set_delivery
   bool solo = false;         // snn_run steps it by the persistent one-workgroup kernel
   uint32_t lds_limit = 0;    // largest workgroup LDS
 

@@ -272,7 +272,7 @@ class Network:
 
     def autotune_delivery(self, reps=5):
         """Time the delivery configurations on the latest window's spikes; keep the
-        fastest (returned as a dict)."""
+        fastest (returned as a dict) for the launches.  The route of run() stays."""
         t = L.DeliveryTuning()
         L.check(self._lib.snn_autotune_delivery(self._h, reps, C.byref(t)))
         return {"delivery": L.DELIVERY_NAME.get(t.delivery, "?"), "tiles": t.tiles, "block": t.block,

@@ -1043,15 +1043,14 @@ snn::LdsPlan lds_plan(size_t need, uint32_t n, size_t limit) {
 
 size_t solo_need(const snn_network *net) { return (size_t)net->delay * net->n * 4; }
 
-// Whether snn_run steps the network by the persistent kernel: a small static network without
+// Whether snn_run may step the network by the persistent kernel: a small static network without
 // drive, with nothing about its delivery chosen by the caller.  A step of the pipeline costs
 // two launches per window of `delay` steps, whatever the size: 6.6-8.9 us with the atomic
 // delivery (1,000-40,000 neurons) and 9.6-11.2 us with the tiled one.  A persistent step
 // costs about 0.9 us, 0.105 us per 1,000 neurons and 1 us per 8,200 synaptic events: 0.9 us
 // at 1,000 neurons, 1.4 at 4,000, 1.9 at 8,000, 3.1 at 16,000, 5.0 at 32,000, against 6.6,
-// 7.9, 8.3, 8.6 and 10.9 us (delay 1).  The rule takes 15 Hz for the unknown rate: at 20 mV
-// of background, 32,000 neurons and 22,500 events a step took 7.8 against 11.4 us, but
-// 40,000 neurons and 80,000 events 14.7 against 11.6.
+// 7.9, 8.3, 8.6 and 10.9 us (delay 1).  The rule takes 15 Hz for the unknown rate; whether the
+// network takes the kernel at the rate it turns out to have is decided below (solo_now).
 bool choose_solo(const snn_network *net) {
   if (net->plastic || net->owner || net->delivery_chosen || net->prm.window) return false;
   if (net->n > snn::kSoloMaxNeurons || net->n_inbuf != net->delay || drive_thresholds(net)) return false;
@@ -1061,15 +1060,91 @@ bool choose_solo(const snn_network *net) {
   return step_us * net->delay <= (net->delivery == SNN_DELIVERY_TILED ? 9.6 : 6.6);
 }
 
+// The rule above guesses the rate.  What follows corrects it by the spikes of the network's latest
+// steps, which calls that wait for the device anyway find out (note_spikes, measure_spikes).
+//
+// us per step of the persistent kernel and of the launches (one update and one delivery per
+// window) at `spikes` spikes per step.  A spike costs one workgroup 0.02 us and 0.13 ns per synapse; measured, with
+// the estimate behind it: 8,000 neurons (800 synapses each) at 56 spikes 7.9 (8.7), at 88 11.0
+// (12.7); 16,000 (320) at 100 9.0 (8.7), at 191 15.3 (14.3); 32,000 (640) at 8 5.0 (5.1), at 128
+// 17.2 (17.5), at 383 39.5 (43.8); delay of one step.  The launches spread it over the device: 8,000 neurons 10.1 and
+// 11.8 (9.6, 10.2), 16,000 9.3 and 10.5 (9.3, 10.2), 32,000 (tiled) 10.9, 12.3 and 13.9 (10.5,
+// 11.5, 13.7).
+double degree_of(const snn_network *net) { return net->n ? (double)net->nnz / net->n : 0.0; }
+double solo_us(const snn_network *net, double spikes) {
+  return 0.9 + 0.105e-3 * net->n + spikes * (0.02 + 0.13e-3 * degree_of(net));
+}
+double launches_us(const snn_network *net, double spikes) {
+  const double events = spikes * degree_of(net) * net->window;
+  const double window = net->delivery == SNN_DELIVERY_TILED
+                            ? 10.4 + 0.0135e-3 * events
+                            : std::min(7.6 + 0.04e-3 * net->n, 6.4 + 0.3e-3 * net->n) + 0.033e-3 * events;
+  return window / net->window;
+}
+
+// The rate taken where none has been measured: population averages in use lie below it.
+constexpr double kHighHz = 100.0;
+double spikes_at(const snn_network *net, double hz) { return net->n * hz * net->prm.dt_ms * 1e-3; }
+
+// Whether a rate in use makes the launches the faster way, so that the rate has to be known.
+// (Networks of up to some 8,000 neurons with rows of 80 are persistent at any such rate.)
+bool rate_matters(const snn_network *net) {
+  return net->solo && solo_us(net, spikes_at(net, kHighHz)) > launches_us(net, spikes_at(net, kHighHz));
+}
+
+// Spikes per step that the route is chosen for.
+double expected_spikes(const snn_network *net) {
+  return net->spikes_per_step >= 0.0 ? net->spikes_per_step : spikes_at(net, kHighHz);
+}
+
+// Whether snn_run takes the persistent kernel now.
+bool solo_now(const snn_network *net) {
+  const double spikes = expected_spikes(net);
+  return net->solo && (!rate_matters(net) || solo_us(net, spikes) <= launches_us(net, spikes));
+}
+
+// Steps a rate is taken over.
+constexpr uint64_t kRateSteps = 64, kRateStepsMost = 256;
+
+// `count` spikes in the latest `steps` steps, known from a download of them: downloads of few
+// steps are added up.
+void note_spikes(snn_network *net, uint64_t count, uint64_t steps) {
+  if (!rate_matters(net)) return;
+  net->noted_spikes += (double)count;
+  net->noted_steps += steps;
+  if (net->noted_steps < kRateSteps) return;
+  net->spikes_per_step = net->noted_spikes / (double)net->noted_steps;
+  net->rate_at = net->t_host;
+  net->noted_spikes = 0.0;
+  net->noted_steps = 0;
+}
+
+uint64_t count_spikes(snn_network *net, uint64_t t0, uint64_t t1);
+
+// Counts the spikes of the latest steps where enough have passed since the last count, in a call
+// that waits for the device: two launches and a wait, 25 us.
+void measure_spikes(snn_network *net) {
+  if (!rate_matters(net) || net->t_host - net->rate_at < kRateSteps) return;
+  const uint64_t steps = std::min<uint64_t>({net->t_host - net->rate_at, net->raster_cap, kRateStepsMost});
+  net->spikes_per_step = (double)count_spikes(net, net->t_host - steps, net->t_host) / (double)steps;
+  net->rate_at = net->t_host;
+  net->noted_spikes = 0.0;
+  net->noted_steps = 0;
+}
+
 // Steps per persistent launch: long enough to amortise the launch and the state's way in
-// and out, short enough that a launch stays well below a tenth of a second.
+// and out, and of a network by itself no more than an estimated tenth of a second.
 constexpr uint32_t kMaxChunk = 1u << 14;
+uint64_t solo_chunk(const snn_network *net) {
+  return std::min<uint64_t>(kMaxChunk, std::max<uint64_t>(256, (uint64_t)(1e5 / solo_us(net, expected_spikes(net)))));
+}
 
 void run_solo(snn_network *net, uint64_t n_steps) {
   const snn::BatchNet d = batch_net(net);
   const snn::LdsPlan lds = lds_plan(solo_need(net), net->n, net->lds_limit - snn::kBatchStaticLds);
+  const uint64_t most = solo_chunk(net);
   while (n_steps > 0) {
-    const uint32_t chunk = (uint32_t)std::min<uint64_t>(n_steps, kMaxChunk);
+    const uint32_t chunk = (uint32_t)std::min<uint64_t>(n_steps, most);
     check(snn::launch_solo(d, chunk, snn::kBatchCommit | snn::kBatchWriteRaster | snn::kBatchQueues, lds,
                            net->stream),
           "persistent launch");
@@ -1252,7 +1327,7 @@ void ensure_graph(snn_network *net) {
 // the caller still need).
 uint32_t route(const snn_network *net) {
   if (net->profiling) return SNN_ROUTE_LAUNCHES;
-  return net->solo ? SNN_ROUTE_PERSISTENT : net->windows ? SNN_ROUTE_WINDOWS : SNN_ROUTE_LAUNCHES;
+  return solo_now(net) ? SNN_ROUTE_PERSISTENT : net->windows ? SNN_ROUTE_WINDOWS : SNN_ROUTE_LAUNCHES;
 }
 
 void run(snn_network *net, uint64_t n_steps) {
@@ -1325,19 +1400,11 @@ void copy_raster_rows(snn_network *net, uint64_t t0, uint64_t t1, uint64_t *out)
 }
 
 
-// The spikes of steps [t0, t1) as sorted pairs in the caller's arrays, their number in
-// *n_spikes.  Device kernels find the pairs and write them into pinned staging, in pieces if
-// they do not fit one block; the caller's arrays are written only once the count is known
-// to fit them.
-void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps, uint32_t *ids,
-                    uint64_t capacity, uint64_t *n_spikes) {
-  *n_spikes = 0;
-  if (t0 == t1) return;
-  constexpr size_t kHead = 256;  // the count, on a line of its own
-  const size_t pair = 2 * sizeof(uint32_t);
-  // (the clamp keeps the product in range for any capacity)
-  Stage stage(kHead + std::min<uint64_t>(capacity, kStageMaxBytes / pair) * pair);
-  const uint64_t piece = (stage.bytes() - kHead) / pair;
+// The download kernels' arguments for steps [t0, t1) (not empty), with `piece` pairs of room in
+// the staging behind the count.
+constexpr size_t kStageHead = 256;  // the count, on a line of its own
+constexpr size_t kPairBytes = 2 * sizeof(uint32_t);
+snn::RasterArgs raster_args(snn_network *net, uint64_t t0, uint64_t t1, const Stage &stage, uint64_t piece) {
   snn::RasterArgs a{};
   a.raster = net->raster;
   a.ring_words = (uint64_t)net->raster_cap * net->words;
@@ -1348,17 +1415,45 @@ void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps,
   a.scratch = net->raster_scratch;
   a.words = net->words;
   a.count = reinterpret_cast<uint64_t *>(stage.data());
-  a.steps = reinterpret_cast<uint32_t *>(stage.data() + kHead);
+  a.steps = reinterpret_cast<uint32_t *>(stage.data() + kStageHead);
   a.ids = a.steps + piece;
+  return a;
+}
+
+struct Drained {  // a staging block goes back only after nothing writes to it any more
+  hipStream_t s;
+  ~Drained() { (void)hipStreamSynchronize(s); }
+};
+
+// Number of spikes of steps [t0, t1), which the raster holds.
+uint64_t count_spikes(snn_network *net, uint64_t t0, uint64_t t1) {
+  Stage stage(kStageHead);
+  Drained drained{net->stream};
+  const snn::RasterArgs a = raster_args(net, t0, t1, stage, 0);
+  check(snn::launch_raster_pairs(a, net->stream), "raster count");
+  sync(net);
+  return *a.count;
+}
+
+// The spikes of steps [t0, t1) as sorted pairs in the caller's arrays, their number in
+// *n_spikes.  Device kernels find the pairs and write them into pinned staging, in pieces if
+// they do not fit one block; the caller's arrays are written only once the count is known
+// to fit them.
+void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps, uint32_t *ids,
+                    uint64_t capacity, uint64_t *n_spikes) {
+  *n_spikes = 0;
+  if (t0 == t1) return;
+  // (the clamp keeps the product in range for any capacity)
+  Stage stage(kStageHead + std::min<uint64_t>(capacity, kStageMaxBytes / kPairBytes) * kPairBytes);
+  Drained drained{net->stream};
+  const uint64_t piece = (stage.bytes() - kStageHead) / kPairBytes;
+  snn::RasterArgs a = raster_args(net, t0, t1, stage, piece);
   a.out_cap = steps && ids ? std::min(capacity, piece) : 0;
-  struct Drained {  // the block goes back only after nothing writes to it any more
-    hipStream_t s;
-    ~Drained() { (void)hipStreamSynchronize(s); }
-  } drained{net->stream};
   check(snn::launch_raster_pairs(a, net->stream), "raster pairs");
   sync(net);
   const uint64_t count = *a.count;
   *n_spikes = count;
+  if (t1 == net->t_host && t1 > net->rate_at) note_spikes(net, count, t1 - t0);
   if (count > capacity) fail(SNN_E_OVERFLOW, "raster holds " + std::to_string(count) + " spikes");
   if (count && (!steps || !ids)) fail(SNN_E_INVALID, "null output arrays");
   for (uint64_t lo = 0; lo < count; lo += piece) {
@@ -2363,6 +2458,7 @@ snn_status snn_sync(snn_network *net) {
   return guarded([&] {
     if (!net) fail(SNN_E_INVALID, "null network");
     sync(net);
+    measure_spikes(net);
   });
 }
 
@@ -2419,6 +2515,7 @@ snn_status snn_get_info(snn_network *net, snn_info *info) {
     r.plasticity = net->lazy ? SNN_PLASTICITY_LAZY : SNN_PLASTICITY_EAGER;
     if (c.t != net->t_host) fail(SNN_E_STATE, "device step counter disagrees with the host");
     *info = r;
+    measure_spikes(net);
   });
 }
 

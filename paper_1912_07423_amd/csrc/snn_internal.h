@@ -546,7 +546,11 @@ struct snn_network {
   uint64_t device_bytes = 0;
 
   bool delivery_chosen = false;  // by the caller, with the parameters or snn_set_delivery
-  bool solo = false;         // snn_run steps it by the persistent one-workgroup kernel
+  bool solo = false;         // snn_run may step it by the persistent one-workgroup kernel
+  double spikes_per_step = -1.0;  // of its latest steps, where the route depends on it (< 0: not known)
+  uint64_t rate_at = 0;           // the step at which that was found
+  double noted_spikes = 0.0;      // of downloads since then, and their steps
+  uint64_t noted_steps = 0;
   uint32_t lds_limit = 0;    // largest workgroup LDS
 
   // graph of a fixed chunk of windows

@@ -40,15 +40,21 @@ __device__ __forceinline__ float surrogate(float z, float slope, bool smooth) {
   return smooth ? 0.5f * slope * g : g;
 }
 
+__device__ __forceinline__ bool finite_f32(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
+
 // x [B][T][C] -> xt [T][C][64]; lanes >= B hold zeros.  A workgroup per (step t, block of
 // 64 inputs) reads the 64 batch rows of its block (256 bytes each, coalesced) into LDS and
 // writes the block transposed; a wavefront per input c then also writes that input's
 // batch mask xbits[c][t] (bit b: x != 0) and sets *flag if some value is neither 0 nor 1
-// (k_bits' rule).
+// (k_bits' rule).  Of n_out readout weights (w_out), one that is not finite sets flag[2].
 __global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, uint64_t *xbits, uint32_t *flag,
-                                                     uint32_t B, uint32_t T, uint32_t C) {
+                                                     uint32_t B, uint32_t T, uint32_t C, const float *w_out,
+                                                     uint32_t n_out) {
   __shared__ float tile[64][65];
   const uint32_t t = blockIdx.y, c0 = blockIdx.x * 64u;
+  const uint32_t n_thr = gridDim.x * gridDim.y * 256u;
+  for (uint32_t e = (blockIdx.y * gridDim.x + blockIdx.x) * 256u + threadIdx.x; e < n_out; e += n_thr)
+    if (!finite_f32(w_out[e])) atomicOr(flag + 2, 1u);
   const uint32_t l = threadIdx.x % 64u, r = threadIdx.x / 64u;
   for (uint32_t b = r; b < 64u; b += 4u)
     tile[b][l] = b < B && c0 + l < C ? x[((uint64_t)b * T + t) * C + c0 + l] : 0.0f;
@@ -470,7 +476,9 @@ __device__ __forceinline__ size_t row_index(const BpttArgs &a, uint32_t t, uint3
 // recurrent weights, and the target-major pairs of the many-spikes form.
 __global__ void k_scatter_weights(BpttArgs a) {
   const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < 2) a.flags[e] = 0;  // k_transpose_x, next, sets flags[0] for inputs other than 0 and 1
+  // k_transpose_x, next, sets flags[0] for inputs other than 0 and 1, flags[2] for readout
+  // weights that are not finite
+  if (e < 3) a.flags[e] = 0;
   if (e < a.nnz_in) a.dense_in[a.in_pos[e]] = a.w_in[e];
   if (e < a.nnz_rec) {
     const float w = a.w_rec[e];
@@ -672,6 +680,7 @@ __global__ __launch_bounds__(256) void k_spike_masks(BpttArgs a) {
   __shared__ unsigned long long mask[64][kMaskBlock];
   const uint32_t w = blockIdx.x, t0 = blockIdx.y * kMaskBlock, tid = threadIdx.x;
   const uint32_t tl = tid % kMaskBlock, t = t0 + tl;
+  if (w == 0 && t0 == 0 && tid == 0) a.flags[3] = 0;  // k_lam_u sets it for adjoints that are not finite
   uint64_t word[64 * kMaskBlock / 256];  // (step tl, batch elements tid / 16 + 16 q)
 #pragma unroll
   for (uint32_t q = 0; q < 64 * kMaskBlock / 256; ++q) {
@@ -692,7 +701,9 @@ __global__ __launch_bounds__(256) void k_spike_masks(BpttArgs a) {
 }
 
 // Readout drive of every (batch element, step) from its spikes: ro[b][t][o] = sum of the
-// spiking neurons' readout weights, ascending; a wavefront per (b, t), lanes = readouts.
+// spiking neurons' readout weights, ascending; a wavefront per (b, t), lanes = readouts.  That is
+// the defined sum of s w over all neurons while the weights are finite; with one that is not,
+// every term is formed (0 w is then no zero).
 __global__ __launch_bounds__(256) void k_readout_events(BpttArgs a, float *ro) {
   const uint32_t bt = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   if (bt >= a.B * a.T) return;
@@ -703,6 +714,13 @@ __global__ __launch_bounds__(256) void k_readout_events(BpttArgs a, float *ro) {
     float acc = 0.0f;
     uint64_t any = __ballot(mine != 0), word = 0;
     uint32_t at = 0;
+    if (a.flags[2]) {
+      any = 0;
+      for (uint32_t i = 0; i < a.H; ++i) {
+        const float on = (lane_read64(mine, i >> 6) >> (i & 63u)) & 1u ? 1.0f : 0.0f;
+        acc = acc + on * a.w_out[(size_t)i * a.O + o];
+      }
+    }
     while (any) {
       float w[4];
       uint32_t n = 0;
@@ -920,10 +938,13 @@ __global__ void k_lam_u(BpttArgs a, const float *g_loss) {
   const float g = b < a.B ? a.dm[(size_t)b * a.O + o] * scale : 0.0f;
   const int32_t tm = b < a.B ? a.tmax[(size_t)b * a.O + o] : -1;
   float nxt = 0.0f;
+  bool finite = true;
   for (int32_t t = (int32_t)a.T - 1; t >= 0; --t) {
     nxt = (t == tm ? g : 0.0f) + a.beta_out * nxt;
     a.lamu[((size_t)t * a.O + o) * 64 + b] = nxt;
+    finite = finite && finite_f32(nxt);
   }
+  if (!finite) atomicOr(a.flags + 3, 1u);
 }
 
 // Readout part of the spike adjoint of every step, the first terms of the sum that
@@ -1503,7 +1524,8 @@ __global__ __launch_bounds__(256) void k_grad_out(BpttArgs a) {
 
 // The same from the spike masks: a wavefront per (neuron, block of kOutBlock readouts) visits
 // the steps at which the neuron spikes in some batch element and adds the readout adjoints of
-// the lanes (batch elements) that spike.
+// the lanes (batch elements) that spike.  With an adjoint that is not finite it visits every step
+// and multiplies, as the sum is defined.
 constexpr int kOutBlock = 4;
 constexpr int kOutSteps = 8;
 __global__ __launch_bounds__(256) void k_grad_out_events(BpttArgs a) {
@@ -1517,6 +1539,15 @@ __global__ __launch_bounds__(256) void k_grad_out_events(BpttArgs a) {
     const uint64_t mine = t0 + lane < a.T ? a.sbits[(size_t)i * a.T + t0 + lane] : 0ull;
     // kOutSteps steps requested together (the last one again where fewer are left, unused)
     uint64_t any = __ballot(mine != 0);
+    if (a.flags[3]) {
+      any = 0;
+      for (uint32_t k = 0; k < kWave && t0 + k < a.T; ++k) {
+        const float on = (lane_read64(mine, k) >> lane) & 1u ? 1.0f : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kOutBlock; ++q)
+          acc[q] += on * a.lamu[((size_t)(t0 + k) * a.O + o0 + std::min<uint32_t>(q, no - 1)) * 64 + lane];
+      }
+    }
     while (any) {
       float l[kOutSteps][kOutBlock];
       uint64_t on[kOutSteps];
@@ -1595,7 +1626,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t 
     const uint64_t nnz = std::max<uint64_t>(std::max(a.nnz_in, a.nnz_rec), 2);
     hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                       a.T, a.C);
+                       a.T, a.C, a.w_out, a.H * a.O);
     hipLaunchKernelGGL(k_input_rows, dim3(blocks_for((uint64_t)a.B * a.T, 4), blocks_for(a.Hp / 256, kInputBlocks)),
                        dim3(256), 0, s, a, x);
     hipLaunchKernelGGL(k_input_current_values, dim3(std::min<uint32_t>(blocks_for((uint64_t)a.T * a.H, 4), kValuesGrid)),
@@ -1614,7 +1645,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t 
   // pass of a smooth-mode plan
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
   hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                     a.T, a.C);
+                     a.T, a.C, (const float *)nullptr, 0u);
   const hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   return e != hipSuccess ? e : hipGetLastError();
 }

@@ -2299,7 +2299,7 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   }
   build_seq(p, rec_ptr, rec_col);
   check(snn::bptt_prepare(a), "bptt prepare");
-  a.flags = dev_array<uint32_t>(pool, 2);
+  a.flags = dev_array<uint32_t>(pool, 4);
   a.w_in_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_in));
   a.w_rec_t = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));
   if (!a.S) a.w_rec_c = dev_array<float>(pool, std::max<uint64_t>(1, nnz_rec));

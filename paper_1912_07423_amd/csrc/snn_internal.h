@@ -350,7 +350,8 @@ struct BpttArgs {
   const uint32_t *ell_edge;    // [H][ell_w] CSR edge index (padding: 0xFFFFFFFF)
   const uint32_t *ell_len;     // [H] in-degree
   float *ell_wt;               // [H][ell_w] weights gathered into that order (padding: 0)
-  uint32_t *flags;             // [2]: a value of x / s is neither 0 nor 1 (masks not used)
+  uint32_t *flags;             // [4]: a value of x / s is neither 0 nor 1 (masks not used); event-driven
+                               // form: a readout weight / adjoint is not finite (no term is left out)
   float *xt, *s, *vck, *vtmp, *vseg, *ro, *lamu, *lamv, *lam_carry, *m, *dm;
   int32_t *tmax;
 };

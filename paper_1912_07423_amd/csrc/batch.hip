@@ -42,8 +42,16 @@ constexpr int groups_in_flight(int block, int per, bool drive) {
   return block == 1024 ? (per >= 16 && drive ? 1 : 2) : 4;
 }
 
-// Words whose inputs are read together before their neurons are advanced.
-constexpr int update_chunk(int per) { return per % 5 == 0 ? 5 : 4; }
+// Words whose inputs are read together before their neurons are advanced.  A wavefront takes
+// whole chunks of words.  Without a drive a word is little work and chunks of four or five cost
+// nothing; with one it is a Philox block and a threshold search, and a chunk that leaves
+// wavefronts of a small network without a word is a loss: in workgroups for up to 4,096 neurons a
+// chunk is one word, up to 8,192 two.  256 driven networks of 300 neurons: 4.9 us a step with
+// chunks of four, 2.6 with one; 300 of 1,000 neurons 10.8 and 6.7; 300 of 5,000 28.7 and 26.7
+// (24.9 with one, which costs 300 of 8,000 2 %); 300 of 20,000 96.4, and 99.8 with one.
+constexpr int update_chunk(int block, int per, bool drive) {
+  return drive && block * per <= 4096 ? 1 : drive && block * per <= 8192 ? 2 : per % 5 == 0 ? 5 : 4;
+}
 
 // The value itself, as one that the compiler knows nothing about (uniform, per lane).
 __device__ __forceinline__ uint32_t opaque(uint32_t x) {
@@ -80,7 +88,7 @@ __device__ __forceinline__ void step_network(const BatchNet &d, uint32_t steps, 
   __shared__ unsigned long long s_count[2];
 
   constexpr int kWaves = kBlock / kWave;
-  constexpr int kChunk = update_chunk(kPer);
+  constexpr int kChunk = update_chunk(kBlock, kPer, kDrive);
   constexpr int kGroupsInFlight = groups_in_flight(kBlock, kPer, kDrive);
   // a wavefront's words are stepped in spans of at most 64: a bit of `fired` and a raster
   // lane per word

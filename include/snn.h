@@ -425,8 +425,10 @@ void snn_batch_destroy(snn_batch *b);
  * the exact derivative with the reset term (smooth = 1, for finite-difference checks).
  * The forward keeps every step's s and the membrane state at the end of every
  * `checkpoint` steps; the backward recomputes each segment's membranes from its
- * checkpoint.  In spiking mode with at most 2,048 hidden neurons it keeps the membranes of
- * every step instead (the spikes then as bits), and the backward recomputes nothing.  The current into neuron j sums its in-edges in ascending source order,
+ * checkpoint.  In spiking mode with at most 2,048 hidden neurons, and at most 2^24 inputs times
+ * hidden neurons (the latter rounded up to a multiple of 256), it keeps the membranes of every
+ * step instead (the spikes then as bits), and the backward recomputes nothing.
+ * The current into neuron j sums its in-edges in ascending source order,
  * input projection first, one term at a time; the readout sums ascending; the maximum
  * over time is taken at its first step. */
 typedef struct snn_bptt snn_bptt;
@@ -456,6 +458,13 @@ snn_status snn_bptt_create(const snn_bptt_desc *desc, const uint64_t *in_row_ptr
  * (NULL: the plan's stream).  The plan keeps the trajectory for the next backward. */
 snn_status snn_bptt_forward(snn_bptt *p, const float *x, const float *w_in, const float *w_rec,
                             const float *w_out, const int32_t *labels, float *loss, void *stream);
+
+/* How the next forward pass takes its hidden steps: SNN_ROUTE_PERSISTENT, one launch that works
+ * on the active inputs and spikes (spiking plans within the limits above), or SNN_ROUTE_LAUNCHES,
+ * a launch per step.  Such a plan takes the way that is faster at the activity of the latest pass
+ * whose end the host has seen, the first at first and on a stream that is being captured unless
+ * the plan is eager; the results are the same. */
+snn_status snn_bptt_get_route(snn_bptt *p, uint32_t *route);
 
 /* Backward pass of the latest forward pass (same weights): writes dloss/dw_in [nnz_in],
  * dloss/dw_rec [nnz_rec] and dloss/dw_out [n_hidden][n_out] (device), each scaled by

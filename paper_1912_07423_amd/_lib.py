@@ -157,6 +157,7 @@ SIGNATURES = {
                                     C.POINTER(C.c_void_p)]),
     "snn_bptt_forward": (C.c_int32, [C.c_void_p] + [C.c_void_p] * 6 + [C.c_void_p]),
     "snn_bptt_backward": (C.c_int32, [C.c_void_p] + [C.c_void_p] * 7 + [C.c_void_p]),
+    "snn_bptt_get_route": (C.c_int32, [C.c_void_p, C.POINTER(C.c_uint32)]),
     "snn_bptt_get_trace": (C.c_int32, [C.c_void_p] + [C.c_void_p] * 4 + [C.c_void_p]),
     "snn_bptt_destroy": (None, [C.c_void_p]),
 }

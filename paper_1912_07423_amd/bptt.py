@@ -136,6 +136,12 @@ class RecurrentLIF:
                                             self._stream()))
         return g_in, g_rec, g_out
 
+    def route(self):
+        """How the next forward pass takes its hidden steps: "persistent" or "launches"."""
+        r = C.c_uint32()
+        L.check(self._lib.snn_bptt_get_route(self._h, C.byref(r)))
+        return L.ROUTE_NAME[r.value]
+
     def trace(self):
         """Host copies of the latest forward pass: spikes [T, B, H], membrane
         checkpoints [n_seg, B, H], readout maxima and argmax steps [B, O]."""

@@ -42,19 +42,21 @@ __device__ __forceinline__ float surrogate(float z, float slope, bool smooth) {
 
 __device__ __forceinline__ bool finite_f32(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
 
+// With at most kSliceMaxNeurons hidden neurons the membrane adjoint is held in slices of 8
+// batch elements, lamv[t][slice][H][8], of which there are S = ceil(B / 8).
+__device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uint32_t b, uint32_t j) {
+  return (((size_t)t * a.S + (b >> 3)) * a.H + j) * 8 + (b & 7u);
+}
+
 // x [B][T][C] -> xt [T][C][64]; lanes >= B hold zeros.  A workgroup per (step t, block of
 // 64 inputs) reads the 64 batch rows of its block (256 bytes each, coalesced) into LDS and
 // writes the block transposed; a wavefront per input c then also writes that input's
 // batch mask xbits[c][t] (bit b: x != 0) and sets *flag if some value is neither 0 nor 1
-// (k_bits' rule).  Of n_out readout weights (w_out), one that is not finite sets flag[2].
+// (k_bits' rule).
 __global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, uint64_t *xbits, uint32_t *flag,
-                                                     uint32_t B, uint32_t T, uint32_t C, const float *w_out,
-                                                     uint32_t n_out) {
+                                                     uint32_t B, uint32_t T, uint32_t C) {
   __shared__ float tile[64][65];
   const uint32_t t = blockIdx.y, c0 = blockIdx.x * 64u;
-  const uint32_t n_thr = gridDim.x * gridDim.y * 256u;
-  for (uint32_t e = (blockIdx.y * gridDim.x + blockIdx.x) * 256u + threadIdx.x; e < n_out; e += n_thr)
-    if (!finite_f32(w_out[e])) atomicOr(flag + 2, 1u);
   const uint32_t l = threadIdx.x % 64u, r = threadIdx.x / 64u;
   for (uint32_t b = r; b < 64u; b += 4u)
     tile[b][l] = b < B && c0 + l < C ? x[((uint64_t)b * T + t) * C + c0 + l] : 0.0f;
@@ -312,14 +314,20 @@ __global__ __launch_bounds__(256) void k_input_current(BpttArgs a) {
   for (int u = 0; u < kMaskSteps; ++u) acc[u] = 0.0f;
   ordered_mask_sum_steps(acc, a.in_t_ptr[j], a.in_t_ptr[j + 1], a.in_t_src, a.w_in_t, a.xbits, a.T, t0);
 #pragma unroll
-  for (int u = 0; u < kMaskSteps; ++u)
-    if ((uint32_t)u < nt) a.iin[((size_t)(t0 + u) * a.H + j) * 64 + b] = acc[u];
+  for (int u = 0; u < kMaskSteps; ++u) {
+    if ((uint32_t)u >= nt) continue;
+    if (!a.events) a.iin[((size_t)(t0 + u) * a.H + j) * 64 + b] = acc[u];
+    else if (b < a.B) a.sg[slice_index(a, t0 + u, b, j)] = acc[u];  // the busy form
+  }
 }
 
 // (a bounded grid that strides over the (t, j) pairs, so that the launch costs little
-// when the flag sends it home)
+// when the flag sends it home; in the event-driven form it also looks the readout weights over)
 constexpr uint32_t kValuesGrid = 2048;
-__global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a) {
+__global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a, bool busy) {
+  if (a.events)
+    for (uint32_t e = blockIdx.x * 256u + threadIdx.x; e < a.H * a.O; e += gridDim.x * 256u)
+      if (!finite_f32(a.w_out[e])) atomicOr(a.flags + 2, 1u);
   if (a.flags[0] == 0) return;
   const uint32_t b = lane_id();
   const uint64_t first = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -345,7 +353,7 @@ __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a) {
       for (uint32_t u = 0; u < 8; ++u)
         if (e + u < e1) sum = sum + wv[u] * x[u];
     }
-    if (b < a.B) a.vall[((size_t)t * a.B + b) * a.Hp + j] = sum;
+    if (b < a.B) (busy ? a.sg[slice_index(a, t, b, j)] : a.vall[((size_t)t * a.B + b) * a.Hp + j]) = sum;
   }
 }
 
@@ -476,8 +484,8 @@ __device__ __forceinline__ size_t row_index(const BpttArgs &a, uint32_t t, uint3
 // recurrent weights, and the target-major pairs of the many-spikes form.
 __global__ void k_scatter_weights(BpttArgs a) {
   const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // k_transpose_x, next, sets flags[0] for inputs other than 0 and 1, flags[2] for readout
-  // weights that are not finite
+  // k_transpose_x sets flags[0] for inputs other than 0 and 1, k_input_current_values flags[2] for
+  // readout weights that are not finite
   if (e < 3) a.flags[e] = 0;
   if (e < a.nnz_in) a.dense_in[a.in_pos[e]] = a.w_in[e];
   if (e < a.nnz_rec) {
@@ -672,6 +680,99 @@ __global__ __launch_bounds__(kSeqThreads) void k_hidden_seq(BpttArgs a) {
   flush((a.T - 1) / kSeqChunk * kSeqChunk, a.T);
 }
 
+// The busy form of the hidden steps, one launch each: lanes are batch elements and a wavefront one
+// neuron, so that the step costs by neurons and synapses, whatever the activity, on all compute
+// units (k_hidden_step_ell with other arrays).  Input currents and membranes are held in the slices
+// of the backward pass's sg and lamv, which are free until then; spikes are batch masks,
+// sbits_t[t][j]; k_busy_rows takes both to the rows of the event-driven form when all steps are
+// done.  (In vall itself, where a neuron's lanes lie Hp floats apart, a step of 700 neurons took
+// 0.4 us longer.)  kChunks = ell_w / 64, or 0 for rows that only the CSR form holds.  6.2 us per step
+// of 1,024 neurons with rows of 102, at any activity; k_hidden_seq takes 1.3 us at 4 spikes a step,
+// 6.5 at 43 and 32 at 268.
+template <int kChunks>
+__global__ __launch_bounds__(256) void k_hidden_step_busy(BpttArgs a, uint32_t t) {
+  extern __shared__ uint64_t prev_masks[];  // [H]: step t - 1
+  const uint32_t j = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform
+  const bool live = j < a.H;
+  const uint32_t jl = live ? j : 0u;
+  const uint32_t b = lane_id();
+  const size_t own = slice_index(a, t, std::min<uint32_t>(b, a.B - 1u), jl);
+  float acc = a.sg[own];
+  const float vp = t ? a.lamv[own - (size_t)a.S * a.H * 8] : 0.0f;
+  int32_t src[kChunks ? kChunks : 1];
+  float wt[kChunks ? kChunks : 1];
+  uint32_t len = 0;
+  if (kChunks) {
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const size_t x = (size_t)jl * a.ell_w + (uint32_t)c * kWave + b;
+      src[c] = a.ell_src[x];
+      wt[c] = a.ell_wt[x];
+    }
+    len = a.ell_len[jl];
+  }
+  const uint64_t *row = a.sbits_t + (size_t)(t ? t - 1 : 0) * a.H;
+  if (t) {
+    for (uint32_t base = 0; base < a.H; base += 4u * 256u) {
+      uint64_t v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = row[std::min<uint32_t>(base + (uint32_t)q * 256u + threadIdx.x, a.H - 1)];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const uint32_t i = base + (uint32_t)q * 256u + threadIdx.x;
+        if (i < a.H) prev_masks[i] = v[q];
+      }
+    }
+  }
+  __syncthreads();
+  if (!live) return;
+  float sp = 0.0f;
+  if (t) {
+    sp = (prev_masks[jl] >> b) & 1u ? 1.0f : 0.0f;
+    if (kChunks) {
+      uint64_t m[kChunks ? kChunks : 1];
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) m[c] = (uint32_t)c * kWave + b < len ? prev_masks[src[c]] : 0u;
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) {
+        const uint32_t n = len > (uint32_t)c * kWave ? std::min<uint32_t>(len - (uint32_t)c * kWave, kWave) : 0u;
+#pragma unroll 8
+        for (uint32_t u = 0; u < ((n + 7u) & ~7u); ++u) {
+          const float sum = acc + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt[c]), (int)u));
+          acc = __builtin_amdgcn_inverse_ballot_w64(lane_read64(m[c], u)) ? sum : acc;
+        }
+      }
+    } else {
+      acc = ordered_mask_sum(acc, a.rec_t_ptr[j], a.rec_t_ptr[j + 1], a.rec_t_src, a.w_rec_t, row, 1, 0);
+    }
+  }
+  float v = a.beta * vp;
+  v = v + acc;
+  v = v - a.theta * sp;
+  if (b < a.B) a.lamv[own] = v;
+  const uint64_t mk = __ballot(b < a.B && spike_fn(v - a.theta, a.slope, false) != 0.0f);
+  if (b == 0) a.sbits_t[(size_t)t * a.H + j] = mk;
+}
+
+// The busy form's membranes and spikes as rows and words of every batch element: a workgroup per
+// (word of 64 neurons, step) transposes the step's slices through LDS.
+__global__ __launch_bounds__(256) void k_busy_rows(BpttArgs a) {
+  __shared__ float tile[64][65];  // [b][neuron]
+  const uint32_t w = blockIdx.x, t = blockIdx.y, n = std::min<uint32_t>(64u, a.H - w * 64u);
+  for (uint32_t x = threadIdx.x; x < a.S * 512u; x += 256u) {
+    const uint32_t j = (x & 511u) >> 3, b = (x >> 9) * 8u + (x & 7u);
+    if (j < n) tile[b][j] = a.lamv[slice_index(a, t, b, w * 64u + j)];
+  }
+  __syncthreads();
+  const uint32_t lane = lane_id();
+  for (uint32_t b = threadIdx.x / kWave; b < a.B; b += 4u) {
+    const float v = lane < n ? tile[b][lane] : 0.0f;
+    const uint64_t word = __ballot(lane < n && spike_fn(v - a.theta, a.slope, false) != 0.0f);
+    if (lane < n) a.vall[row_index(a, t, b) + w * 64u + lane] = v;
+    if (lane == 0) a.spk[((size_t)b * a.T + t) * a.nw + w] = word;
+  }
+}
+
 // Batch masks of the hidden spikes from the words of every batch element: a workgroup per
 // (word, kMaskBlock steps) sets the few spikes' bits in LDS and writes the 64 neurons' masks
 // of its steps, contiguous per neuron.
@@ -709,18 +810,12 @@ __global__ __launch_bounds__(256) void k_readout_events(BpttArgs a, float *ro) {
   if (bt >= a.B * a.T) return;
   const uint32_t lane = lane_id();
   const uint64_t mine = lane < a.nw ? a.spk[(size_t)bt * a.nw + lane] : 0ull;
+  const bool every = a.flags[2] != 0;
   for (uint32_t o0 = 0; o0 < a.O; o0 += kWave) {
     const uint32_t o = std::min<uint32_t>(o0 + lane, a.O - 1);
     float acc = 0.0f;
     uint64_t any = __ballot(mine != 0), word = 0;
     uint32_t at = 0;
-    if (a.flags[2]) {
-      any = 0;
-      for (uint32_t i = 0; i < a.H; ++i) {
-        const float on = (lane_read64(mine, i >> 6) >> (i & 63u)) & 1u ? 1.0f : 0.0f;
-        acc = acc + on * a.w_out[(size_t)i * a.O + o];
-      }
-    }
     while (any) {
       float w[4];
       uint32_t n = 0;
@@ -741,13 +836,89 @@ __global__ __launch_bounds__(256) void k_readout_events(BpttArgs a, float *ro) {
       for (int u = 0; u < 4; ++u)
         if ((uint32_t)u < n) acc = acc + w[u];
     }
+    if (every) {
+      acc = 0.0f;
+      for (uint32_t i = 0; i < a.H; ++i) {
+        const float on = (lane_read64(mine, i >> 6) >> (i & 63u)) & 1u ? 1.0f : 0.0f;
+        acc = acc + on * a.w_out[(size_t)i * a.O + o];
+      }
+    }
     if (o0 + lane < a.O) ro[(size_t)bt * a.O + o0 + lane] = acc;
   }
 }
 
-// The leaky readout's scan (as k_readout_scan) over ro[b][t][o]: block (b, 64 readouts).
+// Readout drive of the busy form, from its masks: lanes are batch elements, a wavefront takes
+// kMaskOuts readouts of a step over all neurons, ascending, with one add and one select each.  The
+// masks and weights of 64 neurons arrive one per lane and reach the wavefront by lane reads, as in
+// ordered_mask_sum; the next 64 are requested ahead.  80 us for 64 x 250 steps, 1,024 neurons and 20
+// readouts, whatever the spikes; k_readout_events, which reads a row of weights per spike, takes 8 us
+// at 4 spikes a step and 235 at 408.
+constexpr int kMaskOuts = 4;
+__global__ __launch_bounds__(64) void k_readout_masks(BpttArgs a, float *ro) {
+  const uint32_t t = blockIdx.x, o0 = blockIdx.y * kMaskOuts, b = threadIdx.x;
+  const uint64_t *masks = a.sbits_t + (size_t)t * a.H;
+  const uint32_t last = std::min<uint32_t>(kMaskOuts, a.O - o0) - 1u;
+  const bool every = a.flags[2] != 0;  // as k_readout_events
+  float acc[kMaskOuts] = {}, w[kMaskOuts], wn[kMaskOuts];
+  uint64_t m, mn;
+  auto request = [&](uint32_t base) {  // past the last neuron: an empty mask, a weight of 0
+    const uint32_t i = base + b;
+    mn = i < a.H ? masks[i] : 0ull;
+#pragma unroll
+    for (uint32_t q = 0; q < kMaskOuts; ++q)
+      wn[q] = i < a.H ? a.w_out[(size_t)i * a.O + o0 + std::min(q, last)] : 0.0f;
+  };
+  request(0);
+  for (uint32_t base = 0; base < a.H; base += kWave) {
+    m = mn;
+#pragma unroll
+    for (int q = 0; q < kMaskOuts; ++q) w[q] = wn[q];
+    if (base + kWave < a.H) request(base + kWave);
+    if (every) {
+      for (uint32_t u = 0; u < kWave; ++u) {
+        const float on = __builtin_amdgcn_inverse_ballot_w64(lane_read64(m, u)) ? 1.0f : 0.0f;
+#pragma unroll
+        for (int q = 0; q < kMaskOuts; ++q)
+          acc[q] = acc[q] + on * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w[q]), (int)u));
+      }
+    } else {
+#pragma unroll 8
+      for (uint32_t u = 0; u < kWave; ++u) {
+        const bool on = __builtin_amdgcn_inverse_ballot_w64(lane_read64(m, u));
+#pragma unroll
+        for (int q = 0; q < kMaskOuts; ++q) {
+          const float sum = acc[q] + __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w[q]), (int)u));
+          acc[q] = on ? sum : acc[q];
+        }
+      }
+    }
+  }
+  if (b < a.B)
+    for (uint32_t q = 0; q <= last; ++q) ro[((size_t)b * a.T + t) * a.O + o0 + q] = acc[q];
+}
+
+// Set bits of kActSamples words at scattered places of an array of n, by a wavefront.
+__device__ __forceinline__ uint32_t sample_bits(const uint64_t *words, uint64_t n) {
+  uint32_t count = 0;
+#pragma unroll 16
+  for (uint32_t e = lane_id(); e < kActSamples; e += kWave) count += (uint32_t)__popcll(words[((uint64_t)(e * 0x9E3779B9u) * n) >> 32]);
+  return wave_sum(count);
+}
+
+// The leaky readout's scan (as k_readout_scan) over ro[b][t][o]: block (b, 64 readouts).  Beside it
+// two blocks take the pass's activity, a sample of the inputs and of the hidden spikes, to host
+// memory: what the next pass's way is chosen by.
 __global__ __launch_bounds__(64) void k_readout_scan_events(BpttArgs a, const float *ro) {
   const uint32_t b = blockIdx.x, o = blockIdx.y * 64u + threadIdx.x;
+  if (b >= a.B) {
+    if (blockIdx.y) return;
+    const uint32_t bits = b == a.B ? sample_bits(a.xbits, (uint64_t)a.C * a.T) : sample_bits(a.spk, (uint64_t)a.B * a.T * a.nw);
+    if (threadIdx.x == 0) {
+      a.act_out[b - a.B] = bits;
+      if (b == a.B) a.act_out[2] = a.flags[0];
+    }
+    return;
+  }
   const float *r0 = ro + (size_t)b * a.T * a.O + std::min<uint32_t>(o, a.O - 1);
   float u = 0.0f, m = 0.0f;
   uint32_t tm = 0;
@@ -938,13 +1109,12 @@ __global__ void k_lam_u(BpttArgs a, const float *g_loss) {
   const float g = b < a.B ? a.dm[(size_t)b * a.O + o] * scale : 0.0f;
   const int32_t tm = b < a.B ? a.tmax[(size_t)b * a.O + o] : -1;
   float nxt = 0.0f;
-  bool finite = true;
   for (int32_t t = (int32_t)a.T - 1; t >= 0; --t) {
     nxt = (t == tm ? g : 0.0f) + a.beta_out * nxt;
     a.lamu[((size_t)t * a.O + o) * 64 + b] = nxt;
-    finite = finite && finite_f32(nxt);
   }
-  if (!finite) atomicOr(a.flags + 3, 1u);
+  // (a value that is not finite makes every later one so)
+  if (!finite_f32(nxt)) atomicOr(a.flags + 3, 1u);
 }
 
 // Readout part of the spike adjoint of every step, the first terms of the sum that
@@ -995,11 +1165,6 @@ __global__ __launch_bounds__(256) void k_adjoint_step(BpttArgs a, uint32_t t, co
 }
 
 // ---- the sliced membrane adjoint -------------------------------------------------------
-// With at most kSliceMaxNeurons hidden neurons the membrane adjoint is held in slices of 8
-// batch elements, lamv[t][slice][H][8], of which there are S = ceil(B / 8).
-__device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uint32_t b, uint32_t j) {
-  return (((size_t)t * a.S + (b >> 3)) * a.H + j) * 8 + (b & 7u);
-}
 
 // Readout part of the spike adjoint of every step (as k_readout_adjoint), in the sliced
 // layout.  A workgroup per (block of 32 neurons, t): thread (neuron, b mod 8) keeps the sums
@@ -1535,19 +1700,11 @@ __global__ __launch_bounds__(256) void k_grad_out_events(BpttArgs a) {
   const uint32_t i = w / n_blocks, o0 = w % n_blocks * kOutBlock, lane = lane_id();
   const uint32_t no = std::min<uint32_t>(kOutBlock, a.O - o0);
   float acc[kOutBlock] = {};
+  const bool every = a.flags[3] != 0;
   for (uint32_t t0 = 0; t0 < a.T; t0 += kWave) {
     const uint64_t mine = t0 + lane < a.T ? a.sbits[(size_t)i * a.T + t0 + lane] : 0ull;
     // kOutSteps steps requested together (the last one again where fewer are left, unused)
     uint64_t any = __ballot(mine != 0);
-    if (a.flags[3]) {
-      any = 0;
-      for (uint32_t k = 0; k < kWave && t0 + k < a.T; ++k) {
-        const float on = (lane_read64(mine, k) >> lane) & 1u ? 1.0f : 0.0f;
-#pragma unroll
-        for (int q = 0; q < kOutBlock; ++q)
-          acc[q] += on * a.lamu[((size_t)(t0 + k) * a.O + o0 + std::min<uint32_t>(q, no - 1)) * 64 + lane];
-      }
-    }
     while (any) {
       float l[kOutSteps][kOutBlock];
       uint64_t on[kOutSteps];
@@ -1570,6 +1727,16 @@ __global__ __launch_bounds__(256) void k_grad_out_events(BpttArgs a) {
       }
     }
   }
+  if (every) {
+#pragma unroll
+    for (int q = 0; q < kOutBlock; ++q) acc[q] = 0.0f;
+    for (uint32_t t = 0; t < a.T; ++t) {
+      const float on = (a.sbits[(size_t)i * a.T + t] >> lane) & 1u ? 1.0f : 0.0f;
+#pragma unroll
+      for (int q = 0; q < kOutBlock; ++q)
+        acc[q] += on * a.lamu[((size_t)t * a.O + o0 + std::min<uint32_t>(q, no - 1)) * 64 + lane];
+    }
+  }
 #pragma unroll
   for (int q = 0; q < kOutBlock; ++q) {
     const float sum = wave_sum(acc[q]);
@@ -1590,6 +1757,18 @@ uint32_t blocks_for(uint64_t n, uint32_t per) { return (uint32_t)((n + per - 1) 
 __global__ void k_gather_ell(const float *w, const uint32_t *edge, float *w_ell, uint64_t n) {
   const uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (x < n) w_ell[x] = edge[x] == 0xFFFFFFFFu ? 0.0f : w[edge[x]];
+}
+
+// The ELL copy of the recurrent in-edges (padding: source 0, edge 0xFFFFFFFF), one place per thread.
+__global__ void k_fill_ell(BpttArgs a, int32_t *src, uint32_t *edge, uint32_t *len) {
+  const uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= (uint64_t)a.H * a.ell_w) return;
+  const uint32_t j = (uint32_t)(x / a.ell_w), k = (uint32_t)(x % a.ell_w);
+  const uint64_t e0 = a.rec_t_ptr[j];
+  const uint32_t n = (uint32_t)(a.rec_t_ptr[j + 1] - e0);
+  src[x] = k < n ? a.rec_t_src[e0 + k] : 0;
+  edge[x] = k < n ? a.rec_t_edge[e0 + k] : 0xFFFFFFFFu;
+  if (k == 0) len[j] = n;
 }
 
 // The weights of the sliced adjoint's padded rows: edge e of the CSR order at pos[e].
@@ -1620,24 +1799,22 @@ static void gather_weights(const BpttArgs &a, hipStream_t s) {
 // in between touches only the plan's own buffers (its weight copies included), so the
 // runtime can capture it once per plan in a HIP graph and replay it on every call.
 
-hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s) {
+hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, bool busy, hipStream_t s) {
   if (a.events) {
-    // every kernel of the pass is launched here: they are few, and some read the caller's arrays
-    const uint64_t nnz = std::max<uint64_t>(std::max(a.nnz_in, a.nnz_rec), 2);
+    const uint64_t nnz = std::max<uint64_t>(std::max(a.nnz_in, a.nnz_rec), 3);
     hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                       a.T, a.C, a.w_out, a.H * a.O);
-    hipLaunchKernelGGL(k_input_rows, dim3(blocks_for((uint64_t)a.B * a.T, 4), blocks_for(a.Hp / 256, kInputBlocks)),
-                       dim3(256), 0, s, a, x);
+                       a.T, a.C);
+    if (busy) {
+      gather_weights(a, s);
+      hipLaunchKernelGGL(k_input_current, dim3(blocks_for((uint64_t)((a.T + kMaskSteps - 1) / kMaskSteps) * a.H, 4)),
+                         dim3(256), 0, s, a);
+    } else {
+      hipLaunchKernelGGL(k_input_rows, dim3(blocks_for((uint64_t)a.B * a.T, 4), blocks_for(a.Hp / 256, kInputBlocks)),
+                         dim3(256), 0, s, a, x);
+    }
     hipLaunchKernelGGL(k_input_current_values, dim3(std::min<uint32_t>(blocks_for((uint64_t)a.T * a.H, 4), kValuesGrid)),
-                       dim3(256), 0, s, a);
-    // whole wavefronts up to Hp, a multiple of 256
-    const size_t lds = (size_t)kSeqChunk * a.Hp * sizeof(float);
-    if (a.Hp <= 256) hipLaunchKernelGGL(k_hidden_seq<1>, dim3(a.B), dim3(a.Hp), lds, s, a);
-    else if (a.Hp <= 1024) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
-    else hipLaunchKernelGGL(k_hidden_seq<4>, dim3(a.B), dim3(a.Hp / 4), lds, s, a);
-    hipLaunchKernelGGL(k_readout_events, dim3(blocks_for((uint64_t)a.B * a.T, 4)), dim3(256), 0, s, a, a.ro);
-    hipLaunchKernelGGL(k_readout_scan_events, dim3(a.B, blocks_for(a.O, 64)), dim3(64), 0, s, a, a.ro);
+                       dim3(256), 0, s, a, busy);
     return hipGetLastError();
   }
   gather_weights(a, s);
@@ -1645,7 +1822,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t 
   // pass of a smooth-mode plan
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
   hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                     a.T, a.C, (const float *)nullptr, 0u);
+                     a.T, a.C);
   const hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   return e != hipSuccess ? e : hipGetLastError();
 }
@@ -1656,13 +1833,46 @@ hipError_t bptt_spike_masks(const BpttArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The hidden steps of the event-driven form, one workgroup per batch element.
+hipError_t bptt_hidden_seq(const BpttArgs &a, hipStream_t s) {
+  // whole wavefronts up to Hp, a multiple of 256
+  const size_t lds = (size_t)kSeqChunk * a.Hp * sizeof(float);
+  if (a.Hp <= 256) hipLaunchKernelGGL(k_hidden_seq<1>, dim3(a.B), dim3(a.Hp), lds, s, a);
+  else if (a.Hp <= 1024) hipLaunchKernelGGL(k_hidden_seq<2>, dim3(a.B), dim3(a.Hp / 2), lds, s, a);
+  else hipLaunchKernelGGL(k_hidden_seq<4>, dim3(a.B), dim3(a.Hp / 4), lds, s, a);
+  return hipGetLastError();
+}
+
+// ... and its readout, after either form of the hidden steps.
+hipError_t bptt_readout_events(const BpttArgs &a, bool busy, hipStream_t s) {
+  if (busy) hipLaunchKernelGGL(k_readout_masks, dim3(a.T, blocks_for(a.O, kMaskOuts)), dim3(64), 0, s, a, a.ro);
+  else hipLaunchKernelGGL(k_readout_events, dim3(blocks_for((uint64_t)a.B * a.T, 4)), dim3(256), 0, s, a, a.ro);
+  hipLaunchKernelGGL(k_readout_scan_events, dim3(a.B + 2, blocks_for(a.O, 64)), dim3(64), 0, s, a, a.ro);
+  return hipGetLastError();
+}
+
 // g: the plan's arguments with w_out = w_out_c
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s) {
+  if (g.events) {  // the hidden steps of the busy form
+    const dim3 grid(blocks_for(g.H, 4));
+    const size_t lds = (size_t)g.H * sizeof(uint64_t);
+    for (uint32_t t = 0; t < g.T; ++t) {
+      switch (g.ell_w / kWave) {
+        case 0: hipLaunchKernelGGL(k_hidden_step_busy<0>, grid, dim3(256), lds, s, g, t); break;
+        case 1: hipLaunchKernelGGL(k_hidden_step_busy<1>, grid, dim3(256), lds, s, g, t); break;
+        case 2: hipLaunchKernelGGL(k_hidden_step_busy<2>, grid, dim3(256), lds, s, g, t); break;
+        case 3: hipLaunchKernelGGL(k_hidden_step_busy<3>, grid, dim3(256), lds, s, g, t); break;
+        default: hipLaunchKernelGGL(k_hidden_step_busy<4>, grid, dim3(256), lds, s, g, t); break;
+      }
+    }
+    hipLaunchKernelGGL(k_busy_rows, dim3(g.nw, g.T), dim3(256), 0, s, g);
+    return hipGetLastError();
+  }
   // the inputs' batch masks and flags[0] come from the prologue's transpose
   hipLaunchKernelGGL(k_input_current, dim3(blocks_for((uint64_t)((g.T + kMaskSteps - 1) / kMaskSteps) * g.H, 4)),
                      dim3(256), 0, s, g);
   hipLaunchKernelGGL(k_input_current_values, dim3(std::min<uint32_t>(blocks_for((uint64_t)g.T * g.H, 4), kValuesGrid)),
-                     dim3(256), 0, s, g);
+                     dim3(256), 0, s, g, false);
   const dim3 grid(blocks_for(g.H, 4));
   float *vprev = nullptr;
   for (uint32_t t = 0; t < g.T; ++t) {
@@ -1796,6 +2006,11 @@ hipError_t bptt_prepare(const BpttArgs &a) {
       e = allow(reinterpret_cast<const void *>(&k_adjoint_seq<kSeqRegs>), kSeqMaxMore * kWave * kSeqGroupBytes);
   }
   return e;
+}
+
+hipError_t bptt_fill_ell(const BpttArgs &a, int32_t *src, uint32_t *edge, uint32_t *len, hipStream_t s) {
+  hipLaunchKernelGGL(k_fill_ell, dim3(blocks_for((uint64_t)a.H * a.ell_w, 256)), dim3(256), 0, s, a, src, edge, len);
+  return hipGetLastError();
 }
 
 uint64_t bptt_lists(const BpttArgs &a) { return (uint64_t)(a.C + a.H) * blocks_for(a.T, kListChunk); }

@@ -2045,6 +2045,10 @@ struct snn_bptt {
   snn::BpttArgs args{};
   uint64_t forwards = 0;     // forward passes run (the backward uses the latest)
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;  // captured bodies of the two passes
+  volatile uint32_t *activity = nullptr;  // of a finished pass (BpttArgs::act_out)
+  ~snn_bptt() {
+    if (activity) (void)hipHostFree(const_cast<uint32_t *>(activity));
+  }
 };
 
 namespace {
@@ -2220,8 +2224,6 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   a.xbits = dev_array<uint64_t>(pool, (size_t)a.C * a.T + 8);
   a.sbits = dev_array<uint64_t>(pool, (size_t)a.H * a.T + 16) + 8;
   a.sbits_t = dev_array<uint64_t>(pool, (size_t)a.T * a.H);
-  // ELL copy of the recurrent in-edges for the hidden steps (rows padded to a multiple of
-  // 64, at most 256 wide, and at most 8,192 neurons, whose masks a workgroup stages)
   uint64_t max_deg = 0;
   for (uint32_t j = 0; j < a.H; ++j) max_deg = std::max<uint64_t>(max_deg, rt_ptr[j + 1] - rt_ptr[j]);
   a.ell_w = 0;
@@ -2256,24 +2258,11 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     a.spk = dev_array<uint64_t>(pool, (size_t)a.B * a.T * a.nw);
     a.lists = dev_array<uint16_t>(pool, snn::bptt_lists(a) * snn::bptt_list_stride());
     a.list_len = dev_array<uint32_t>(pool, snn::bptt_lists(a));
+    void *out = nullptr;
+    check(hipHostMalloc(&out, 3 * sizeof(uint32_t), hipHostMallocPortable), "activity of a pass");
+    p->activity = a.act_out = static_cast<uint32_t *>(out);
+    p->activity[0] = p->activity[1] = p->activity[2] = 0;
     check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
-  }
-  if (!a.events && nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {
-    const uint32_t wd = (uint32_t)((max_deg + 63) / 64 * 64);
-    std::vector<int32_t> es((size_t)a.H * wd, 0);
-    std::vector<uint32_t> ee((size_t)a.H * wd, 0xFFFFFFFFu), el(a.H);
-    for (uint32_t j = 0; j < a.H; ++j) {
-      el[j] = (uint32_t)(rt_ptr[j + 1] - rt_ptr[j]);
-      for (uint64_t e = rt_ptr[j]; e < rt_ptr[j + 1]; ++e) {
-        es[(size_t)j * wd + (e - rt_ptr[j])] = rt_src[e];
-        ee[(size_t)j * wd + (e - rt_ptr[j])] = rt_edge[e];
-      }
-    }
-    a.ell_w = wd;
-    a.ell_src = upload(pool, es);
-    a.ell_edge = upload(pool, ee);
-    a.ell_len = upload(pool, el);
-    a.ell_wt = dev_array<float>(pool, es.size());
   }
   // padded rows of the recurrent weights for the sliced adjoint
   uint64_t max_row = 0;
@@ -2320,6 +2309,20 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   a.m = dev_array<float>(pool, (size_t)a.B * a.O);
   a.dm = dev_array<float>(pool, (size_t)a.B * a.O);
   a.tmax = dev_array<int32_t>(pool, (size_t)a.B * a.O);
+  // ELL copy of the recurrent in-edges for the hidden steps (rows padded to a multiple of
+  // 64, at most 256 wide, and at most 8,192 neurons, whose masks a workgroup stages), made on the
+  // device from the CSR form
+  if (nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {
+    a.ell_w = (uint32_t)((max_deg + 63) / 64 * 64);
+    const size_t places = (size_t)a.H * a.ell_w;
+    int32_t *src = dev_array<int32_t>(pool, places);
+    uint32_t *edge = dev_array<uint32_t>(pool, places), *len = dev_array<uint32_t>(pool, a.H);
+    check(snn::bptt_fill_ell(a, src, edge, len, pool->stream), "padded in-edges");
+    a.ell_src = src;
+    a.ell_edge = edge;
+    a.ell_len = len;
+    a.ell_wt = dev_array<float>(pool, places);
+  }
   check(hipStreamSynchronize(pool->stream), "sync after plan");
 }
 
@@ -2345,6 +2348,46 @@ void bptt_body(snn_bptt *p, hipGraphExec_t &exec, hipStream_t s, F &&body) {
     check(e3, "bptt graph instantiate");
   }
   check(hipGraphLaunch(exec, s), "bptt graph launch");
+}
+
+// us of a forward pass's input currents and hidden steps: the quiet form with `inputs` nonzero
+// inputs and `spikes` hidden spikes per step and batch element, and the busy form.  The quiet form
+// (k_input_rows, k_hidden_seq) pays for every input and spike with a row of weights, or, past
+// twice the longest column, for the columns; the busy form (k_input_current, k_hidden_step_busy) for
+// every synapse and launch.  64 x 250 x 700 -> 1,024 with rows of 102, at 4 / 43 / 76 / 208 / 302
+// spikes: quiet 467 / 1,850 / 2,833 / 6,929 / 4,553 us, busy 1,834 / 1,859 / 1,873 / 1,944 / 1,996
+// (whole forward passes); the two are equal at 43 spikes, at 33 of 201 neurons, at 42 of 500, 66 of
+// 2,048, 20 of 1,024 with rows of 20 and 135 with rows of 512, where this model has 43, 28, 35, 57,
+// 23 and 115.
+double bptt_quiet_us(const snn::BpttArgs &a, double inputs, double spikes) {
+  const bool wide = a.Hp > 1024;
+  const double row = a.Hp <= 256 ? 0.10 : wide ? 0.18 : 0.14, column = wide ? 0.23 : 0.115;
+  const double step = 0.6 + (spikes > 2.0 * a.col_w ? a.col_w * column : spikes * row);
+  return inputs * a.B * a.T * a.Hp * 0.2e-6 + a.T * step;
+}
+double bptt_busy_us(const snn::BpttArgs &a, bool binary) {
+  const double degree = (double)a.nnz_rec / a.H;
+  return (binary ? (double)a.nnz_in * a.T * 6e-6 : 0.0) + a.T * (2.8 + 0.6e-3 * a.H + degree * (a.Hp > 1024 ? 0.034 : 0.026));
+}
+
+// Whether the next forward pass takes the busy form (event-driven plans): the faster one at the
+// activity of the latest finished pass that the host has seen (0 before the first); the results
+// are the same.
+bool bptt_busy(const snn_bptt *p) {
+  const snn::BpttArgs &a = p->args;
+  if (!a.events) return false;
+  // bits per word: of an input and step over the batch, of 64 neurons
+  const double inputs = (double)p->activity[0] / snn::kActSamples * a.C / a.B;
+  const double spikes = (double)p->activity[1] / snn::kActSamples * a.nw;
+  // (inputs other than 0 and 1 take neither form's way to the input currents)
+  const bool binary = p->activity[2] == 0;
+  return bptt_quiet_us(a, binary ? inputs : 0.0, spikes) > bptt_busy_us(a, binary);
+}
+
+// A graph of the plan's cannot be launched into a stream that is being captured.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
 void bptt_release_graphs(snn_bptt *p) {
@@ -2852,12 +2895,22 @@ snn_status snn_bptt_forward(snn_bptt *p, const float *x, const float *w_in, cons
     a.w_rec = w_rec;
     a.w_out = w_out;
     hipStream_t s = stream ? (hipStream_t)stream : p->pool.stream;
-    check(snn::bptt_forward_prologue(a, x, s), "bptt forward");
+    const bool busy = bptt_busy(p) && (p->desc.eager || !capturing(s));
+    check(snn::bptt_forward_prologue(a, x, busy, s), "bptt forward");
     snn::BpttArgs g = p->args;  // the body reads the plan's buffers only
     g.w_out = g.w_out_c;
-    if (!a.events) bptt_body(p, p->g_fwd, s, [&](hipStream_t st) { return snn::bptt_forward_body(g, st); });
+    if (a.events && !busy) check(snn::bptt_hidden_seq(a, s), "bptt forward");
+    else bptt_body(p, p->g_fwd, s, [&](hipStream_t st) { return snn::bptt_forward_body(g, st); });
+    if (a.events) check(snn::bptt_readout_events(a, busy, s), "bptt forward");
     check(snn::bptt_forward_epilogue(a, labels, loss, s), "bptt forward");
     p->forwards++;
+  });
+}
+
+snn_status snn_bptt_get_route(snn_bptt *p, uint32_t *out) {
+  return guarded([&] {
+    if (!p || !out) fail(SNN_E_INVALID, "null argument");
+    *out = p->args.events && !bptt_busy(p) ? SNN_ROUTE_PERSISTENT : SNN_ROUTE_LAUNCHES;
   });
 }
 

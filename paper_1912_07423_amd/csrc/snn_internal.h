@@ -300,6 +300,7 @@ constexpr int kSeqRegs = 48;
 constexpr uint32_t kSeqGroupBytes = 24;
 constexpr uint32_t kSeqMaxMore = 98;
 constexpr uint64_t kSliceMaxPairs = 1ull << 26;
+constexpr uint32_t kActSamples = 4096;  // words that a pass's activity is estimated from
 struct BpttArgs {
   uint32_t B, T, C, H, O, K;
   uint32_t events;             // event-driven forward pass (spiking mode); then also:
@@ -354,17 +355,25 @@ struct BpttArgs {
                                // form: a readout weight / adjoint is not finite (no term is left out)
   float *xt, *s, *vck, *vtmp, *vseg, *ro, *lamu, *lamv, *lam_carry, *m, *dm;
   int32_t *tmax;
+  uint32_t *act_out;           // [3] set bits of kActSamples words of xbits and of spk, flags[0]: pinned
+                               // host memory
 };
 // Forward and backward passes in three parts each: prologue and epilogue touch the
 // caller's arrays, the body only the plan's buffers (capturable once per plan).  The body
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
 hipError_t bptt_prepare(const BpttArgs &a);
+hipError_t bptt_fill_ell(const BpttArgs &a, int32_t *src, uint32_t *edge, uint32_t *len, hipStream_t s);
 hipError_t bptt_spike_masks(const BpttArgs &a, hipStream_t s);
 uint64_t bptt_lists(const BpttArgs &a);  // number of event lists, entries held for each
 uint32_t bptt_list_stride();
 hipError_t bptt_trace_v(const BpttArgs &a, hipStream_t s);  // fills vck (event-driven plans)
-hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, hipStream_t s);
+// busy (event-driven plans): the input currents by masks and the hidden steps by launches
+// (bptt_forward_body), for passes whose activity makes that the faster way; else bptt_hidden_seq.
+// Either is followed by bptt_readout_events, and the results are the same bit for bit.
+hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, bool busy, hipStream_t s);
+hipError_t bptt_hidden_seq(const BpttArgs &a, hipStream_t s);
+hipError_t bptt_readout_events(const BpttArgs &a, bool busy, hipStream_t s);
 hipError_t bptt_forward_body(const BpttArgs &g, hipStream_t s);
 hipError_t bptt_forward_epilogue(const BpttArgs &a, const int32_t *labels, float *loss, hipStream_t s);
 hipError_t bptt_backward_prologue(const BpttArgs &a, const float *g_loss, hipStream_t s);

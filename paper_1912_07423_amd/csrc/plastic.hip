@@ -42,7 +42,7 @@ constexpr uint32_t kPlasticTarget = 0x8000u;  // flag of a laid-out target: its 
 constexpr int kListBlock = 1024;
 constexpr int kT = kPlasticBlock;
 constexpr int kWaves = kT / kWave;
-constexpr int kU = 8;           // synapses of a lane in flight: delivery
+constexpr int kU = kPlasticAhead;  // synapses of a lane in flight: delivery
 constexpr int kLtp = 8;         //   potentiation
 constexpr uint32_t kLtpParts = 32;
 constexpr uint32_t kXcds = 8;

@@ -982,6 +982,10 @@ void issue_window(snn_network *net, uint32_t steps) {
   net->t_host += steps;
 }
 
+// A high rate (population averages in use lie below it), and the spikes per step at a rate.
+constexpr double kHighHz = 100.0;
+double spikes_at(const snn_network *net, double hz) { return net->n * hz * net->prm.dt_ms * 1e-3; }
+
 // ---- the persistent one-workgroup form -----------------------------------------------
 // Drive thresholds a 32-bit word can reach.
 uint32_t drive_thresholds(const snn_network *net) {
@@ -1082,10 +1086,6 @@ double launches_us(const snn_network *net, double spikes) {
   return window / net->window;
 }
 
-// The rate taken where none has been measured: population averages in use lie below it.
-constexpr double kHighHz = 100.0;
-double spikes_at(const snn_network *net, double hz) { return net->n * hz * net->prm.dt_ms * 1e-3; }
-
 // Whether a rate in use makes the launches the faster way, so that the rate has to be known.
 // (Networks of up to some 8,000 neurons with rows of 80 are persistent at any such rate.)
 bool rate_matters(const snn_network *net) {
@@ -1184,9 +1184,19 @@ bool choose_windows(snn_network *net) {
   if (net->range_off) return true;
   const bool off16 = net->row_len_bound < 65536;
   const size_t entries = (size_t)net->n * (ranges + 1);
-  // a slot holds nearly every sub-row (their lengths are about Poisson)
-  const double mean = (double)net->nnz / ((double)net->n * ranges);
-  const uint32_t shift = lanes_shift_for(mean + 2.5 * std::sqrt(mean) + 0.5, 1);
+  // Lanes of a sub-row (their lengths are about Poisson): nearly every one fits.  A workgroup has
+  // kPlasticAhead of them per lane group in flight and takes what is beyond one by one, which at
+  // twice as many spikes a step is slower than the launches; where a rate in use brings that
+  // many, the lanes go down to the mean and a deviation.  100,000 neurons with 2,000 synapses each (8.9
+  // a sub-row), at 852 / 500 / 148 spikes a step: 32 lanes 129 / 68.9 / 18.8 us, 16 lanes 94 / 49.4 /
+  // 17.0 (launches 103 / 59.8 / 33.8); 60,000 (5.1) at 937 / 743: 16 lanes 76.5 / 63.8, 8 lanes 55.1 / 47.2
+  // (69.5 / 62.8); 300,000 (1.5) at 3,316 / 772: 8 lanes 268 / 64.7, 4 lanes 203 / 53.3 (215 / 66.8).  At
+  // low rates the long sub-rows cost more than is gained (10,000 neurons, 1.3 a sub-row: 3.8 us with 8
+  // lanes, 4.0 with 4).
+  const double mean = (double)net->nnz / ((double)net->n * ranges), rows = spikes_at(net, kHighHz);
+  uint32_t shift = lanes_shift_for(mean + 2.5 * std::sqrt(mean) + 0.5, 1);
+  const uint32_t fewest = lanes_shift_for(mean + std::sqrt(mean) + 0.5, 1);
+  while (shift > fewest && rows > 2.0 * (snn::kPlasticAhead * snn::kPlasticBlock >> shift)) --shift;
   const size_t row_bytes = (size_t)ranges * (sizeof(snn::SubRow) + (sizeof(uint16_t) << shift));
   const uint32_t cap = (uint32_t)std::min<size_t>(snn::kPlasticRows, kWindowRowBytes / row_bytes);
   const uint32_t slots = net->delay + std::min(net->delay - 1, snn::kPlasticSteps) + 1;

@@ -166,6 +166,7 @@ struct StdpArgs {
 
 // Windows of an eagerly plastic network (plastic.hip): a workgroup per range of targets.
 constexpr uint32_t kPlasticBlock = 512;  // its lanes, and the most targets of a range
+constexpr uint32_t kPlasticAhead = 8;    // sub-rows of a lane group in flight
 constexpr uint32_t kPlasticRows = 2048;  // most arriving rows of a window that are laid out
 constexpr uint32_t kPlasticSteps = 16;   // most steps of a window (its arrivals are one 32-bit mask)
 // One arriving neuron's synapses on the range: [lo, lo + len), those from p0 to p1 (offsets

@@ -1759,16 +1759,39 @@ __global__ void k_gather_ell(const float *w, const uint32_t *edge, float *w_ell,
   if (x < n) w_ell[x] = edge[x] == 0xFFFFFFFFu ? 0.0f : w[edge[x]];
 }
 
-// The ELL copy of the recurrent in-edges (padding: source 0, edge 0xFFFFFFFF), one place per thread.
-__global__ void k_fill_ell(BpttArgs a, int32_t *src, uint32_t *edge, uint32_t *len) {
-  const uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= (uint64_t)a.H * a.ell_w) return;
-  const uint32_t j = (uint32_t)(x / a.ell_w), k = (uint32_t)(x % a.ell_w);
+// The layouts' index arrays, a wavefront per neuron: its in-edges of both projections and its row.
+__global__ __launch_bounds__(256) void k_fill_layouts(BpttArgs a, BpttLayouts lay) {
+  const uint32_t j = blockIdx.x * 4 + threadIdx.x / kWave, lane = lane_id();
+  if (j >= a.H) return;
+  if (lay.in_pos)
+    for (uint64_t x = a.in_t_ptr[j] + lane; x < a.in_t_ptr[j + 1]; x += kWave)
+      lay.in_pos[a.in_t_edge[x]] = (uint32_t)a.in_t_src[x] * a.Hp + j;
   const uint64_t e0 = a.rec_t_ptr[j];
-  const uint32_t n = (uint32_t)(a.rec_t_ptr[j + 1] - e0);
-  src[x] = k < n ? a.rec_t_src[e0 + k] : 0;
-  edge[x] = k < n ? a.rec_t_edge[e0 + k] : 0xFFFFFFFFu;
-  if (k == 0) len[j] = n;
+  const uint32_t n_in = (uint32_t)(a.rec_t_ptr[j + 1] - e0);
+  if (lay.rec_pos)
+    for (uint32_t k = lane; k < n_in; k += kWave) {
+      const uint32_t src = (uint32_t)a.rec_t_src[e0 + k], edge = a.rec_t_edge[e0 + k];
+      lay.rec_pos[edge] = src * a.Hp + j;
+      lay.col_pos[edge] = k * a.Hp + j;
+      a.col_pair[(size_t)k * a.Hp + j].x = src;
+    }
+  if (lay.ell_src) {  // padding: source 0, edge 0xFFFFFFFF
+    const size_t row = (size_t)j * a.ell_w;
+    for (uint32_t k = lane; k < a.ell_w; k += kWave) {
+      lay.ell_src[row + k] = k < n_in ? a.rec_t_src[e0 + k] : 0;
+      lay.ell_edge[row + k] = k < n_in ? a.rec_t_edge[e0 + k] : 0xFFFFFFFFu;
+    }
+    if (lane == 0) lay.ell_len[j] = n_in;
+  }
+  if (lay.adj_pos) {
+    const uint64_t r0 = a.rec_ptr[j];
+    const uint32_t n_out = (uint32_t)(a.rec_ptr[j + 1] - r0);
+    for (uint32_t k = lane; k < n_out; k += kWave) {
+      lay.adj_pos[r0 + k] = j * a.adj_w + k;
+      a.adj_pair[(size_t)j * a.adj_w + k].x = (uint32_t)a.rec_col[r0 + k];
+    }
+    if (lane == 0) lay.adj_len[j] = n_out;
+  }
 }
 
 // The weights of the sliced adjoint's padded rows: edge e of the CSR order at pos[e].
@@ -2008,8 +2031,8 @@ hipError_t bptt_prepare(const BpttArgs &a) {
   return e;
 }
 
-hipError_t bptt_fill_ell(const BpttArgs &a, int32_t *src, uint32_t *edge, uint32_t *len, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_ell, dim3(blocks_for((uint64_t)a.H * a.ell_w, 256)), dim3(256), 0, s, a, src, edge, len);
+hipError_t bptt_fill_layouts(const BpttArgs &a, const BpttLayouts &lay, hipStream_t s) {
+  hipLaunchKernelGGL(k_fill_layouts, dim3(blocks_for(a.H, 4)), dim3(256), 0, s, a, lay);
   return hipGetLastError();
 }
 

@@ -2174,12 +2174,21 @@ void build_seq(snn_bptt *pl, const uint64_t *rec_ptr, const int32_t *rec_col) {
   snn_network *pool = &pl->pool;
   a.seq_p = p;
   a.seq_max = g_max;
-  a.seq_row = upload(pool, row);
-  a.seq_groups = upload(pool, groups);
-  a.seq_more = upload(pool, more);
   a.seq_more_all = more_all;
-  a.seq_col = upload(pool, col);
-  a.seq_pos = upload(pool, pos);
+  // one array, one copy
+  std::vector<uint32_t> all(row);
+  all.insert(all.end(), groups.begin(), groups.end());
+  all.insert(all.end(), more.begin(), more.end());
+  const size_t at_col = all.size();
+  all.resize(at_col + places / 2);
+  std::memcpy(all.data() + at_col, col.data(), places * sizeof(uint16_t));
+  all.insert(all.end(), pos.begin(), pos.end());
+  const uint32_t *dev = upload(pool, all);
+  a.seq_row = dev;
+  a.seq_groups = dev + n_thr;
+  a.seq_more = a.seq_groups + groups.size();
+  a.seq_col = reinterpret_cast<const uint16_t *>(dev + at_col);
+  a.seq_pos = dev + at_col + places / 2;
   a.seq_w = dev_array<float>(pool, places);
   check(hipMemsetAsync(a.seq_w, 0, places * 4, pool->stream), "clear weights");
   check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
@@ -2236,6 +2245,7 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   a.sbits_t = dev_array<uint64_t>(pool, (size_t)a.T * a.H);
   uint64_t max_deg = 0;
   for (uint32_t j = 0; j < a.H; ++j) max_deg = std::max<uint64_t>(max_deg, rt_ptr[j + 1] - rt_ptr[j]);
+  snn::BpttLayouts lay{};
   a.ell_w = 0;
   a.Hp = (a.H + 255) / 256 * 256;
   a.nw = (a.H + 63) / 64;
@@ -2243,22 +2253,12 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   if (a.events) {
     // dense rows of both weight matrices and the target-major pairs of W_rec
     a.col_w = (uint32_t)max_deg;
-    std::vector<uint32_t> in_pos(nnz_in), rec_pos(nnz_rec), col_pos(nnz_rec);
-    for (uint32_t c = 0; c < a.C; ++c)
-      for (uint64_t e = in_ptr[c]; e < in_ptr[c + 1]; ++e) in_pos[e] = c * a.Hp + (uint32_t)in_col[e];
-    for (uint32_t i = 0; i < a.H; ++i)
-      for (uint64_t e = rec_ptr[i]; e < rec_ptr[i + 1]; ++e) rec_pos[e] = i * a.Hp + (uint32_t)rec_col[e];
-    std::vector<uint2> pair(std::max<size_t>(1, (size_t)a.col_w * a.Hp), make_uint2(0u, 0u));
-    for (uint32_t j = 0; j < a.H; ++j)
-      for (uint64_t x = rt_ptr[j]; x < rt_ptr[j + 1]; ++x) {
-        const uint32_t at = (uint32_t)(x - rt_ptr[j]) * a.Hp + j;
-        pair[at].x = (uint32_t)rt_src[x];
-        col_pos[rt_edge[x]] = at;
-      }
-    a.in_pos = upload(pool, in_pos);
-    a.rec_pos = upload(pool, rec_pos);
-    a.col_pos = upload(pool, col_pos);
-    a.col_pair = upload(pool, pair);
+    a.in_pos = lay.in_pos = dev_array<uint32_t>(pool, nnz_in);
+    a.rec_pos = lay.rec_pos = dev_array<uint32_t>(pool, nnz_rec);
+    a.col_pos = lay.col_pos = dev_array<uint32_t>(pool, nnz_rec);
+    const size_t n_pair = (size_t)a.col_w * a.Hp;
+    a.col_pair = dev_array<uint2>(pool, n_pair);
+    check(hipMemsetAsync(a.col_pair, 0, n_pair * sizeof(uint2), pool->stream), "clear padding");
     const size_t n_in = (size_t)a.C * a.Hp, n_rec = (size_t)a.H * a.Hp;
     a.dense_in = dev_array<float>(pool, n_in);
     a.dense_rec = dev_array<float>(pool, n_rec);
@@ -2272,7 +2272,6 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     check(hipHostMalloc(&out, 3 * sizeof(uint32_t), hipHostMallocPortable), "activity of a pass");
     p->activity = a.act_out = static_cast<uint32_t *>(out);
     p->activity[0] = p->activity[1] = p->activity[2] = 0;
-    check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
   }
   // padded rows of the recurrent weights for the sliced adjoint
   uint64_t max_row = 0;
@@ -2281,20 +2280,11 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   if (a.H <= snn::kSliceMaxNeurons && adj_w * a.H <= snn::kSliceMaxPairs) {
     a.S = (a.B + 7) / 8;
     a.adj_w = (uint32_t)adj_w;
-    std::vector<uint2> pair((size_t)a.H * adj_w, make_uint2(0u, 0u));
-    std::vector<uint32_t> pos(nnz_rec), len(a.H);
-    for (uint32_t i = 0; i < a.H; ++i) {
-      len[i] = (uint32_t)(rec_ptr[i + 1] - rec_ptr[i]);
-      for (uint32_t k = 0; k < len[i]; ++k) {
-        const uint64_t e = rec_ptr[i] + k;
-        pos[e] = (uint32_t)(i * adj_w + k);
-        pair[pos[e]].x = (uint32_t)rec_col[e];
-      }
-    }
-    a.adj_pair = upload(pool, pair);
-    a.adj_pos = upload(pool, pos);
-    a.adj_len = upload(pool, len);
-    check(hipStreamSynchronize(pool->stream), "sync");  // the vectors end here
+    const size_t n_pair = (size_t)a.H * adj_w;
+    a.adj_pair = dev_array<uint2>(pool, n_pair);
+    check(hipMemsetAsync(a.adj_pair, 0, n_pair * sizeof(uint2), pool->stream), "clear padding");
+    a.adj_pos = lay.adj_pos = dev_array<uint32_t>(pool, nnz_rec);
+    a.adj_len = lay.adj_len = dev_array<uint32_t>(pool, a.H);
   }
   build_seq(p, rec_ptr, rec_col);
   check(snn::bptt_prepare(a), "bptt prepare");
@@ -2320,19 +2310,17 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   a.dm = dev_array<float>(pool, (size_t)a.B * a.O);
   a.tmax = dev_array<int32_t>(pool, (size_t)a.B * a.O);
   // ELL copy of the recurrent in-edges for the hidden steps (rows padded to a multiple of
-  // 64, at most 256 wide, and at most 8,192 neurons, whose masks a workgroup stages), made on the
-  // device from the CSR form
+  // 64, at most 256 wide, and at most 8,192 neurons, whose masks a workgroup stages)
   if (nnz_rec && max_deg <= snn::kEllMaxWidth && a.H <= snn::kEllMaxNeurons) {
     a.ell_w = (uint32_t)((max_deg + 63) / 64 * 64);
     const size_t places = (size_t)a.H * a.ell_w;
-    int32_t *src = dev_array<int32_t>(pool, places);
-    uint32_t *edge = dev_array<uint32_t>(pool, places), *len = dev_array<uint32_t>(pool, a.H);
-    check(snn::bptt_fill_ell(a, src, edge, len, pool->stream), "padded in-edges");
-    a.ell_src = src;
-    a.ell_edge = edge;
-    a.ell_len = len;
+    a.ell_src = lay.ell_src = dev_array<int32_t>(pool, places);
+    a.ell_edge = lay.ell_edge = dev_array<uint32_t>(pool, places);
+    a.ell_len = lay.ell_len = dev_array<uint32_t>(pool, a.H);
     a.ell_wt = dev_array<float>(pool, places);
   }
+  // these layouts are made on the device from the CSR forms
+  check(snn::bptt_fill_layouts(a, lay, pool->stream), "weight layouts");
   check(hipStreamSynchronize(pool->stream), "sync after plan");
 }
 

@@ -364,7 +364,15 @@ struct BpttArgs {
 // takes the plan's arguments with w_out (and, backward, w_rec) pointing at the plan's
 // copies w_out_c / w_rec_c, which the prologue fills.
 hipError_t bptt_prepare(const BpttArgs &a);
-hipError_t bptt_fill_ell(const BpttArgs &a, int32_t *src, uint32_t *edge, uint32_t *len, hipStream_t s);
+// The plan's index arrays that follow from the CSR forms (null: not used); col_pair and adj_pair get
+// their sources and targets too.
+struct BpttLayouts {
+  uint32_t *in_pos, *rec_pos, *col_pos;  // event-driven form
+  uint32_t *adj_pos, *adj_len;           // sliced adjoint
+  int32_t *ell_src;                      // padded in-edges
+  uint32_t *ell_edge, *ell_len;
+};
+hipError_t bptt_fill_layouts(const BpttArgs &a, const BpttLayouts &lay, hipStream_t s);
 hipError_t bptt_spike_masks(const BpttArgs &a, hipStream_t s);
 uint64_t bptt_lists(const BpttArgs &a);  // number of event lists, entries held for each
 uint32_t bptt_list_stride();

@@ -202,7 +202,7 @@ class Stage {
 };
 
 // ---- streams -------------------------------------------------------------------------
-// Networks without a caller's stream have one of their own.  Making and destroying one takes
+// Networks, batches and plans without a caller's stream have one of their own.  Making and destroying one takes
 // about 50 us each, so up to kStreamKeep idle ones are kept; snn_memory_cache_release destroys
 // them.
 constexpr size_t kStreamKeep = 8;
@@ -2789,7 +2789,7 @@ snn_status snn_build_batch(const snn_batch_member *nets, uint32_t n_nets, uint32
       if (stream) {
         b->pool.stream = (hipStream_t)stream;
       } else {
-        check(hipStreamCreateWithFlags(&b->pool.stream, hipStreamNonBlocking), "hipStreamCreate");
+        b->pool.stream = stream_take(b->pool.device);
         b->pool.own_stream = true;
       }
       build_batch(b, nets, n_nets, raster_steps);
@@ -2870,7 +2870,7 @@ snn_status snn_bptt_create(const snn_bptt_desc *desc, const uint64_t *in_row_ptr
       if (stream) {
         p->pool.stream = (hipStream_t)stream;
       } else {
-        check(hipStreamCreateWithFlags(&p->pool.stream, hipStreamNonBlocking), "hipStreamCreate");
+        p->pool.stream = stream_take(p->pool.device);
         p->pool.own_stream = true;
       }
       build_bptt(p, in_row_ptr, in_col, rec_row_ptr, rec_col);

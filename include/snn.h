@@ -345,7 +345,8 @@ const char *snn_last_error(const snn_network *net);
  * from the cache (hits) and by hipMalloc (misses) since the process started; NULL
  * outputs are skipped.  snn_memory_cache_release: return the kept blocks of `device`
  * (every device if negative) to HIP, and the free blocks of pinned host memory that spike
- * downloads are staged in (at most four are kept, of at most 32 MiB each), and destroys the
+ * downloads are staged in (at most four are kept, of at most 32 MiB each) and, once no training
+ * plan is left, the 4 KiB ones that their passes leave counts in, and destroys the
  * idle streams kept for the next networks (at most eight).  Neither call touches memory that
  * is in use. */
 snn_status snn_memory_cache_stats(int device, uint64_t *bytes, uint64_t *blocks, uint64_t *hits,

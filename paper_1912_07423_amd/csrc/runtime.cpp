@@ -201,6 +201,47 @@ class Stage {
   StageBlock b_;
 };
 
+// ---- pinned slots ---------------------------------------------------------------------
+// A few numbers each that a plan's passes leave for the host.  Slots come from 4 KiB blocks, as many
+// as the most plans at a time need, and stay mapped when their plan is closed: a pass on a
+// caller's stream may still write one.  snn_memory_cache_release returns the blocks when no
+// plan has a slot, after the device has drained.
+constexpr size_t kSlotBlock = 4096, kSlotBytes = 64;
+std::mutex g_slot_mutex;
+std::vector<unsigned char *> g_slot_blocks;
+std::vector<uint32_t *> g_slots;  // free ones
+
+uint32_t *slot_take() {
+  std::lock_guard<std::mutex> lock(g_slot_mutex);
+  if (g_slots.empty()) {
+    g_slot_blocks.reserve(g_slot_blocks.size() + 1);
+    g_slots.reserve((g_slot_blocks.size() + 1) * (kSlotBlock / kSlotBytes));  // giving back cannot fail
+    void *p = nullptr;
+    check(hipHostMalloc(&p, kSlotBlock, hipHostMallocPortable), "pinned slots");
+    g_slot_blocks.push_back(static_cast<unsigned char *>(p));
+    for (size_t k = kSlotBlock; k > 0; k -= kSlotBytes)
+      g_slots.push_back(reinterpret_cast<uint32_t *>(g_slot_blocks.back() + k - kSlotBytes));
+  }
+  uint32_t *slot = g_slots.back();
+  g_slots.pop_back();
+  std::memset(slot, 0, kSlotBytes);
+  return slot;
+}
+
+void slot_give(uint32_t *slot) {
+  std::lock_guard<std::mutex> lock(g_slot_mutex);
+  g_slots.push_back(slot);
+}
+
+void slot_release() {
+  std::lock_guard<std::mutex> lock(g_slot_mutex);
+  if (g_slot_blocks.empty() || g_slots.size() != g_slot_blocks.size() * (kSlotBlock / kSlotBytes)) return;
+  if (hipDeviceSynchronize() != hipSuccess) return;
+  for (unsigned char *p : g_slot_blocks) (void)hipHostFree(p);
+  g_slot_blocks.clear();
+  g_slots.clear();
+}
+
 // ---- streams -------------------------------------------------------------------------
 // Networks, batches and plans without a caller's stream have one of their own.  Making and destroying one takes
 // about 50 us each, so up to kStreamKeep idle ones are kept; snn_memory_cache_release destroys
@@ -2057,7 +2098,7 @@ struct snn_bptt {
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;  // captured bodies of the two passes
   volatile uint32_t *activity = nullptr;  // of a finished pass (BpttArgs::act_out)
   ~snn_bptt() {
-    if (activity) (void)hipHostFree(const_cast<uint32_t *>(activity));
+    if (activity) slot_give(const_cast<uint32_t *>(activity));
   }
 };
 
@@ -2268,10 +2309,7 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
     a.spk = dev_array<uint64_t>(pool, (size_t)a.B * a.T * a.nw);
     a.lists = dev_array<uint16_t>(pool, snn::bptt_lists(a) * snn::bptt_list_stride());
     a.list_len = dev_array<uint32_t>(pool, snn::bptt_lists(a));
-    void *out = nullptr;
-    check(hipHostMalloc(&out, 3 * sizeof(uint32_t), hipHostMallocPortable), "activity of a pass");
-    p->activity = a.act_out = static_cast<uint32_t *>(out);
-    p->activity[0] = p->activity[1] = p->activity[2] = 0;
+    p->activity = a.act_out = slot_take();
   }
   // padded rows of the recurrent weights for the sliced adjoint
   uint64_t max_row = 0;
@@ -2491,6 +2529,7 @@ snn_status snn_memory_cache_release(int device) {
   return guarded([&] {
     pool_release(device);
     stage_release();
+    slot_release();
     stream_release(device);
   });
 }

@@ -127,3 +127,30 @@ def test_captured_busy_pass():
             assert out.item() == want
             assert p.plan.loss(x, *ws, p.y).item() == want
             s.synchronize()
+
+
+def test_plans_made_and_closed_with_the_caches_released():
+    """Every plan reads its own passes' activity: a new plan starts quiet although a busy one has
+    just been closed, and more plans at once than one block of slots serves keep theirs apart."""
+    from paper_1912_07423_amd.network import memory_cache_release
+    d = _data(8, 20, 20, 400, 2)
+    want = None
+    for release in (False, True, False):
+        p = _Plan(d, theta=0.02)
+        first = p.run(d["x"])
+        assert first[0] == "persistent" and p.plan.route() == "launches"
+        want = want or first
+        _same(first, want)
+        p.plan.close()
+        if release:
+            memory_cache_release()
+    small = _data(2, 4, 6, 20, 2)
+    plans = [_Plan(d, theta=0.02)] + [_Plan(small, theta=10.0) for _ in range(70)]
+    plans[0].run(d["x"])
+    memory_cache_release()
+    assert plans[0].plan.route() == "launches" and all(q.plan.route() == "persistent" for q in plans[1:])
+    _same(plans[0].run(d["x"]), want)
+    for q in plans:
+        q.plan.close()
+    memory_cache_release()
+    _same(_Plan(d, theta=0.02).run(d["x"]), want)

@@ -322,16 +322,19 @@ __global__ __launch_bounds__(256) void k_input_current(BpttArgs a) {
 }
 
 // (a bounded grid that strides over the (t, j) pairs, so that the launch costs little
-// when the flag sends it home; in the event-driven form it also looks the readout weights over)
+// when the flag sends it home; in the event-driven form it also looks the readout weights over,
+// last: an atomic before the sums takes their edge lists off the scalar unit, and the forward
+// pass of 64 x 250 x 700 -> 1,024 with inputs other than 0 and 1 took 4.5 ms instead of 3.1)
 constexpr uint32_t kValuesGrid = 2048;
 __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a, bool busy) {
-  if (a.events)
-    for (uint32_t e = blockIdx.x * 256u + threadIdx.x; e < a.H * a.O; e += gridDim.x * 256u)
-      if (!finite_f32(a.w_out[e])) atomicOr(a.flags + 2, 1u);
-  if (a.flags[0] == 0) return;
   const uint32_t b = lane_id();
   const uint64_t first = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  for (uint64_t w = first; w < (uint64_t)a.T * a.H; w += (uint64_t)gridDim.x * 4) {
+  const uint64_t end = a.flags[0] == 0 ? 0 : (uint64_t)a.T * a.H;
+  // the lane's place in vall, or of slice_index in sg for the busy form
+  float *out = busy ? a.sg + slice_index(a, 0, b, 0) : a.vall + (size_t)b * a.Hp;
+  const size_t step = busy ? (size_t)a.S * a.H * 8 : (size_t)a.B * a.Hp;
+  const uint32_t neuron = busy ? 8 : 1;
+  for (uint64_t w = first; w < end; w += (uint64_t)gridDim.x * 4) {
     const uint32_t t = (uint32_t)(w / a.H), j = (uint32_t)(w % a.H);
     const float *xt = a.xt + (size_t)t * a.C * 64;
     if (!a.events) {
@@ -353,8 +356,11 @@ __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a, bool b
       for (uint32_t u = 0; u < 8; ++u)
         if (e + u < e1) sum = sum + wv[u] * x[u];
     }
-    if (b < a.B) (busy ? a.sg[slice_index(a, t, b, j)] : a.vall[((size_t)t * a.B + b) * a.Hp + j]) = sum;
+    if (b < a.B) out[t * step + j * neuron] = sum;
   }
+  if (a.events)
+    for (uint32_t e = blockIdx.x * 256u + threadIdx.x; e < a.H * a.O; e += gridDim.x * 256u)
+      if (!finite_f32(a.w_out[e])) atomicOr(a.flags + 2, 1u);
 }
 
 // One step t of the hidden layer: one wavefront per hidden neuron j, lane = batch.  The

@@ -51,13 +51,19 @@ __device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uin
 // x [B][T][C] -> xt [T][C][64]; lanes >= B hold zeros.  A workgroup per (step t, block of
 // 64 inputs) reads the 64 batch rows of its block (256 bytes each, coalesced) into LDS and
 // writes the block transposed; a wavefront per input c then also writes that input's
-// batch mask xbits[c][t] (bit b: x != 0) and sets *flag if some value is neither 0 nor 1
-// (k_bits' rule).
-__global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, uint64_t *xbits, uint32_t *flag,
-                                                     uint32_t B, uint32_t T, uint32_t C) {
+// batch mask xbits[c][t] (bit b: x != 0) and sets flags[0] if some value is neither 0 nor 1
+// (k_bits' rule).  Beside that the grid looks over n_out readout weights and sets flags[2] if some
+// are not finite: here the look costs nothing (6.5 us at 19 x 103 x 77 with and without it), in
+// k_input_current_values, which otherwise returns at once, 0.7 us.
+__global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, uint64_t *xbits, uint32_t *flags,
+                                                     uint32_t B, uint32_t T, uint32_t C, const float *w_out,
+                                                     uint32_t n_out) {
   __shared__ float tile[64][65];
   const uint32_t t = blockIdx.y, c0 = blockIdx.x * 64u;
   const uint32_t l = threadIdx.x % 64u, r = threadIdx.x / 64u;
+  bool finite = true;
+  for (uint32_t e = (t * gridDim.x + blockIdx.x) * 256u + threadIdx.x; e < n_out; e += gridDim.x * T * 256u)
+    finite = finite && finite_f32(w_out[e]);
   for (uint32_t b = r; b < 64u; b += 4u)
     tile[b][l] = b < B && c0 + l < C ? x[((uint64_t)b * T + t) * C + c0 + l] : 0.0f;
   __syncthreads();
@@ -70,9 +76,10 @@ __global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, 
     const uint64_t bad = __ballot(on && v != 1.0f);
     if (l == 0) {
       xbits[(size_t)c * T + t] = m;
-      if (bad) atomicOr(flag, 1u);
+      if (bad) atomicOr(flags, 1u);
     }
   }
+  if (!finite) atomicOr(flags + 2, 1u);
 }
 
 // Transposed-order copy of a CSR weight vector: w_t[e] = w[edge[e]].
@@ -322,19 +329,19 @@ __global__ __launch_bounds__(256) void k_input_current(BpttArgs a) {
 }
 
 // (a bounded grid that strides over the (t, j) pairs, so that the launch costs little
-// when the flag sends it home; in the event-driven form it also looks the readout weights over,
-// last: an atomic before the sums takes their edge lists off the scalar unit, and the forward
-// pass of 64 x 250 x 700 -> 1,024 with inputs other than 0 and 1 took 4.5 ms instead of 3.1)
+// when the flag sends it home.  An atomic before the sums would take their edge lists off the
+// scalar unit: a forward pass of 64 x 250 x 700 -> 1,024 with inputs other than 0 and 1 took 4.5
+// ms instead of 3.1.)
 constexpr uint32_t kValuesGrid = 2048;
 __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a, bool busy) {
+  if (a.flags[0] == 0) return;
   const uint32_t b = lane_id();
   const uint64_t first = (uint64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint64_t end = a.flags[0] == 0 ? 0 : (uint64_t)a.T * a.H;
   // the lane's place in vall, or of slice_index in sg for the busy form
   float *out = busy ? a.sg + slice_index(a, 0, b, 0) : a.vall + (size_t)b * a.Hp;
   const size_t step = busy ? (size_t)a.S * a.H * 8 : (size_t)a.B * a.Hp;
   const uint32_t neuron = busy ? 8 : 1;
-  for (uint64_t w = first; w < end; w += (uint64_t)gridDim.x * 4) {
+  for (uint64_t w = first; w < (uint64_t)a.T * a.H; w += (uint64_t)gridDim.x * 4) {
     const uint32_t t = (uint32_t)(w / a.H), j = (uint32_t)(w % a.H);
     const float *xt = a.xt + (size_t)t * a.C * 64;
     if (!a.events) {
@@ -358,9 +365,6 @@ __global__ __launch_bounds__(256) void k_input_current_values(BpttArgs a, bool b
     }
     if (b < a.B) out[t * step + j * neuron] = sum;
   }
-  if (a.events)
-    for (uint32_t e = blockIdx.x * 256u + threadIdx.x; e < a.H * a.O; e += gridDim.x * 256u)
-      if (!finite_f32(a.w_out[e])) atomicOr(a.flags + 2, 1u);
 }
 
 // One step t of the hidden layer: one wavefront per hidden neuron j, lane = batch.  The
@@ -490,8 +494,8 @@ __device__ __forceinline__ size_t row_index(const BpttArgs &a, uint32_t t, uint3
 // recurrent weights, and the target-major pairs of the many-spikes form.
 __global__ void k_scatter_weights(BpttArgs a) {
   const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // k_transpose_x sets flags[0] for inputs other than 0 and 1, k_input_current_values flags[2] for
-  // readout weights that are not finite
+  // k_transpose_x sets flags[0] for inputs other than 0 and 1, flags[2] for readout weights that
+  // are not finite
   if (e < 3) a.flags[e] = 0;
   if (e < a.nnz_in) a.dense_in[a.in_pos[e]] = a.w_in[e];
   if (e < a.nnz_rec) {
@@ -911,20 +915,21 @@ __device__ __forceinline__ uint32_t sample_bits(const uint64_t *words, uint64_t 
   return wave_sum(count);
 }
 
-// The leaky readout's scan (as k_readout_scan) over ro[b][t][o]: block (b, 64 readouts).  Beside it
-// two blocks take the pass's activity, a sample of the inputs and of the hidden spikes, to host
+// The leaky readout's scan (as k_readout_scan) over ro[b][t][o]: block (2 + b, 64 readouts).  Beside
+// it two blocks take the pass's activity, a sample of the inputs and of the hidden spikes, to host
 // memory: what the next pass's way is chosen by.
 __global__ __launch_bounds__(64) void k_readout_scan_events(BpttArgs a, const float *ro) {
-  const uint32_t b = blockIdx.x, o = blockIdx.y * 64u + threadIdx.x;
-  if (b >= a.B) {
+  if (blockIdx.x < 2) {  // (first, so that the other blocks branch without waiting for an argument)
     if (blockIdx.y) return;
-    const uint32_t bits = b == a.B ? sample_bits(a.xbits, (uint64_t)a.C * a.T) : sample_bits(a.spk, (uint64_t)a.B * a.T * a.nw);
+    const uint32_t bits = blockIdx.x == 0 ? sample_bits(a.xbits, (uint64_t)a.C * a.T)
+                                          : sample_bits(a.spk, (uint64_t)a.B * a.T * a.nw);
     if (threadIdx.x == 0) {
-      a.act_out[b - a.B] = bits;
-      if (b == a.B) a.act_out[2] = a.flags[0];
+      a.act_out[blockIdx.x] = bits;
+      if (blockIdx.x == 0) a.act_out[2] = a.flags[0];
     }
     return;
   }
+  const uint32_t b = blockIdx.x - 2, o = blockIdx.y * 64u + threadIdx.x;
   const float *r0 = ro + (size_t)b * a.T * a.O + std::min<uint32_t>(o, a.O - 1);
   float u = 0.0f, m = 0.0f;
   uint32_t tm = 0;
@@ -1833,7 +1838,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, bool busy, h
     const uint64_t nnz = std::max<uint64_t>(std::max(a.nnz_in, a.nnz_rec), 3);
     hipLaunchKernelGGL(k_scatter_weights, dim3(blocks_for(nnz, 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                       a.T, a.C);
+                       a.T, a.C, a.w_out, a.H * a.O);
     if (busy) {
       gather_weights(a, s);
       hipLaunchKernelGGL(k_input_current, dim3(blocks_for((uint64_t)((a.T + kMaskSteps - 1) / kMaskSteps) * a.H, 4)),
@@ -1851,7 +1856,7 @@ hipError_t bptt_forward_prologue(const BpttArgs &a, const float *x, bool busy, h
   // pass of a smooth-mode plan
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, reinterpret_cast<float *>(a.flags), (uint64_t)2, 0.0f);
   hipLaunchKernelGGL(k_transpose_x, dim3((a.C + 63) / 64, a.T), dim3(256), 0, s, x, a.xt, a.xbits, a.flags, a.B,
-                     a.T, a.C);
+                     a.T, a.C, a.w_out, 0u);
   const hipError_t e = hipMemcpyAsync(a.w_out_c, a.w_out, (size_t)a.H * a.O * 4, hipMemcpyDeviceToDevice, s);
   return e != hipSuccess ? e : hipGetLastError();
 }

@@ -230,7 +230,7 @@ snn_status snn_run(snn_network *net, uint32_t n_steps);
                                    network, a workgroup per range of targets.  Taken only where
                                    device memory for its buffers is left: 2 bytes (4 with rows of
                                    65,536 and more) per neuron and range of 64 to 512 targets, up
-                                   to 256 MiB of laid-out rows, and 2 delay + 1 spike lists */
+                                   to 256 MiB of laid-out rows, and up to 2 delay spike lists */
 snn_status snn_get_route(snn_network *net, uint32_t *route);
 
 /* Download of timestamped spikes (Sec. III-B: the simulators compared there let the
@@ -440,9 +440,11 @@ typedef struct {
     uint32_t checkpoint;   /* steps per checkpoint segment, 1..32 */
     float beta, beta_out, theta, slope;
     uint32_t smooth;       /* 0: spiking forward, surrogate backward; 1: smooth forward */
-    uint32_t eager;        /* 0: replay the per-step kernels of each pass from a HIP graph
-                              captured at the plan's first call; 1: launch them one by one
-                              (same kernels, same results) */
+    uint32_t eager;        /* 0: replay the kernels that a pass launches once per step from a HIP
+                              graph captured at their first use; 1: launch them one by one
+                              (same kernels, same results).  Passes without such launches
+                              (snn_bptt_get_route, and the backward pass where the recurrent
+                              synapses fit a compute unit) do not depend on it. */
 } snn_bptt_desc;
 
 /* A plan for one network structure: host CSR arrays (rows = presynaptic neuron, targets

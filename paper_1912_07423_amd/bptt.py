@@ -26,9 +26,11 @@ def _csr(mask):
 
 
 class RecurrentLIF:
-    """Plan (structure + workspace) of the recurrent LIF network on one GPU.  The per-step
-    kernels of each pass are replayed from HIP graphs captured at the first call, or
-    launched one by one with eager=True (same kernels, same results)."""
+    """Plan (structure + workspace) of the recurrent LIF network on one GPU.  Kernels that a
+    pass launches once per step are replayed from HIP graphs captured at their first use, or
+    launched one by one with eager=True (same kernels, same results).  Spiking plans of up to
+    2,048 hidden neurons have none in a forward pass with few spikes (route()), and none in
+    the backward pass where the recurrent synapses fit a compute unit."""
 
     def __init__(self, in_mask, rec_mask, n_out, batch, steps, checkpoint=25, tau_ms=20.0,
                  tau_out_ms=20.0, dt_ms=1.0, theta=1.0, slope=25.0, smooth=False, eager=False,

@@ -1259,7 +1259,7 @@ __device__ __forceinline__ float row_sum(float x) {
 // 16-byte LDS read and four multiply-adds per synapse, and a 16-lane sum completes them.
 // Slices are dealt round-robin over the workgroups, so that with 8 slices each XCD (they
 // take workgroups round-robin too) works on one slice, which its own L2 holds.  A launch and
-// its round trip bound it: 4.9 us per step at 64 x 1,024 with rows of about 102 synapses
+// its round trip bound it: 4.7 us per step at 64 x 1,024 with rows of about 102 synapses
 // (7.4 with a wavefront per neuron that gathers 256-byte rows from memory, the form kept for
 // more neurons), 3.6 us at 19 x 201 (7.7).
 // lam_next / lam_out: slices of steps t + 1 and t; lam_out holds the readout part on entry.
@@ -1334,9 +1334,9 @@ __global__ __launch_bounds__(1024) void k_adjoint_slice(BpttArgs a, const float 
 // synapses so that the 32 lanes that read LDS together meet few bank conflicts, and deals
 // rows to lanes by length, so that a wavefront's lanes carry equally many.  Places without a
 // synapse read a zero that follows the neurons.  One barrier per step; no step waits for a
-// launch: 0.5 us per step at 201 neurons (3.4 launched), 2.5 at 700 with 70 synapses each
+// launch: 0.5 us per step at 201 neurons (3.6 launched), 2.5 at 700 with 70 synapses each
 // (about 4).  104,000 synapses at 1,024 neurons do not fit; a variant that streamed what did
-// not fit from L2 took 6.2 us per step, against 4.5 launched.
+// not fit from L2 took 6.2 us per step, against 4.7 launched.
 constexpr int kSeqState = 4;  // steps of (readout part, surrogate) requested ahead
 template <int kRegs>
 __global__ __launch_bounds__(1024) void k_adjoint_seq(BpttArgs a) {

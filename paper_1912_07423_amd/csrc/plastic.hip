@@ -21,9 +21,9 @@
 // what counts is the number of lines and that all units have the same number to read: 1.4
 // lines per sub-row (weights, a part of a line of targets) in the window launch, two per
 // potentiated synapse (weight, its source's trace) in the prepare launch.  A window of nine
-// steps of 100,000 neurons (2e8 synapses, 130 arriving spikes a step) takes 39 + 62 us with
-// 1.9e6 potentiations, one of 10,000 neurons (45 spikes a step) 17 + 10 us: 7.9 and 3.0 us a
-// step in all, where update, plasticity and delivery launches took 30 and 17.
+// steps of 100,000 neurons (2e8 synapses) takes 34 + 61 us in a trace of 8,300 steps, start-up
+// burst included, one of 10,000 neurons (45 spikes a step) 17 + 9 us; by the clock 14 us a step
+// at 120 spikes a step and 2.9, where update, plasticity and delivery launches take 30 and 16.
 //
 // k_plastic_import and k_plastic_export take the spikes to and from the FIFO ring's form at
 // both ends of a run.

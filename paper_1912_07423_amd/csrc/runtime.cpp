@@ -1211,11 +1211,11 @@ uint32_t window_range(const snn_network *net) {
 // eagerly plastic network with nothing about its delivery chosen by the caller and a delay of
 // at least two steps (a window is at most delay - 1 steps).  Two launches per window against
 // three per step, in us per step: delay 2 (one-step windows) 11.0 against 12.6 with 500
-// neurons, 13.7 against 19.3 with 20,000, 21.2 against 24.1 with 60,000; delay 10, 3.9 against
-// 19.3 with 20,000; delay 15, 2.6 against 14.0 with 4,000 and 9.6 against 24.1 with 60,000.
+// neurons, 13.7 against 19.3 with 20,000, 20.4 against 22.5 with 60,000; delay 10, 3.9 against
+// 19.3 with 20,000; delay 15, 2.6 against 14.0 with 4,000 and 9.1 against 22.7 with 60,000.
 // Every range looks at every arriving spike, so rows of fewer synapses than half the ranges
-// stay with the launches (200,000 neurons with 500 synapses each, 1.3 per range: 30.8 against
-// 43.5), and so does a network whose memory has no room for the windows' index.
+// stay with the launches (200,000 neurons with 500 synapses each, 1.3 per range: 24.7 against
+// 40.8), and so does a network whose memory has no room for the windows' index.
 bool choose_windows(snn_network *net) {
   if (!net->plastic || net->lazy || net->owner || net->delay < 2 || net->n == 0 || net->delivery_chosen ||
       net->prm.window)

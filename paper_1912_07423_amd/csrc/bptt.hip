@@ -42,7 +42,7 @@ __device__ __forceinline__ float surrogate(float z, float slope, bool smooth) {
 
 __device__ __forceinline__ bool finite_f32(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
 
-// With at most kSliceMaxNeurons hidden neurons the membrane adjoint is held in slices of 8
+// Where the plan takes slices (BpttArgs::S) the membrane adjoint is held in slices of 8
 // batch elements, lamv[t][slice][H][8], of which there are S = ceil(B / 8).
 __device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uint32_t b, uint32_t j) {
   return (((size_t)t * a.S + (b >> 3)) * a.H + j) * 8 + (b & 7u);
@@ -1184,7 +1184,6 @@ __global__ __launch_bounds__(256) void k_adjoint_step(BpttArgs a, uint32_t t, co
 // of one readout are two 16-byte reads.  Bound: the store of the result (65 MB for 64 x 250
 // x 1,024).
 constexpr int kReadoutChunk = 32;
-constexpr int kAdjointRows = 32;  // neurons per workgroup, here and in k_adjoint_slice
 // In the event-driven form it also takes the surrogate derivative of its membranes, which
 // come as rows of one batch element each, to the slices (an adjoint step that gathered them
 // itself took 0.8 us longer).
@@ -1261,7 +1260,7 @@ __device__ __forceinline__ float row_sum(float x) {
 // take workgroups round-robin too) works on one slice, which its own L2 holds.  A launch and
 // its round trip bound it: 4.7 us per step at 64 x 1,024 with rows of about 102 synapses
 // (7.4 with a wavefront per neuron that gathers 256-byte rows from memory, the form kept for
-// more neurons), 3.6 us at 19 x 201 (7.7).
+// layers whose workgroups the device does not hold at once), 3.6 us at 19 x 201 (7.7).
 // lam_next / lam_out: slices of steps t + 1 and t; lam_out holds the readout part on entry.
 // v_t: V_t as [H][64], or, in the event-driven form, its surrogate derivative in the slices.
 constexpr int kAdjointAhead = 8;  // rounds of synapses requested before the barrier

@@ -2236,6 +2236,25 @@ void build_seq(snn_bptt *pl, const uint64_t *rec_ptr, const int32_t *rec_col) {
   a.seq_threads = n_thr;
 }
 
+// Whether the sliced adjoint (k_adjoint_slice) is the faster one of plans without the
+// event-driven form.  It is where the device holds a step's workgroups at once; further rounds
+// stage the slices of all neurons again, and a wavefront per neuron (k_adjoint_step) is faster
+// except with few synapses, whose gathers are short.  us per step, spiking, a wavefront per neuron
+// against slices: 256 workgroups of 4,096 neurons 17.2 against 14.1 with rows of 100, 45.5 against
+// 30.3 with 400; 1.1 to 1.5 rounds (2,300 neurons x 64, 3,000 x 24, 4,096 x 24) 12.9 to 14.7 against
+// 11.2 to 13.4 with rows of 20, 12.3 to 14.1 against 11.8 to 14.2 with 30, 11.8 to 13.6 against
+// 12.4 to 14.5 with 40 and 13.8 to 17.0 against 15.7 to 19.1 with 100; 2.9 rounds (3,000 x 64) 13.8
+// against 14.7 with 20 and 14.9 against 22.3 with 100.
+bool slices_fit(const snn::BpttArgs &a) {
+  int device = 0, cus = 0, lds = 0;
+  check(hipGetDevice(&device), "hipGetDevice");
+  check(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device), "CU count");
+  check(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device), "LDS limit");
+  const uint64_t held = (uint64_t)cus * std::min<uint64_t>(2, (uint64_t)lds / (a.H * 32ull));
+  const uint64_t blocks = (uint64_t)((a.B + 7) / 8) * ((a.H + snn::kAdjointRows - 1) / snn::kAdjointRows);
+  return blocks <= held || (blocks <= 2 * held && a.nnz_rec <= 32ull * a.H);
+}
+
 void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, const uint64_t *rec_ptr,
                 const int32_t *rec_col) {
   const snn_bptt_desc &d = p->desc;
@@ -2315,7 +2334,7 @@ void build_bptt(snn_bptt *p, const uint64_t *in_ptr, const int32_t *in_col, cons
   uint64_t max_row = 0;
   for (uint32_t i = 0; i < a.H; ++i) max_row = std::max<uint64_t>(max_row, rec_ptr[i + 1] - rec_ptr[i]);
   const uint64_t adj_w = std::max<uint64_t>(16, (max_row + 15) / 16 * 16);
-  if (a.H <= snn::kSliceMaxNeurons && adj_w * a.H <= snn::kSliceMaxPairs) {
+  if (a.H <= snn::kSliceMaxNeurons && adj_w * a.H <= snn::kSliceMaxPairs && (a.events || slices_fit(a))) {
     a.S = (a.B + 7) / 8;
     a.adj_w = (uint32_t)adj_w;
     const size_t n_pair = (size_t)a.H * adj_w;

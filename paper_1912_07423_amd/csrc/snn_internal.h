@@ -288,6 +288,7 @@ constexpr uint32_t kEllMaxNeurons = 8192;
 // The sliced membrane adjoint: a slice of all neurons (32 bytes each) is staged in LDS, and
 // the synapses are held as padded rows of at most kSliceMaxPairs entries in all.
 constexpr uint32_t kSliceMaxNeurons = 4096;
+constexpr int kAdjointRows = 32;  // neurons per workgroup of the sliced kernels
 // The event-driven forward pass holds the weights as dense rows: at most 2,048 hidden neurons
 // (16 MB of recurrent weights; a presynaptic spike costs a whole row of them) and 64 MB of
 // input weights.

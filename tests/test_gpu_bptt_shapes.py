@@ -113,6 +113,14 @@ def test_no_recurrent_synapses():
     _compare(d, 4)
 
 
+@pytest.mark.parametrize("B,H,degree", [(64, 2080, 28), (64, 2080, 40), (9, 4096, 40), (17, 4096, 20), (17, 4096, 40), (64, 2561, 10)])
+@pytest.mark.parametrize("smooth", [False, True])
+def test_both_adjoints_of_large_layers(B, H, degree, smooth):
+    """One, up to two and more rounds of the slices' workgroups on 256 compute units, with rows on
+    both sides of the line between slices and a wavefront per neuron."""
+    _compare(_inputs(B, 4, 6, H, 2, p_rec=degree / H), 3, smooth=smooth)
+
+
 def test_more_neurons_than_the_sliced_adjoint_holds():
     d = _inputs(3, 6, 10, 4100, 2, p_rec=0.003)
     _compare(d, 4)

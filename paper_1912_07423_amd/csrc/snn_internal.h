@@ -569,6 +569,7 @@ struct snn_network {
   bool solo = false;         // snn_run may step it by the persistent one-workgroup kernel
   double spikes_per_step = -1.0;  // of its latest steps, where the route depends on it (< 0: not known)
   uint64_t rate_at = 0;           // the step at which that was found
+  uint64_t rate_gap = 64;         // steps after which it is counted again
   double noted_spikes = 0.0;      // of downloads since then, and their steps
   uint64_t noted_steps = 0;
   uint32_t lds_limit = 0;    // largest workgroup LDS

@@ -107,3 +107,18 @@ def test_a_network_that_is_faster_at_any_rate_does_not_count():
     a.run(100)
     a.sync()
     assert a.route() == "persistent"
+
+
+def test_a_rate_that_changes_late_is_noticed():
+    """After many counts that confirmed the route, within 4,096 steps."""
+    n = 32001
+    a = _net(_quiet(n, 300), raster_steps=128)
+    for _ in range(60):
+        a.run(100)
+        a.sync()
+    assert a.route() == "persistent"
+    for _ in range(48):
+        a.set_state(v=np.full(n, 100.0, np.float32), ref=np.zeros(n, np.int32))  # all spike
+        a.run(100)
+        a.sync()
+    assert a.route() == "launches"

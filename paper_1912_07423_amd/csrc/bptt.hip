@@ -53,17 +53,14 @@ __device__ __forceinline__ size_t slice_index(const BpttArgs &a, uint32_t t, uin
 // writes the block transposed; a wavefront per input c then also writes that input's
 // batch mask xbits[c][t] (bit b: x != 0) and sets flags[0] if some value is neither 0 nor 1
 // (k_bits' rule).  Beside that the grid looks over n_out readout weights and sets flags[2] if some
-// are not finite: here the look costs nothing (6.5 us at 19 x 103 x 77 with and without it), in
-// k_input_current_values, which otherwise returns at once, 0.7 us.
+// are not finite: here the look costs nothing (6.5 us at 19 x 103 x 77 with and without it; 3 us
+// with 360,000 weights), in k_input_current_values, which otherwise returns at once, 0.7 us.
 __global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, uint64_t *xbits, uint32_t *flags,
                                                      uint32_t B, uint32_t T, uint32_t C, const float *w_out,
                                                      uint32_t n_out) {
   __shared__ float tile[64][65];
   const uint32_t t = blockIdx.y, c0 = blockIdx.x * 64u;
   const uint32_t l = threadIdx.x % 64u, r = threadIdx.x / 64u;
-  bool finite = true;
-  for (uint32_t e = (t * gridDim.x + blockIdx.x) * 256u + threadIdx.x; e < n_out; e += gridDim.x * T * 256u)
-    finite = finite && finite_f32(w_out[e]);
   for (uint32_t b = r; b < 64u; b += 4u)
     tile[b][l] = b < B && c0 + l < C ? x[((uint64_t)b * T + t) * C + c0 + l] : 0.0f;
   __syncthreads();
@@ -79,6 +76,10 @@ __global__ __launch_bounds__(256) void k_transpose_x(const float *x, float *xt, 
       if (bad) atomicOr(flags, 1u);
     }
   }
+  bool finite = true;
+#pragma unroll 8
+  for (uint32_t e = (t * gridDim.x + blockIdx.x) * 256u + threadIdx.x; e < n_out; e += gridDim.x * T * 256u)
+    finite &= finite_f32(w_out[e]);
   if (!finite) atomicOr(flags + 2, 1u);
 }
 
@@ -907,11 +908,20 @@ __global__ __launch_bounds__(64) void k_readout_masks(BpttArgs a, float *ro) {
     for (uint32_t q = 0; q <= last; ++q) ro[((size_t)b * a.T + t) * a.O + o0 + q] = acc[q];
 }
 
-// Set bits of kActSamples words at scattered places of an array of n, by a wavefront.
+// Set bits of kActSamples words of an array of n, by a wavefront: eight words at each of a number
+// of scattered places, as a compute unit has some 64 line reads in flight, and in few
+// instructions, which all come from memory (in two kilobytes of them the sample took longer than
+// the scan of a short pass).
 __device__ __forceinline__ uint32_t sample_bits(const uint64_t *words, uint64_t n) {
+  constexpr uint32_t kEach = kActSamples / kWave;
+  const uint32_t most = (uint32_t)std::min<uint64_t>(n, 8), places = (uint32_t)std::min<uint64_t>(n, UINT32_MAX) - most + 1;
+  const uint64_t *own = words + std::min<uint32_t>(lane_id() & 7u, most - 1);
+  uint64_t w[kEach];
+#pragma unroll
+  for (uint32_t k = 0; k < kEach; ++k) w[k] = own[__umulhi((k * 8u + (lane_id() >> 3)) * 0x9E3779B9u, places)];
   uint32_t count = 0;
-#pragma unroll 16
-  for (uint32_t e = lane_id(); e < kActSamples; e += kWave) count += (uint32_t)__popcll(words[((uint64_t)(e * 0x9E3779B9u) * n) >> 32]);
+#pragma unroll
+  for (uint32_t k = 0; k < kEach; ++k) count += (uint32_t)__popcll(w[k]);
   return wave_sum(count);
 }
 
@@ -921,8 +931,8 @@ __device__ __forceinline__ uint32_t sample_bits(const uint64_t *words, uint64_t 
 __global__ __launch_bounds__(64) void k_readout_scan_events(BpttArgs a, const float *ro) {
   if (blockIdx.x < 2) {  // (first, so that the other blocks branch without waiting for an argument)
     if (blockIdx.y) return;
-    const uint32_t bits = blockIdx.x == 0 ? sample_bits(a.xbits, (uint64_t)a.C * a.T)
-                                          : sample_bits(a.spk, (uint64_t)a.B * a.T * a.nw);
+    const bool in = blockIdx.x == 0;
+    const uint32_t bits = sample_bits(in ? a.xbits : a.spk, in ? (uint64_t)a.C * a.T : (uint64_t)a.B * a.T * a.nw);
     if (threadIdx.x == 0) {
       a.act_out[blockIdx.x] = bits;
       if (blockIdx.x == 0) a.act_out[2] = a.flags[0];

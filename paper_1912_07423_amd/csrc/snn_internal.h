@@ -302,7 +302,7 @@ constexpr int kSeqRegs = 48;
 constexpr uint32_t kSeqGroupBytes = 24;
 constexpr uint32_t kSeqMaxMore = 98;
 constexpr uint64_t kSliceMaxPairs = 1ull << 26;
-constexpr uint32_t kActSamples = 4096;  // words that a pass's activity is estimated from
+constexpr uint32_t kActSamples = 1024;  // words that a pass's activity is estimated from
 struct BpttArgs {
   uint32_t B, T, C, H, O, K;
   uint32_t events;             // event-driven forward pass (spiking mode); then also:

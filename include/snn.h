@@ -213,8 +213,8 @@ snn_status snn_step(snn_network *net);
  * of up to `window` steps and replayed from a captured HIP graph where possible; a small
  * static network without drive whose delivery is left to AUTO (and whose window, tiles,
  * block and grid are 0) is stepped by one persistent launch instead where that is the faster
- * way at its rate (where the rate decides, the way that risks less serves until snn_sync,
- * snn_get_info or snn_get_raster has counted spikes), and an eagerly plastic
+ * way at its rate (where the rate decides, its first 512 steps take that launch and later ones
+ * the way that risks less until snn_sync, snn_get_info or snn_get_raster has counted spikes), and an eagerly plastic
  * one (delay of at least two steps, the same parameters 0) in windows of up to delay - 1
  * steps by two launches each (snn_get_route).  The
  * result is identical to n_steps calls of snn_step.  Asynchronous.  SNN_E_STATE for a

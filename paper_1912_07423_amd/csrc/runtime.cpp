@@ -1138,14 +1138,28 @@ double expected_spikes(const snn_network *net) {
   return net->spikes_per_step >= 0.0 ? net->spikes_per_step : spikes_at(net, kHighHz);
 }
 
-// Whether snn_run takes the persistent kernel now.  Before the rate is known, it does where that
-// loses less at 100 Hz than the launches lose at 15 Hz: by this model 20,000 neurons with 400
-// synapses each 1.5 times against 2.0, 32,000 with 640 2.8 times against 1.2.
+// Steps for which the persistent kernel serves whatever the rate: enough for what a program runs
+// before it first looks, some milliseconds where the launches were the faster way (32,000
+// neurons with 640 synapses each at 40 Hz: 3.4 ms lost, at 3 Hz 2.6 ms gained).
+constexpr uint64_t kGuessSteps = 512;
+
+// Whether snn_run takes the persistent kernel now.  Before the rate is known, and after the first
+// steps, it does where that loses less at 100 Hz than the launches lose at 15 Hz: by this model
+// 20,000 neurons with 400 synapses each 1.5 times against 2.0, 32,000 with 640 2.8 times against
+// 1.2.
+bool risks_less(const snn_network *net) {
+  const double low = spikes_at(net, kLowHz), high = spikes_at(net, kHighHz);
+  return solo_us(net, high) / launches_us(net, high) <= launches_us(net, low) / solo_us(net, low);
+}
 bool solo_now(const snn_network *net) {
   if (!net->solo || !rate_matters(net)) return net->solo;
-  const double known = net->spikes_per_step, low = spikes_at(net, kLowHz), high = spikes_at(net, kHighHz);
-  if (known >= 0.0) return solo_us(net, known) <= launches_us(net, known);
-  return solo_us(net, high) / launches_us(net, high) <= launches_us(net, low) / solo_us(net, low);
+  if (net->spikes_per_step < 0.0) return net->t_host < kGuessSteps || risks_less(net);
+  return solo_us(net, net->spikes_per_step) <= launches_us(net, net->spikes_per_step);
+}
+// Steps of the persistent kernel until the route is to be looked at again.
+uint64_t solo_steps(const snn_network *net, uint64_t n_steps) {
+  if (!rate_matters(net) || net->spikes_per_step >= 0.0 || risks_less(net)) return n_steps;
+  return std::min(n_steps, kGuessSteps - net->t_host);
 }
 
 // Steps a rate is taken over.
@@ -1391,8 +1405,12 @@ uint32_t route(const snn_network *net) {
 }
 
 void run(snn_network *net, uint64_t n_steps) {
+  if (n_steps > 1 && route(net) == SNN_ROUTE_PERSISTENT) {
+    const uint64_t steps = solo_steps(net, n_steps);
+    run_solo(net, steps);
+    n_steps -= steps;
+  }
   const uint32_t way = n_steps > 1 ? route(net) : SNN_ROUTE_LAUNCHES;
-  if (way == SNN_ROUTE_PERSISTENT) return run_solo(net, n_steps);
   if (way == SNN_ROUTE_WINDOWS) {
     for (; n_steps > 0 && net->t_host < net->windows_from; --n_steps) issue_window(net, 1);
     if (n_steps > 0) run_windows(net, n_steps);
@@ -1513,9 +1531,9 @@ void download_pairs(snn_network *net, uint64_t t0, uint64_t t1, uint32_t *steps,
   sync(net);
   const uint64_t count = *a.count;
   *n_spikes = count;
-  if (t1 == net->t_host && t1 > net->rate_at) note_spikes(net, count, t1 - t0);
   if (count > capacity) fail(SNN_E_OVERFLOW, "raster holds " + std::to_string(count) + " spikes");
   if (count && (!steps || !ids)) fail(SNN_E_INVALID, "null output arrays");
+  if (t1 == net->t_host && t1 > net->rate_at) note_spikes(net, count, t1 - t0);
   for (uint64_t lo = 0; lo < count; lo += piece) {
     if (lo) {
       a.out_lo = lo;

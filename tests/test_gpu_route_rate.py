@@ -1,7 +1,7 @@
 """The route of a small static network follows its rate where the rate decides which way is the
-faster: the way that risks less until a call that waits for the device has counted spikes, the
-persistent kernel at a low rate, the launches at a high one, and back; the results do not depend
-on it."""
+faster.  Until a call that waits for the device has counted spikes, the first 512 steps take the
+persistent kernel and later ones the way that risks less; then the persistent kernel serves at a
+low rate, the launches at a high one, and back.  The results do not depend on it."""
 import numpy as np
 import pytest
 
@@ -55,14 +55,13 @@ def _advance(nets, steps):
 
 
 @pytest.mark.parametrize("how", ["sync", "info", "spikes"])
-@pytest.mark.parametrize("n,degree,first", [(16000, 320, "persistent"), (24000, 200, "persistent"), (32001, 300, "launches"),
-                                            (40700, 60, "launches")])
-def test_route_follows_the_rate(n, degree, first, how):
+@pytest.mark.parametrize("n,degree", [(16000, 320), (24000, 200), (32001, 300), (40700, 60)])
+def test_route_follows_the_rate(n, degree, how):
     print(f"[route] n={n} degree={degree} {how}", flush=True)
     a, b = _net(_spec(n, degree, 60.0), raster_steps=128), _net(_spec(n, degree, 60.0), raster_steps=128, delivery="atomic")
-    assert a.route() == first  # nothing counted yet
+    assert a.route() == "persistent"  # nothing counted yet
     _advance((a, b), 100)
-    assert a.route() == first
+    assert a.route() == "persistent"
     _know(a, how)
     assert a.route() == "launches"  # some 100 Hz
     # refractory for 200 steps: no spikes
@@ -95,12 +94,24 @@ def test_large_persistent_networks_equal_the_pipeline(n, degree):
 
 
 def test_downloads_of_few_steps_add_up():
-    a = _net(_quiet(32001, 300), raster_steps=64)
+    a = _net(_spec(32001, 300, 60.0), raster_steps=64)
     for k in range(7):
-        assert a.route() == "launches"
+        assert a.route() == "persistent"
         a.run(10)
         a.spikes(10 * k, 10 * k + 10)
-    assert a.route() == "persistent"
+    assert a.route() == "launches"
+
+
+@pytest.mark.parametrize("n,degree,then", [(24000, 200, "persistent"), (32001, 300, "launches")])
+@pytest.mark.parametrize("steps", [(512,), (511, 2), (513,), (700,)])
+def test_first_steps(n, degree, then, steps):
+    """Around the 512th step and across it, nothing counted."""
+    a, b = _net(_spec(n, degree, 60.0), raster_steps=128), _net(_spec(n, degree, 60.0), raster_steps=128, delivery="atomic")
+    for k in steps:
+        assert a.route() == "persistent"
+        _advance((a, b), k)
+    assert a.route() == then
+    _same(a, b)
 
 
 def test_a_network_that_is_faster_at_any_rate_does_not_count():
